@@ -233,6 +233,14 @@ __device__ __forceinline__ float rows_sum(float v) {
   return v;
 }
 
+// maximum over the four lanes that differ in lane >> 4
+__device__ __forceinline__ float rows_max(float v) {
+  float a, b;
+  xor16_pair(v, &a, &b); v = fmaxf(a, b);
+  xor32_pair(v, &a, &b); v = fmaxf(a, b);
+  return v;
+}
+
 // LDS-visible ordering inside one wavefront (no workgroup barrier needed: DS
 // instructions of a wavefront execute in order).
 __device__ __forceinline__ void wave_lds_sync() {
@@ -987,7 +995,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
     for (int w = 0; w < NWB; ++w) {
       const float mw = ml_lds[w][gg][0];
-      const float a = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      const float a = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
       acc += a * o_lds[w][gg][c];
       L += a * ml_lds[w][gg][1];
     }
@@ -1020,93 +1028,92 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   }
   __syncthreads();
   if (!is_last) return;
-  static_assert(NWB * 4 * D >= 4 * 256, "o_lds too small for the merge weights");
-  static_assert(NWB >= 4, "one wavefront per head merges the splits");
-  float* w_lds = &o_lds[0][0][0];              // [4][256] weights, o_lds is free again
-  // Wavefront w merges head w.  The partials are read past the caches (device-
-  // coherent loads), 16 bytes per lane so that the address unit sees few, wide
-  // instructions, and all of them are issued before anything is consumed: the merge
-  // then costs about one memory round trip.
-  if (wave < P.hb) {
-    constexpr int PR = D + 4;                    // floats per partial row
-    constexpr int C4 = D / 4;                    // 16-byte chunks per row
-    constexpr int RPI = 64 / C4;                 // rows covered by one wave-level load
-    constexpr int PASS = 32;                     // splits per pass
-    constexpr int NI = PASS / RPI;               // loads per pass
-    const int rows = P.splits;
-    const int64_t gstride = (int64_t)P.gh * PR;  // floats between consecutive splits
-    const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + wave) * PR;
-    // buffer descriptor over this head's rows of all splits: out-of-range lanes read 0
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(gbase), 0, (int)(((int64_t)(rows - 1) * gstride + PR) * 4), 0x00020000);
-    const int r = lane / C4, c4 = lane % C4;
-    const int oob = 0x7FFFFFF0;
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 ml[4];
+  // All wavefronts merge: those with wave % hb == h share the rows (splits) of head h.  (One wavefront per head, with
+  // NWB / hb times the loads and sums in a row, took 0.8 us longer from the ticket to the end at 32 splits.)  The
+  // partials are read past the caches (device-coherent loads), 16 bytes per lane so that the address unit sees few,
+  // wide instructions, and all of them are issued before anything is consumed: the merge then costs about one
+  // memory round trip.
+  static_assert(NWB % 4 == 0, "every head gets the same number of wavefronts");
+  constexpr int PR = D + 4;                    // floats per partial row
+  constexpr int C4 = D / 4;                    // 16-byte chunks per row
+  constexpr int RPI = 64 / C4;                 // rows covered by one wave-level load
+  constexpr int NI = 8;                        // loads in flight
+  static_assert(64 % RPI == 0, "the rows of one load have their weights in one register");
+  const int head = wave % P.hb, part = wave / P.hb, parts = NWB / P.hb;
+  const int rows = P.splits;
+  const int64_t gstride = (int64_t)P.gh * PR;  // floats between consecutive splits
+  const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + head) * PR;
+  // buffer descriptor over this head's rows of all splits: out-of-range lanes read 0
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(gbase), 0, (int)(((int64_t)(rows - 1) * gstride + PR) * 4), 0x00020000);
+  const int r = lane / C4, c4 = lane % C4;
+  const int oob = 0x7FFFFFF0;
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 ml[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int sidx = lane + 64 * k;
-      ml[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, sidx < rows ? (int)((sidx * gstride + D) * 4) : oob, 0, 16);
-    }
-    u32x4 ov[NI];
+  for (int k = 0; k < 4; ++k) {
+    const int sidx = lane + 64 * k;
+    ml[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, sidx < rows ? (int)((sidx * gstride + D) * 4) : oob, 0, 16);
+  }
+  u32x4 ov[NI];
+  auto load_rows = [&](int i0) {               // the i0-th .. (i0 + NI - 1)-th load of this wavefront
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int sidx = i * RPI + r;
+      const int sidx = ((i0 + i) * parts + part) * RPI + r;
       ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (r < RPI && sidx < rows) ? (int)((sidx * gstride + 4 * c4) * 4) : oob, 0, 16);
     }
-    float m[4], l[4];
+  };
+  load_rows(0);
+  float w[4], mx = -INFINITY, ls = 0.f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const bool live = lane + 64 * k < rows;
-      m[k] = live ? __uint_as_float(ml[k][0]) : -INFINITY;
-      l[k] = live ? __uint_as_float(ml[k][1]) : 0.f;
+  for (int k = 0; k < 4; ++k) {
+    w[k] = lane + 64 * k < rows ? __uint_as_float(ml[k][0]) : -INFINITY;
+    mx = fmaxf(mx, w[k]);
+  }
+  mx = rows_max(row_max(mx));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    w[k] = w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[k] - mx);
+    ls += w[k] * __uint_as_float(ml[k][1]);    // (0 * 0 past the last row)
+  }
+  ls = rows_sum(row_sum(ls));
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0;;) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int s0 = ((i0 + i) * parts + part) * RPI;
+      const float wk = s0 < 64 ? w[0] : s0 < 128 ? w[1] : s0 < 192 ? w[2] : w[3];
+      const float ws = __shfl(wk, (s0 + r) & 63);
+      const float wi = (r < RPI && s0 + r < rows) ? ws : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, __uint_as_float(ov[i][e]), acc[e]);
     }
-    float mx = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+    i0 += NI;
+    if (i0 * parts * RPI >= rows) break;
+    load_rows(i0);
+  }
+  // add the RPI row classes (lanes c4, c4 + C4, ...), then the parts, in LDS (o_lds is free again)
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    float ls = 0.f;
+  for (int e = 0; e < 4; ++e) {
+    float t = acc[e];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float w = m[k] == -INFINITY ? 0.f : exp2f(m[k] - mx);
-      w_lds[wave * 256 + lane + 64 * k] = w;
-      ls += w * l[k];
+    for (int k = 1; k < RPI; ++k) t += __shfl(acc[e], (lane + k * C4) & 63);
+    acc[e] = t;
+  }
+  float* sum = &o_lds[0][0][0];                // [part][head][D]
+  if (lane < C4) *reinterpret_cast<float4*>(sum + (part * P.hb + head) * D + 4 * c4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  if (part == 0 && lane == 0) ml_lds[0][head][1] = ls;
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < P.hb * D / 2; idx += 64 * NWB) {
+    float2 t = *reinterpret_cast<const float2*>(sum + 2 * idx);
+    for (int k = 1; k < parts; ++k) {
+      const float2 x = *reinterpret_cast<const float2*>(sum + k * P.hb * D + 2 * idx);
+      t.x += x.x; t.y += x.y;
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) ls += __shfl_xor(ls, o);
-    wave_lds_sync();
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0;;) {
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int sidx = s0 + i * RPI + r;
-        const float w = (r < RPI && sidx < rows) ? w_lds[wave * 256 + sidx] : 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, __uint_as_float(ov[i][e]), acc[e]);
-      }
-      s0 += PASS;
-      if (s0 >= rows) break;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int sidx = s0 + i * RPI + r;
-        ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (r < RPI && sidx < rows) ? (int)((sidx * gstride + 4 * c4) * 4) : oob, 0, 16);
-      }
-    }
-    // add the RPI row classes: lanes c4, c4 + C4, ...
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = acc[e];
-#pragma unroll
-      for (int k = 1; k < RPI; ++k) t += __shfl(acc[e], (lane + k * C4) & 63);
-      acc[e] = t;
-    }
-    if (lane < C4) {
-      const float inv = 1.0f / ls;
-      uint16_t* o = P.out + ((int64_t)bh * P.gh + hsub * P.hb + wave) * D + 4 * c4;
-      const uint32_t lo = (uint32_t)f2t<BF16>(acc[0] * inv) | ((uint32_t)f2t<BF16>(acc[1] * inv) << 16);
-      const uint32_t hi = (uint32_t)f2t<BF16>(acc[2] * inv) | ((uint32_t)f2t<BF16>(acc[3] * inv) << 16);
-      *reinterpret_cast<uint2*>(o) = make_uint2(lo, hi);
-    }
+    const float inv = 1.0f / ml_lds[0][2 * idx / D][1];
+    *reinterpret_cast<uint32_t*>(P.out + ((int64_t)bh * P.gh + hsub * P.hb) * D + 2 * idx) =
+        (uint32_t)f2t<BF16>(t.x * inv) | ((uint32_t)f2t<BF16>(t.y * inv) << 16);
   }
 }
 
