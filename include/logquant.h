@@ -257,7 +257,8 @@ typedef struct {
   int32_t blocks;           /* workgroups of the attention kernel                    */
   int32_t waves_per_block;
   int32_t splits;           /* context splits per (batch row, kv head)               */
-  int32_t fp_waves;         /* of splits*waves_per_block waves, those on the fp rows */
+  int32_t fp_waves;         /* the fp rows' share of the work, in whole wavefronts of
+                               the splits*waves_per_block of a head group            */
   int64_t bytes_read;       /* cache bytes one call must read (codes, scales,
                                zero-points, fp rows of live slots)                   */
 } lq_plan;

@@ -16,8 +16,8 @@ static int env_int(const char* name, int dflt) {
   return v && *v ? atoi(v) : dflt;
 }
 
-// Launch shape: wavefronts per workgroup (12, 8 or 4), context splits per (b, kv head,
-// head group), and the share of wavefronts that walks the fp rows.  Work is counted
+// Launch shape: wavefronts per workgroup (12, 8 or 4) and context splits per (b, kv head,
+// head group).  Work is counted
 // in units of one 64-slot quantized tile; a 32-row fp unit weighs its bytes relative
 // to that.  A compute unit holds eight wavefronts of this kernel, i.e. one
 // workgroup of 8 or two of 4; the candidate shapes are ranked by
@@ -30,15 +30,14 @@ static double fp_unit_weight(const Shape& s) {
   return fp_unit_bytes / q_tile_bytes;
 }
 
-// Wavefronts for the fp rows: units of 32 rows are dealt out statically (a wavefront
-// takes every nwf-th unit), the quantized tiles are shared by the others.  Pick the
-// count that minimises the longer of the two sides, whole units per fp wavefront
-// counted (with 16 units, 9 wavefronts are no better than 8: some still take two).
+// The fp rows' share of the wavefronts, as the plan reports it: the number that, given
+// every unit of 32 rows, would be done when the others are done with the tiles (whole
+// units counted).  The kernel deals units and tiles to the same wavefronts.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
   const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
   if (TF == 0) return 0;
   if (TQ == 0) return NW;
-  const double r = fp_unit_weight(s);   // (measured: halving or doubling this weight changes nothing on the five workloads)
+  const double r = fp_unit_weight(s);
   int best = 1;
   double best_t = 1e300;
   const int hi = TF < NW - 1 ? TF : NW - 1;
