@@ -339,16 +339,18 @@ static SeqState seq_entry(const Shape& s, int n_fp, int n_q, int cur) {
   return e;
 }
 
-// Plan for the longest sequence; bytes over all of them.
+// Plan for the longest sequence; bytes over all of them, the fp share of the wavefronts for each.
 static void plan_seq(const Shape& s, const int* n_fp, const int* n_q, lq_plan* plan, SeqState* st) {
   int mf = 0, mq = 0;
   for (int b = 0; b < s.B; ++b) { if (n_fp[b] > mf) mf = n_fp[b]; if (n_q[b] > mq) mq = n_q[b]; }
   plan_decode(s, mf, mq, plan, true);
+  const int NW = plan->splits * plan->waves_per_block;
   int64_t bytes = 0;
   Shape one = s;
   one.B = 1;
   for (int b = 0; b < s.B; ++b) {
     bytes += cache_bytes_read(one, n_fp[b], n_q[b]);
+    if (st) st[b].nwf = fp_wave_share(s, NW, n_fp[b], n_q[b]);
   }
   plan->bytes_read = bytes;
   if (st) {   // rows by decreasing work (stable: equal rows keep their order)

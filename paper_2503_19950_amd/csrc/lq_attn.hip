@@ -16,6 +16,11 @@ static int env_int(const char* name, int dflt) {
   return v && *v ? atoi(v) : dflt;
 }
 
+int compute_units() {
+  static const int cus = env_int("LOGQUANT_ATTN_CUS", 256);
+  return cus;
+}
+
 // Launch shape: wavefronts per workgroup (12, 8 or 4) and context splits per (b, kv head,
 // head group).  Work is counted
 // in units of one 64-slot quantized tile; a 32-row fp unit weighs its bytes relative
@@ -32,7 +37,8 @@ static double fp_unit_weight(const Shape& s) {
 
 // The fp rows' share of the wavefronts, as the plan reports it: the number that, given
 // every unit of 32 rows, would be done when the others are done with the tiles (whole
-// units counted).  The kernel deals units and tiles to the same wavefronts.
+// units counted).  The kernel keeps to it
+// where the context is split and the schedule static; else wavefronts take both.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
   const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
   if (TF == 0) return 0;
@@ -55,7 +61,7 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, bool per_sequ
   const double units = TQ + r * TF;
   const int hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
   const int groups = s.B * s.Hkv * (s.gh / hb);
-  static const int cus = env_int("LOGQUANT_ATTN_CUS", 256);
+  const int cus = compute_units();
   static const int force_wpb = env_int("LOGQUANT_ATTN_WPB", 0);
   static const int force_splits = env_int("LOGQUANT_ATTN_SPLITS", 0);
   const double fixed = 2.5, per_split = 0.02, merge_tail = 1.5;

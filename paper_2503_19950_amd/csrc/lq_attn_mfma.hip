@@ -77,7 +77,8 @@ struct AttnParams {
   const SeqState* seq;    // device array of per-sequence state (seq_mode 2)
   int seq_mode;           // 0: counts below hold for every sequence; 1: state in the kernel arguments
   int Hkv;
-  int cap, qcap, n_fp, n_q, gh, hb, splits;
+  int cap, qcap, n_fp, n_q, gh, hb, splits, nwf;
+  int cus;            // compute units the launch was planned for
   int W, Wq;          // of every Wq quantized slots (one filtering event) the first W hold tokens
   int n_tok_q;        // tokens in the n_q quantized slots
   int dynamic;        // 0: static tile schedule only
@@ -410,12 +411,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 
   // counts and live fp buffer: the same for every sequence, or (per-sequence lengths)
   // read from the sequence's entry of the state array
-  int n_fp = P.n_fp, n_q = P.n_q, n_tok_q = P.n_tok_q, cur = 0;
+  int n_fp = P.n_fp, n_q = P.n_q, nwf = P.nwf, n_tok_q = P.n_tok_q, cur = 0;
   if constexpr (GENERAL) {
     if (P.seq_mode) {
       const SeqState sq = P.seq_mode == 1 ? seq_load(seq_in_args(args_offset_after(sizeof(AttnParams))), bh / P.Hkv)
                                           : P.seq[bh / P.Hkv];
-      n_fp = sq.n_fp; n_q = sq.n_q; n_tok_q = sq.n_tok_q; cur = sq.cur;
+      n_fp = sq.n_fp; n_q = sq.n_q; nwf = sq.nwf; n_tok_q = sq.n_tok_q; cur = sq.cur;
     }
   }
   // (a select between two kernel arguments, not a load that depends on `cur`)
@@ -425,7 +426,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   const uint16_t* k_fp = k_fp_w;
   const uint16_t* v_fp = v_fp_w;
   const int TQ = (n_q + 63) >> 6, TF = (n_fp + 31) >> 5;
-  // ---- schedule.  Every wavefront first takes its units of fp rows, if it has any, then quantized tiles, with
+  // ---- schedule.  A wavefront first takes its units of fp rows, if it has any, then quantized tiles, with
   // one softmax state for both.  (With a share of the wavefronts kept for the fp rows, those were done long before
   // the others - after 40 of 240 us at 32768 tokens x 16 rows x 32 kv heads - and idled.)  The wavefronts of a head
   // group are numbered across its workgroups, so that the units, fewer than wavefronts when the context is split,
@@ -436,28 +437,26 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   // Long contexts: tiles are dealt out dynamically (see "Tile schedule" below); the wavefronts with a unit join in
   // when they are done with it.
   const bool dyn = P.dynamic && NS > 1 && NWQ > NSUB && TQ >= 5 * NWQ;
-  // Otherwise the schedule is static, hence reproducible.  Each split gets a range of tiles, [lo, hi), such that
-  // tiles and units together are the same number of bytes for all of them (R64: bytes of a unit in 1/64 tiles; the
-  // boundary grows with the split: where the units of the splits before alone exceed the share, it is clamped to 0)
-  int lo = 0, hi = TQ;
-  const int units = split < TF ? (TF - 1 - split) / NS + 1 : 0;   // of this split
-  if (!dyn && NS > 1) {
-    constexpr int TILE_BYTES = 64 * (D * BITS / 4 + 4 * NGC) + 256 * D / G, UNIT_BYTES = 128 * D;
-    constexpr int R64 = (64 * UNIT_BYTES + TILE_BYTES / 2) / TILE_BYTES;
-    const uint32_t all = 64u * TQ + (uint32_t)R64 * TF, per = all / NS, rem = all % NS;
-    auto first_tile = [&](int s) {
-      const int units_before = TF / NS * s + min(s, TF % NS);
-      return max(0, (int)(per * s + rem * s / NS) - R64 * units_before) >> 6;
-    };
-    lo = first_tile(split);
-    hi = first_tile(split + 1);
-  }
-  // and its wavefronts take the tiles of the range in turn.  When the units do not come out even, the nl wavefronts
-  // with one unit less are a round of tiles ahead of the nh others: a unit takes about as long as a tile (its loads
-  // are issued together, so it is latency for both; a lead of 0, 2 or 3 rounds measured 0 to 2% slower).
-  const int nh = units % NWB, nl = NWB - nh;
-  int lead = !dyn && nh > 0 && wave >= nh ? 1 : 0;
-  const int first = dyn ? wi - nfw : lo + (nh == 0 ? wave : wave >= nh ? wave - nh : 2 * nl + wave);
+  // Otherwise the schedule is static, hence reproducible.  With a single split the wavefronts of the workgroup take
+  // units and tiles in turn; when the units do not come out even, the nl wavefronts with one unit less are a round of
+  // tiles ahead of the nh others (a unit takes about as long as a tile: a lead of 0 or 2 rounds measured 1 to 2% slower).
+  // With several splits and few tiles for each wavefront a share of them, nwf, keeps to the units: a unit before the
+  // tiles is a load latency more for its wavefront (8 rows of 8192 tokens: 18.7 instead of 18.1 us).
+  const bool apart = !dyn && NS > 1;
+  const int gw = split * NWB + wave, nh = TF % NWB, nl = NWB - nh;
+  const int unit0 = !apart ? wi : gw < nwf ? gw : TF, unit_step = apart ? nwf : NW;
+  const int hi = TQ, tile_step = apart ? NW - nwf : NWB;
+  int lead = NS == 1 && nh > 0 && wave >= nh ? 1 : 0;
+  const int first = apart ? (gw < nwf ? TQ : gw - nwf) : dyn ? wi - nfw : nh == 0 ? wave : wave >= nh ? wave - nh : 2 * nl + wave;
+  // Of wavefronts that share a SIMD the older one wins the issue slots: with two to a SIMD and a static schedule the
+  // younger ones ended 25% later (165 against 212 us at 16 rows x 32 kv heads x 32768 tokens), the last part with the
+  // SIMD to themselves and too few loads in flight.  So the younger ones - the upper four of a workgroup of 8; of
+  // workgroups of 4, those dispatched when every compute unit already has one - take precedence for the first half
+  // of their tiles, which lets both end together (206 -> 199 us; a batch of 64 x 4096 tokens 47.6 -> 46.6 us a step,
+  // with rows of different lengths 46.4 -> 45.0; three and five eighths of the tiles measured up to 1% slower).
+  const bool young = NS == 1 && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)(blockIdx.y * gridDim.x + blockIdx.x) >= P.cus);
+  const int own_half = young ? (first + hi) / 2 : 0;
+  if (young) __builtin_amdgcn_s_setprio(1);
   const int64_t part_base = (((int64_t)bh * P.splits + split) * P.gh + hsub * P.hb) * (D + 4);
   State<NNT> st;
 #pragma unroll
@@ -468,7 +467,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) st.zacc[i] = 0.f;
 
-  if (wi < TF) {
+  if (unit0 < TF) {
     // ------------------------- original-precision rows -------------------------
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
     const uint16_t* kb = k_fp + fp_slice + lane * 8;
@@ -482,7 +481,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     // Fused append: the wavefront that owns the unit receiving the new row fetches the row
     // right away, so that it has arrived by the time that unit is processed.
     const int new_unit = (n_fp - 1) >> 5, new_sx = (n_fp - 1) & 31, new_kx = kperm(new_sx);
-    const bool owner = P.k_new && new_unit % NW == wi;
+    const bool owner = P.k_new && new_unit % unit_step == unit0;
     uint4 kn_r[NKC];
     uint32_t vn_r[NNT];
     if (owner) {
@@ -493,7 +492,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
       for (int nt = 0; nt < NNT; ++nt) vn_r[nt] = vn[16 * nt + n16];
     }
-    for (int unit = wi; unit < TF; unit += NW) {
+    for (int unit = unit0; unit < TF; unit += unit_step) {
       uint4 ka[2][NKC], va[NNT];
 #pragma unroll
       for (int uu = 0; uu < 2; ++uu)
@@ -730,7 +729,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     };
     auto drawn_tile = [&](int k) { return 2 * NWQ + __builtin_amdgcn_readfirstlane(k) * NSUB + sub; };
     auto after = [&](int t) {   // static schedule: the tile of this wavefront that follows tile t
-      const int step = lead > 0 ? nl : NWB;
+      const int step = lead > 0 ? nl : tile_step;
       lead = 0;
       return t + step;
     };
@@ -957,6 +956,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         const bool more = tb < hi;
         const int kd = draw();                 // for the tile after tb
         process(A, ta, more ? tb : ta);
+        if (NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
         slack = MAX_SLACK;
         if (!more) break;
         ta = tb;
@@ -1228,7 +1228,7 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.cap = s.cap; P.qcap = s.qcap; P.n_fp = c.n_fp; P.n_q = c.n_q; P.gh = s.gh;
   P.W = s.W; P.Wq = s.Wq; P.n_tok_q = quantized_tokens(s, c.n_q);
   P.hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
-  P.splits = plan.splits;
+  P.splits = plan.splits; P.nwf = plan.fp_waves; P.cus = compute_units();
   P.c = scale * 1.4426950408889634f;
   static const int dynamic = [] { const char* v = getenv("LOGQUANT_ATTN_DYNAMIC"); return v && *v ? atoi(v) : 1; }();
   P.dynamic = dynamic;

@@ -22,7 +22,7 @@ struct Shape {
 struct SeqState {
   int n_fp, n_q;      // rows in the fp region, slots in the quantized region
   int cur;            // which fp buffer is live
-  int unused;
+  int nwf;            // attention: wavefronts of a head group that keep to the fp rows where a share of them does
   int n_tok_q;        // tokens held in the n_q slots
   int item;           // compress: the i-th entry names the i-th sequence that is compressed
   int flag;           // append: 1 if the sequence takes a token; prefill: prompt length
@@ -57,7 +57,7 @@ __device__ __forceinline__ SeqArgsPtr seq_in_args(size_t offset) {
 }
 __device__ __forceinline__ SeqState seq_load(SeqArgsPtr p, int i) {
   SeqState r;
-  r.n_fp = p[i].n_fp; r.n_q = p[i].n_q; r.cur = p[i].cur; r.unused = 0;
+  r.n_fp = p[i].n_fp; r.n_q = p[i].n_q; r.cur = p[i].cur; r.nwf = p[i].nwf;
   r.n_tok_q = p[i].n_tok_q; r.item = p[i].item; r.flag = p[i].flag; r.order = p[i].order;
   return r;
 }
@@ -123,6 +123,7 @@ hipError_t launch_decode_step(const Shape& s, const lq_cache& c, const void* k_n
                               const void* q, float scale, void* out, const Workspace& ws, const lq_plan& plan,
                               hipStream_t st, const SeqArg* seq = nullptr);
 void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, bool per_sequence = false);
+int compute_units();   // of the device the launches are planned for
 // How many wavefronts' worth of time (of the NW a head group has) n_fp fp rows take beside
 // n_q quantized slots.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q);
