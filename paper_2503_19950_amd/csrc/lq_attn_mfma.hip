@@ -436,7 +436,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   const int nfw = min(TF, NW), NWQ = NW - nfw;   // wavefronts that start with a unit, and with a tile
   // Long contexts: tiles are dealt out dynamically (see "Tile schedule" below); the wavefronts with a unit join in
   // when they are done with it.
-  const bool dyn = P.dynamic && NS > 1 && NWQ > NSUB && TQ >= 5 * NWQ;
+  // (five tiles for each of the NW - nwf wavefronts that a static schedule would have: counted for the NWQ alone, 8 rows
+  // of 8192 tokens went dynamic and took 3% longer)
+  const bool dyn = P.dynamic && NS > 1 && NWQ > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
   // Otherwise the schedule is static, hence reproducible.  With a single split the wavefronts of the workgroup take
   // units and tiles in turn; when the units do not come out even, the nl wavefronts with one unit less are a round of
   // tiles ahead of the nh others (a unit takes about as long as a tile: a lead of 0 or 2 rounds measured 1 to 2% slower).
