@@ -87,6 +87,7 @@ struct AttnParams {
 
 constexpr int PSHIFT = 5;   // probabilities are kept relative to 2^(max - PSHIFT)
 constexpr float MAX_SLACK = 4.f;
+constexpr int FP_LEAD = 30;     // the fp rows' reference is lowered by this much when their sums pass to the quantized rows
 constexpr float DEAD_LOGIT = -1e30f;   // logit of a padding slot; exp2(DEAD_LOGIT - anything finite) == 0
 
 __device__ __forceinline__ floatx4 mfma_f16(uint4 a, uint4 b, floatx4 c) {
@@ -318,12 +319,10 @@ __device__ __forceinline__ void online_softmax(State<NNT>& st, const float* s, f
 // output step uses them, and the denominator sums these rounded values.  Numerator and
 // denominator then describe the same (slightly perturbed) weights, so that the rounding
 // cancels where one token dominates instead of scaling the whole output.
-// slack: MAX_SLACK, but 0 for the first tile of a wavefront that comes from fp rows: the heaviest token of a first tile
-// then has the exact probability 2^PSHIFT whether or not fp rows came before.
 template <int NNT, bool ROUND_P>
-__device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float* s, float* p, int g, float slack) {
+__device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float* s, float* p, int g) {
   float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-  if (__any(mx > st.m + slack)) {
+  if (__any(mx > st.m + MAX_SLACK)) {
     mx = row_max(mx);
     const float m_new = fmaxf(st.m, mx);
     const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);   // 0 on the first tile (m = -inf)
@@ -590,10 +589,16 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     // Hand-over to the quantized rows, whose state is laid out differently: m and l by lane row (l as one addend,
     // of a lane whose token slot carries the factor 2^pos_exp(0)), and the sum of head and residual rows of a
     // channel tile in the lane row of its channel group, in units of a code.
+    // The reference m goes down by FP_LEAD, the sums up by 2^FP_LEAD (exact): the first tile then raises it to its own
+    // maximum, unless that lies more than FP_LEAD below the fp rows'.  The tiles' probabilities are fp16 operands and
+    // must not shrink beside heavy fp rows; the fp32 sums do not mind (at most 2^9 |v| per row, times 2^30).  Tiles
+    // further below weigh under 2^-30 a token, 2^17 tokens under 2^-13 of the output, and down to 2^-40 their operands
+    // are still normal numbers.  (With the fp rows' maximum as the reference, 16384 tokens 2^14 below 10 heavy rows,
+    // value scales of 2^-8.5, were off by 1.3e-2 of the output; now within the output's own rounding.)
     const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
     const float m_g = st.m;
-    st.m = __shfl(m_g, q4);
-    const float l_q = __shfl(l_tot, q4) * __builtin_ldexpf(1.f, pos_exp<BITS>(0));
+    st.m = __shfl(m_g, q4) - (float)FP_LEAD;
+    const float l_q = __shfl(l_tot, q4) * __builtin_ldexpf(1.f, FP_LEAD + pos_exp<BITS>(0));
     st.l[0] = n16 == 0 ? l_q : 0.f;
     st.l[1] = st.l[2] = st.l[3] = 0.f;
 #pragma unroll
@@ -605,7 +610,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         xor16_pair(st.acc[nt][gg], &x, &y);
         float tot = x + y;
         if (gc >= 2) { xor32_pair(tot, &x, &y); tot = x + y; }
-        st.acc[nt][gg] = q4 == gc ? tot * (1.f / CODE_SCALE<BITS>) : 0.f;
+        st.acc[nt][gg] = q4 == gc ? tot * (__builtin_ldexpf(1.f, FP_LEAD) / CODE_SCALE<BITS>) : 0.f;
       }
     }
   }
@@ -789,7 +794,6 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       if (lane < 32) { p_lds[wave][0][4][lane] = 0; p_lds[wave][1][4][lane] = 0; }
     }
 
-    float slack = 0.f;
     auto process = [&](Tile& cur, int t, int tn) {   // tn: the tile to refill the registers with
       // ---- q*s (fp16 head and tail) and bias = sum_c q_c z_c for each key group
       float bo[4];
@@ -876,7 +880,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
           if (r >= P.W) s[u] = DEAD_LOGIT;
         }
       }
-      online_softmax_rows<NNT, VPIECES == 1>(st, s, p, g, slack);
+      online_softmax_rows<NNT, VPIECES == 1>(st, s, p, g);
 
       // ---- hand the probabilities (fp16) to the lanes that feed the output step
 #pragma unroll
@@ -959,7 +963,6 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         const int kd = draw();                 // for the tile after tb
         process(A, ta, more ? tb : ta);
         if (NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
-        slack = MAX_SLACK;
         if (!more) break;
         ta = tb;
         tb = dyn ? drawn_tile(kd) : after(tb);
