@@ -351,6 +351,12 @@ __device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float*
   }
 }
 
+// Several splits: whether the tiles are drawn from the pools.  At least five tiles for each wavefront that an even deal
+// would give them to, and more wavefronts than pools, also of those that start without a unit.
+__host__ __device__ __forceinline__ bool draws_tiles(int dynamic, int NW, int nwf, int TF, int TQ) {
+  return dynamic && NW - TF > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
+}
+
 // NWB: wavefronts per workgroup: 8; 4 when there are enough (b, kv head) groups to put
 // two workgroups on every compute unit; 12 (three wavefronts per SIMD, at most 168
 // registers) for long contexts, where the extra wavefront hides more than the tighter
@@ -362,9 +368,12 @@ __device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float*
 template <bool GENERAL> struct SeqArgs {};
 template <> struct SeqArgs<true> { SeqState e[SEQ_CHUNK]; };
 
-template <bool BF16, int D, int G, int NWB, int BITS, bool GENERAL = false>
+// PROG: how fp rows and tiles are dealt to the wavefronts, see "schedule" in the kernel.
+enum { APART, ONE_SPLIT, DRAWN };
+template <bool BF16, int D, int G, int NWB, int BITS, bool GENERAL, int PROG>
 __global__ void __launch_bounds__(64 * NWB, NWB == 12 ? 3 : 2)
 attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
+  constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN, JOIN = ONE || DRAW;
   constexpr int NKC = D / 32, NNT = D / 16, NGC = (D + G - 1) / G;
   constexpr int WPL = NKC * (BITS / 2);           // code words per lane and 32-slot block
   constexpr int NGRP = G < 64 ? 64 / G : 1;     // key groups per 64-token tile
@@ -386,8 +395,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   // Workgroups are handed to the eight XCDs in turn (linear index mod 8).  When the
   // number of groups allows it, all splits of one group are placed on one XCD, so
   // that the partials they exchange at the end meet in that XCD's L2.
-  int split = blockIdx.x, group = blockIdx.y;
-  if (gridDim.y % 8 == 0) {
+  int split = ONE ? 0 : blockIdx.x, group = blockIdx.y;
+  if (!ONE && gridDim.y % 8 == 0) {
     const int L = blockIdx.y * gridDim.x + blockIdx.x;
     const int r = L >> 3;
     group = (L & 7) + 8 * (r / (int)gridDim.x);
@@ -425,38 +434,37 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   const uint16_t* k_fp = k_fp_w;
   const uint16_t* v_fp = v_fp_w;
   const int TQ = (n_q + 63) >> 6, TF = (n_fp + 31) >> 5;
-  // ---- schedule.  A wavefront first takes its units of fp rows, if it has any, then quantized tiles, with
-  // one softmax state for both.  (With a share of the wavefronts kept for the fp rows, those were done long before
-  // the others - after 40 of 240 us at 32768 tokens x 16 rows x 32 kv heads - and idled.)  The wavefronts of a head
-  // group are numbered across its workgroups, so that the units, fewer than wavefronts when the context is split,
-  // fall on different compute units: unit u belongs to wavefront u mod NW.
-  const int NS = P.splits, NW = NS * NWB;
-  const int wi = wave * NS + split;
-  const int nfw = min(TF, NW), NWQ = NW - nfw;   // wavefronts that start with a unit, and with a tile
-  // Long contexts: tiles are dealt out dynamically (see "Tile schedule" below); the wavefronts with a unit join in
-  // when they are done with it.
-  // (five tiles for each of the NW - nwf wavefronts that a static schedule would have: counted for the NWQ alone, 8 rows
-  // of 8192 tokens went dynamic and took 3% longer)
-  const bool dyn = P.dynamic && NS > 1 && NWQ > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
-  // Otherwise the schedule is static, hence reproducible.  With a single split the wavefronts of the workgroup take
-  // units and tiles in turn; when the units do not come out even, the nl wavefronts with one unit less are a round of
-  // tiles ahead of the nh others (a unit takes about as long as a tile: a lead of 0 or 2 rounds measured 1 to 2% slower).
-  // With several splits and few tiles for each wavefront a share of them, nwf, keeps to the units: a unit before the
-  // tiles is a load latency more for its wavefront (8 rows of 8192 tokens: 18.7 instead of 18.1 us).
-  const bool apart = !dyn && NS > 1;
-  const int gw = split * NWB + wave, nh = TF % NWB, nl = NWB - nh;
-  const int unit0 = !apart ? wi : gw < nwf ? gw : TF, unit_step = apart ? nwf : NW;
-  const int hi = TQ, tile_step = apart ? NW - nwf : NWB;
-  int lead = NS == 1 && nh > 0 && wave >= nh ? 1 : 0;
-  const int first = apart ? (gw < nwf ? TQ : gw - nwf) : dyn ? wi - nfw : nh == 0 ? wave : wave >= nh ? wave - nh : 2 * nl + wave;
+  // ---- schedule: three programs, chosen per launch (launch_mfma_p).  Fp rows come in units of 32, quantized rows in
+  // tiles of 64, and the wavefronts of all workgroups of a head group are numbered 0..NW-1.
+  //  APART      a share of the wavefronts, NWF, keeps to the units, the others walk the tiles and have their first loads
+  //             on the way before anything else.  For several splits with few tiles per wavefront, and for launches
+  //             without tiles.
+  //  ONE_SPLIT  every wavefront takes its units and then tiles, with one set of sums for both.  (With a share kept for
+  //             the units those wavefronts were done long before the others - after 40 of 240 us at 32768 tokens x 16
+  //             rows x 32 kv heads - and idled.)  Units and tiles are dealt out in turn; when the units do not come out
+  //             even, the nl wavefronts with one unit less are a round of tiles ahead of the nh others (a unit takes
+  //             about as long as a tile: a lead of 0 or 2 rounds measured 1 to 2% slower).
+  //  DRAWN      several splits, many tiles: unit u belongs to wavefront u mod NW, numbered so that units fall on
+  //             different compute units; the tiles are drawn (see "Tile schedule" below) and the wavefronts with a unit
+  //             join in when they are done with it.
+  // (One program for all, the deal worked out from the counts, cost the launches that are now APART a second wait for
+  // kernel arguments before the first load, and wavefronts without tiles the whole prologue and epilogue of tiles:
+  // 8 rows of 8192 tokens, four layers, 75.9 instead of 73.4 us.)
+  const int NW = ONE ? NWB : P.splits * NWB, NWF = ONE ? 0 : DRAW ? min(TF, NW) : nwf, NWQ = NW - NWF;
+  const bool one_split = ONE || (!DRAW && P.splits == 1);
+  const int gw = split * NWB + wave;
+  const int wi = DRAW ? wave * P.splits + split : gw;   // units on different compute units
+  const int nh = TF % NWB, nl = NWB - nh;
+  int lead = ONE && nh > 0 && wave >= nh ? 1 : 0;
+  const int first = !ONE ? wi - NWF : nh == 0 ? wave : wave >= nh ? wave - nh : 2 * nl + wave;
   // Of wavefronts that share a SIMD the older one wins the issue slots: with two to a SIMD and a static schedule the
   // younger ones ended 25% later (165 against 212 us at 16 rows x 32 kv heads x 32768 tokens), the last part with the
   // SIMD to themselves and too few loads in flight.  So the younger ones - the upper four of a workgroup of 8; of
   // workgroups of 4, those dispatched when every compute unit already has one - take precedence for the first half
   // of their tiles, which lets both end together (206 -> 199 us; a batch of 64 x 4096 tokens 47.6 -> 46.6 us a step,
   // with rows of different lengths 46.4 -> 45.0; three and five eighths of the tiles measured up to 1% slower).
-  const bool young = NS == 1 && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)(blockIdx.y * gridDim.x + blockIdx.x) >= P.cus);
-  const int own_half = young ? (first + hi) / 2 : 0;
+  const bool young = ONE && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)blockIdx.y >= P.cus);
+  const int own_half = young ? (first + TQ) / 2 : 0;
   if (young) __builtin_amdgcn_s_setprio(1);
   const int64_t part_base = (((int64_t)bh * P.splits + split) * P.gh + hsub * P.hb) * (D + 4);
   State<NNT> st;
@@ -468,8 +476,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) st.zacc[i] = 0.f;
 
-  if (unit0 < TF) {
-    // ------------------------- original-precision rows -------------------------
+  // ------------------------- original-precision rows -------------------------
+  auto fp_rows = [&](const int unit0, const int unit_step) __attribute__((always_inline)) {
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
     const uint16_t* kb = k_fp + fp_slice + lane * 8;
     const uint16_t* vb = v_fp + fp_slice + lane * 8;
@@ -560,16 +568,17 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         pv[j] = __shfl(p[j], src0);
         pv[4 + j] = __shfl(p[j], src1);
       }
-      // rows 0..3: p rounded to T; rows 4..7: the rounding residual, again in T
-      float av[8];
+      // rows 0..3: p rounded to T; rows 4..7: the rounding residual, again in T (masks: as a choice between the two
+      // the compiler made eight branches of it; 512 tokens, 8 kv heads 10.2 instead of 9.9 us)
+      const uint32_t hi_row = up == 0 ? 0xFFFFFFFFu : 0u, lo_row = up == 1 ? 0xFFFFFFFFu : 0u;
+      uint32_t aw[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float hi = t2f<BF16>(f2t<BF16>(pv[i]));
-        av[i] = up == 0 ? hi : up == 1 ? pv[i] - hi : 0.f;
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t hi = pack_T<BF16>(pv[2 * r], pv[2 * r + 1]);
+        const uint32_t lo = pack_T<BF16>(pv[2 * r] - lo_T<BF16>(hi), pv[2 * r + 1] - hi_T<BF16>(hi));
+        aw[r] = (hi & hi_row) | (lo & lo_row);
       }
-      uint4 a;
-      a.x = pack_T<BF16>(av[0], av[1]); a.y = pack_T<BF16>(av[2], av[3]);
-      a.z = pack_T<BF16>(av[4], av[5]); a.w = pack_T<BF16>(av[6], av[7]);
+      const uint4 a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
       if (32 * unit + 32 > n_fp) {   // slots beyond n_fp hold unspecified bits
         uint32_t keep[4];
 #pragma unroll
@@ -586,6 +595,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
       for (int nt = 0; nt < NNT; ++nt) st.acc[nt] = mfma_T<BF16>(a, va[nt], st.acc[nt]);
     }
+  };
+  auto hand_over = [&]() __attribute__((always_inline)) {
     // Hand-over to the quantized rows, whose state is laid out differently: m and l by lane row (l as one addend,
     // of a lane whose token slot carries the factor 2^pos_exp(0)), and the sum of head and residual rows of a
     // channel tile in the lane row of its channel group, in units of a code.
@@ -613,9 +624,10 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         st.acc[nt][gg] = q4 == gc ? tot * (__builtin_ldexpf(1.f, FP_LEAD) / CODE_SCALE<BITS>) : 0.f;
       }
     }
-  }
-  {
-    // ------------------------- quantized rows -------------------------
+  };
+
+  // ------------------------- quantized rows -------------------------
+  auto quantized_rows = [&]() __attribute__((always_inline)) {
     const char* kcb = (const char*)(P.k_codes + (int64_t)bh * (P.qcap >> 5) * 64 * WPL);
     const char* vcb = (const char*)(P.v_codes + (int64_t)bh * (P.qcap >> 5) * 64 * WPL);
     const char* ksb = (const char*)(P.k_scale + (int64_t)bh * (P.qcap / G) * D);
@@ -695,7 +707,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     auto load_kmeta = [&](Tile& T, int t) {
 #pragma unroll
       for (int e = 0; e < NGRP; ++e) {
-        const int grp = G <= 64 ? t * NGRP + e : t / (G / 64);
+        const int grp = t * NGRP / (G <= 64 ? 1 : G / 64) + e;
         T.ks8[e] = load16(rs_ks, km_off, (uint32_t)grp * (D * 2));
         T.kz8[e] = load16(rs_kz, km_off, (uint32_t)grp * (D * 2));
       }
@@ -711,12 +723,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       T.vz[b2] = load16(rs_vz, vm_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
     };
 
-    // Tile schedule.  The first two tiles of a wavefront without fp units are fixed (first, first + NWQ)
+    // Tile schedule with several splits.  The first two tiles of a wavefront are fixed (first, first + NWQ)
     // and the loads of the first go out before anything else touches memory.  The later
     // tiles are dealt out dynamically, so that wavefronts that start late or see
     // slower memory take fewer of them: tile 2 * NWQ + v * NSUB + j belongs to
-    // pool j (NSUB pools), and the wavefronts with wi % NSUB == j, spread over the
-    // whole chip, draw v from that pool's counter.  Several pools because atomics on
+    // pool j (NSUB pools), and the wavefronts with first % NSUB == j, spread over all
+    // workgroups, draw v from that pool's counter.  Several pools because atomics on
     // one address are serialised at a rate that a single counter could not sustain.
     // A draw is issued a whole tile ahead of its use and before that tile's loads: loads
     // and atomics return in issue order, so waiting for the drawn index does not wait
@@ -725,29 +737,38 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     // branch is needed (the join of a branch would make the compiler wait for every
     // outstanding load).
     // With few tiles per wavefront, or no more wavefronts than pools, there is nothing
-    // to balance: the schedule is then static (see above) and the atomic is aimed out of range.
+    // to balance: the schedule is then static (tile first + v * NWQ), and where only the
+    // row's counts decide (per-sequence lengths) the atomic is aimed out of range.
     // A single split has no last workgroup that could re-arm the pool counters for the
     // next launch (it returns before the ticket): static as well.
-    const int sub = wi % NSUB;
+    const bool dyn = DRAW || (GENERAL && P.seq_mode && !one_split && draws_tiles(P.dynamic, NW, NWF, TF, TQ));
+    const int nsub = dyn ? NSUB : NWQ;
+    const int sub = ONE ? 0 : DRAW ? wi % NSUB : first % nsub;
+    int v_static = 0;
     const __amdgpu_buffer_rsrc_t pool = __builtin_amdgcn_make_buffer_rsrc(
         P.counters + (group * CTR_LINES + 1 + sub) * CTR_LINE, 0, 4, 0x00020000);
     auto draw = [&]() {   // raw counter value in lane 0
-      return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, pool, dyn ? lane * 4 : 4, 0, 0);
+      if constexpr (!DRAW && !GENERAL) return 0;
+      else if constexpr (ONE) return 0;
+      else return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, pool, dyn ? lane * 4 : 4, 0, 0);
     };
-    auto drawn_tile = [&](int k) { return 2 * NWQ + __builtin_amdgcn_readfirstlane(k) * NSUB + sub; };
-    auto after = [&](int t) {   // static schedule: the tile of this wavefront that follows tile t
-      const int step = lead > 0 ? nl : tile_step;
+    auto drawn_tile = [&](int k) {
+      const int v = dyn ? __builtin_amdgcn_readfirstlane(k) : v_static++;
+      return 2 * NWQ + v * nsub + sub;
+    };
+    auto after = [&](int t) {   // single split: the tile of this wavefront that follows tile t
+      const int step = lead > 0 ? nl : NWB;
       lead = 0;
       return t + step;
     };
-    int ta = first, tb = dyn ? first + NWQ : after(first);
-    if (dyn && wi < nfw) {      // done with its units: joins in
+    int ta = first, tb = ONE ? after(first) : first + NWQ;
+    if (DRAW && wi < NWF) {      // done with its units: joins in
       const int ka = draw(), kb = draw();
       ta = drawn_tile(ka);
       tb = drawn_tile(kb);
     }
     Tile A;
-    if (ta < hi) {
+    if (ta < TQ) {
       load_kmeta(A, ta);
       load_kcodes(A, ta);
       load_v(A, ta, 0);
@@ -777,7 +798,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int v = 2 * (u & 1) + ((n16 & 3) >> 1);
-      offs[u] = (float)(BITS == 2 ? 3 - 2 * v : 2 - 4 * (v & 1));
+      offs[u] = (float)pos_exp<BITS>(v);
     }
 
     // rows of the q*s operand: matrix row n16 = 4*head + piece, piece 3 is zero
@@ -957,15 +978,15 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       wave_lds_sync();   // p_lds and qs_lds are rewritten by the next tile
     };
 
-    if (ta < hi) {
+    if (ta < TQ) {
       while (true) {
-        const bool more = tb < hi;
+        const bool more = tb < TQ;
         const int kd = draw();                 // for the tile after tb
         process(A, ta, more ? tb : ta);
-        if (NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
+        if (ONE && NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
         if (!more) break;
         ta = tb;
-        tb = dyn ? drawn_tile(kd) : after(tb);
+        tb = ONE ? after(tb) : drawn_tile(kd);
       }
     }
     // canonical partial of this wavefront: o[g][c], m[g], l[g]
@@ -1023,16 +1044,42 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
       for (int nt = 0; nt < NNT; ++nt) {
         const int gc = (16 * nt) / G;
+        if constexpr (VPIECES == 2) {   // add the residual piece's row: lane group q4 + NGC
+          float a[4];
 #pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-          float a = st.acc[nt][gg];
-          if constexpr (VPIECES == 2) {   // add the residual piece's row: lane group q4 + NGC
+          for (int gg = 0; gg < 4; ++gg) {
             float x, y;
-            if constexpr (NGC == 2) xor32_pair(a, &x, &y); else xor16_pair(a, &x, &y);
-            a = x + y;
+            xor16_pair(st.acc[nt][gg], &x, &y);   // (NGC == 1)
+            a[gg] = x + y;
           }
-          if (q4 == gc) o_lds[wave][gg][16 * nt + n16] = a * CODE_SCALE<BITS> + zsv[gg];
+          if (q4 == gc) {
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg) o_lds[wave][gg][16 * nt + n16] = a[gg] * CODE_SCALE<BITS> + zsv[gg];
+          }
+        } else {
+#pragma unroll
+          for (int gg = 0; gg < 4; ++gg)
+            if (q4 == gc) o_lds[wave][gg][16 * nt + n16] = st.acc[nt][gg] * CODE_SCALE<BITS> + zsv[gg];
         }
+      }
+    }
+  };
+
+  if constexpr (JOIN) {
+    if (wi < TF) { fp_rows(wi, NW); hand_over(); }
+    quantized_rows();
+  } else if (gw >= NWF) {
+    quantized_rows();
+  } else {
+    fp_rows(gw, NWF);
+    const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
+    if (lane < 4) { ml_lds[wave][g][0] = st.m; ml_lds[wave][g][1] = l_tot; }
+#pragma unroll
+    for (int nt = 0; nt < NNT; ++nt) {
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) {   // the sum of head and residual rows
+        const float v = st.acc[nt][gg] + __shfl_xor(st.acc[nt][gg], 16);
+        if (q4 == 0) o_lds[wave][gg][16 * nt + n16] = v;
       }
     }
   }
@@ -1051,7 +1098,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       acc += a * o_lds[w][gg][c];
       L += a * ml_lds[w][gg][1];
     }
-    if (P.splits == 1) {   // nothing to merge across workgroups: this is the result
+    if (one_split) {   // nothing to merge across workgroups: this is the result
       P.out[((int64_t)bh * P.gh + hsub * P.hb + gg) * D + c] = f2t<BF16>(acc / L);
       continue;
     }
@@ -1059,7 +1106,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     st_dev(P.ws + base + c, acc);
     if (c == 0) { st_dev(P.ws + base + D, M); st_dev(P.ws + base + D + 1, L); }
   }
-  if (P.splits == 1) return;
+  if (one_split) return;
 
   // ---- ticket: the last workgroup of this (b, kv head, head group) merges the splits.
   // The barrier waits for this workgroup's stores to be acknowledged before thread 0
@@ -1169,7 +1216,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   }
 }
 
-template <bool BF16, int D, int NWB, int BITS>
+template <bool BF16, int D, int NWB, int BITS, int PROG>
 static hipError_t launch_mfma_dg(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   if constexpr (NWB == 8 || NWB == 12) {
     if (s.Wq != s.W || seq) {
@@ -1177,28 +1224,38 @@ static hipError_t launch_mfma_dg(const Shape& s, const AttnParams& P, const SeqA
       if (seq && seq->in_args())
         for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
       switch (s.G) {
-        case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, true>), grid, dim3(64 * NWB), 0, st, P, S); break;
-        case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, true>), grid, dim3(64 * NWB), 0, st, P, S); break;
-        default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, true>), grid, dim3(64 * NWB), 0, st, P, S); break;
+        case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+        case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+        default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
       }
       return launch_status(__func__);
     }
   }
   const SeqArgs<false> S;
   switch (s.G) {
-    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
   }
   return launch_status(__func__);
+}
+
+template <bool BF16, int D, int NWB, int BITS>
+static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
+  const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = (P.n_q + 63) / 64;
+  if (P.splits == 1 && P.n_q > 0) return launch_mfma_dg<BF16, D, NWB, BITS, ONE_SPLIT>(s, P, seq, grid, st);
+  // (with counts per sequence each row decides for itself, in the kernel)
+  if (P.splits > 1 && !seq && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
+    return launch_mfma_dg<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
+  return launch_mfma_dg<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
 }
 
 template <bool BF16, int NWB, int BITS>
 static hipError_t launch_mfma_d(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   switch (s.d) {
-    case 64: return launch_mfma_dg<BF16, 64, NWB, BITS>(s, P, seq, grid, st);
-    case 96: return launch_mfma_dg<BF16, 96, NWB, BITS>(s, P, seq, grid, st);
-    default: return launch_mfma_dg<BF16, 128, NWB, BITS>(s, P, seq, grid, st);
+    case 64: return launch_mfma_p<BF16, 64, NWB, BITS>(s, P, seq, grid, st);
+    case 96: return launch_mfma_p<BF16, 96, NWB, BITS>(s, P, seq, grid, st);
+    default: return launch_mfma_p<BF16, 128, NWB, BITS>(s, P, seq, grid, st);
   }
 }
 
