@@ -3,6 +3,8 @@ the library has a plain C ABI and is loaded with ctypes)."""
 import glob
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -12,7 +14,7 @@ CSRC_PLAIN = os.path.join(HERE, "csrc_plain")
 LIB_PLAIN = os.path.join(HERE, "liblogquant_plain.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
 ]
@@ -41,8 +43,15 @@ def build(verbose=False):
     vector-unit measurement load on top of it."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     inc = ["-I", os.path.join(HERE, "..", "include")]
-    _hipcc([hipcc, *HIPCC_FLAGS, *inc, "-o", LIB, *sources()], verbose)
-    _hipcc([hipcc, *HIPCC_FLAGS, *inc, "-o", LIB_PLAIN, *sorted(glob.glob(os.path.join(CSRC_PLAIN, "*.hip"))),
+    with tempfile.TemporaryDirectory() as tmp:
+        def compile_one(src):
+            obj = os.path.join(tmp, os.path.basename(src) + ".o")
+            _hipcc([hipcc, *HIPCC_FLAGS, *inc, "-c", "-o", obj, src], verbose)
+            return obj
+        with ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:   # one hipcc a source file
+            objs = list(pool.map(compile_one, sources()))
+        _hipcc([hipcc, *HIPCC_FLAGS, "-shared", "-o", LIB, *objs], verbose)
+    _hipcc([hipcc, *HIPCC_FLAGS, "-shared", *inc, "-o", LIB_PLAIN, *sorted(glob.glob(os.path.join(CSRC_PLAIN, "*.hip"))),
             "-L", HERE, "-llogquant", "-Wl,-rpath,$ORIGIN"], verbose)
     return LIB
 
