@@ -34,7 +34,7 @@
 //
 // Work split: a workgroup has eight (or four, or twelve) independent wavefronts; the
 // wavefronts of all workgroups of one (batch row, kv head, head group) share its fp rows
-// in units of 32 and its quantized rows in tiles of 64 (see "schedule" below).
+// in units of 32 and its quantized rows in tiles of 64 (lq_schedule.h).
 // Partial (max, sum, output) triples are merged in LDS per workgroup and written
 // to the workspace.  Every workgroup then takes a ticket from a counter of its
 // (batch row, kv head, head group); the one that draws the last ticket merges all
@@ -46,6 +46,7 @@
 #pragma once
 #include "lq_device.h"
 #include "lq_internal.h"
+#include "lq_schedule.h"
 
 namespace lq {
 
@@ -350,12 +351,6 @@ __device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float*
   }
 }
 
-// Several splits: whether the tiles are drawn from the pools.  At least five tiles for each wavefront that an even deal
-// would give them to, and more wavefronts than pools, also of those that start without a unit.
-__host__ __device__ __forceinline__ bool draws_tiles(int dynamic, int NW, int nwf, int TF, int TQ) {
-  return dynamic && NW - TF > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
-}
-
 // NWB: wavefronts per workgroup: 8; 4 when there are enough (b, kv head) groups to put
 // two workgroups on every compute unit; 12 (three wavefronts per SIMD, at most 168
 // registers) for long contexts, where the extra wavefront hides more than the tighter
@@ -367,12 +362,11 @@ __host__ __device__ __forceinline__ bool draws_tiles(int dynamic, int NW, int nw
 template <bool GENERAL> struct SeqArgs {};
 template <> struct SeqArgs<true> { SeqState e[SEQ_CHUNK]; };
 
-// PROG: how fp rows and tiles are dealt to the wavefronts, see "schedule" in the kernel.
-enum { APART, ONE_SPLIT, DRAWN };
+// PROG: how fp rows and tiles are dealt to the wavefronts, see lq_schedule.h.
 template <bool BF16, int D, int G, int NWB, int BITS, bool GENERAL, int PROG>
 __global__ void __launch_bounds__(64 * NWB, NWB == 12 ? 3 : 2)
 attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
-  constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN, JOIN = ONE || DRAW;
+  constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN;
   constexpr int NKC = D / 32, NNT = D / 16, NGC = (D + G - 1) / G;
   constexpr int WPL = NKC * (BITS / 2);           // code words per lane and 32-slot block
   constexpr int NGRP = G < 64 ? 64 / G : 1;     // key groups per 64-token tile
@@ -433,29 +427,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   const uint16_t* k_fp = k_fp_w;
   const uint16_t* v_fp = v_fp_w;
   const int TQ = (n_q + 63) >> 6, TF = (n_fp + 31) >> 5;
-  // ---- schedule: three programs, chosen per launch (launch_mfma_p).  Fp rows come in units of 32, quantized rows in
-  // tiles of 64, and the wavefronts of all workgroups of a head group are numbered 0..NW-1.
-  //  APART      a share of the wavefronts, NWF, keeps to the units, the others walk the tiles and have their first loads
-  //             on the way before anything else.  For several splits with few tiles per wavefront, and for launches
-  //             without tiles.
-  //  ONE_SPLIT  every wavefront takes its units and then tiles, with one set of sums for both.  (With a share kept for
-  //             the units those wavefronts were done long before the others - after 40 of 240 us at 32768 tokens x 16
-  //             rows x 32 kv heads - and idled.)  Units and tiles are dealt out in turn; when the units do not come out
-  //             even, the nl wavefronts with one unit less are a round of tiles ahead of the nh others (a unit takes
-  //             about as long as a tile: a lead of 0 or 2 rounds measured 1 to 2% slower).
-  //  DRAWN      several splits, many tiles: unit u belongs to wavefront u mod NW, numbered so that units fall on
-  //             different compute units; the tiles are drawn (see "Tile schedule" below) and the wavefronts with a unit
-  //             join in when they are done with it.
-  // (One program for all, the deal worked out from the counts, cost the launches that are now APART a second wait for
-  // kernel arguments before the first load, and wavefronts without tiles the whole prologue and epilogue of tiles:
-  // 8 rows of 8192 tokens, four layers, 75.9 instead of 73.4 us.)
-  const int NW = ONE ? NWB : P.splits * NWB, NWF = ONE ? 0 : DRAW ? min(TF, NW) : nwf, NWQ = NW - NWF;
+  const Deal<PROG, NWB> deal(P.splits, split, wave, nwf, TF);
   const bool one_split = ONE || (!DRAW && P.splits == 1);
-  const int gw = split * NWB + wave;
-  const int wi = DRAW ? wave * P.splits + split : gw;   // units on different compute units
-  const int nh = TF % NWB, nl = NWB - nh;
-  int lead = ONE && nh > 0 && wave >= nh ? 1 : 0;
-  const int first = !ONE ? wi - NWF : nh == 0 ? wave : wave >= nh ? wave - nh : 2 * nl + wave;
   // Of wavefronts that share a SIMD the older one wins the issue slots: with two to a SIMD and a static schedule the
   // younger ones ended 25% later (165 against 212 us at 16 rows x 32 kv heads x 32768 tokens), the last part with the
   // SIMD to themselves and too few loads in flight.  So the younger ones - the upper four of a workgroup of 8; of
@@ -463,7 +436,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   // of their tiles, which lets both end together (206 -> 199 us; a batch of 64 x 4096 tokens 47.6 -> 46.6 us a step,
   // with rows of different lengths 46.4 -> 45.0; three and five eighths of the tiles measured up to 1% slower).
   const bool young = ONE && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)blockIdx.y >= P.cus);
-  const int own_half = young ? (first + TQ) / 2 : 0;
+  const int own_half = young ? (deal.first + TQ) / 2 : 0;
   if (young) __builtin_amdgcn_s_setprio(1);
   const int64_t part_base = (((int64_t)bh * P.splits + split) * P.gh + hsub * P.hb) * (D + 4);
   State<NNT> st;
@@ -722,13 +695,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       T.vz[b2] = load16(rs_vz, vm_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
     };
 
-    // Tile schedule with several splits.  The first two tiles of a wavefront are fixed (first, first + NWQ)
-    // and the loads of the first go out before anything else touches memory.  The later
-    // tiles are dealt out dynamically, so that wavefronts that start late or see
-    // slower memory take fewer of them: tile 2 * NWQ + v * NSUB + j belongs to
-    // pool j (NSUB pools), and the wavefronts with first % NSUB == j, spread over all
-    // workgroups, draw v from that pool's counter.  Several pools because atomics on
-    // one address are serialised at a rate that a single counter could not sustain.
+    // Tiles that are drawn.  The first two of a wavefront without units are fixed, and the loads of the first go out
+    // before anything else touches memory.  The later tiles are dealt out dynamically, so that wavefronts that start
+    // late or see slower memory take fewer of them.
     // A draw is issued a whole tile ahead of its use and before that tile's loads: loads
     // and atomics return in issue order, so waiting for the drawn index does not wait
     // for the loads behind it.  The draw is a buffer atomic over a 4-byte buffer: only
@@ -736,32 +705,21 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     // branch is needed (the join of a branch would make the compiler wait for every
     // outstanding load).
     // With few tiles per wavefront, or no more wavefronts than pools, there is nothing
-    // to balance: the schedule is then static (tile first + v * NWQ), and where only the
-    // row's counts decide (per-sequence lengths) the atomic is aimed out of range.
+    // to balance: the deal is then static, and where only the row's counts decide
+    // (per-sequence lengths) the atomic is aimed out of range.
     // A single split has no last workgroup that could re-arm the pool counters for the
     // next launch (it returns before the ticket): static as well.
-    const bool dyn = DRAW || (GENERAL && P.seq_mode && !one_split && draws_tiles(P.dynamic, NW, NWF, TF, TQ));
-    const int nsub = dyn ? NSUB : NWQ;
-    const int sub = ONE ? 0 : DRAW ? wi % NSUB : first % nsub;
-    int v_static = 0;
+    constexpr bool MAY_DRAW = DRAW || (GENERAL && !ONE);
+    const bool dyn = DRAW || (MAY_DRAW && P.seq_mode && !one_split && draws_tiles(P.dynamic, P.splits * NWB, nwf, TF, TQ));
     const __amdgpu_buffer_rsrc_t pool = __builtin_amdgcn_make_buffer_rsrc(
-        P.counters + (group * CTR_LINES + 1 + sub) * CTR_LINE, 0, 4, 0x00020000);
+        P.counters + (group * CTR_LINES + 1 + (MAY_DRAW ? deal.pool() : 0)) * CTR_LINE, 0, 4, 0x00020000);
     auto draw = [&]() {   // raw counter value in lane 0
-      if constexpr (!DRAW && !GENERAL) return 0;
-      else if constexpr (ONE) return 0;
+      if constexpr (!MAY_DRAW) return 0;
       else return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, pool, dyn ? lane * 4 : 4, 0, 0);
     };
-    auto drawn_tile = [&](int k) {
-      const int v = dyn ? __builtin_amdgcn_readfirstlane(k) : v_static++;
-      return 2 * NWQ + v * nsub + sub;
-    };
-    auto after = [&](int t) {   // single split: the tile of this wavefront that follows tile t
-      const int step = lead > 0 ? nl : NWB;
-      lead = 0;
-      return t + step;
-    };
-    int ta = first, tb = ONE ? after(first) : first + NWQ;
-    if (DRAW && wi < NWF) {      // done with its units: joins in
+    auto drawn_tile = [&](int k) { return deal.drawn(__builtin_amdgcn_readfirstlane(k)); };
+    int ta = deal.first, tb = deal.second();
+    if (DRAW && deal.takes_units(TF)) {   // done with its units: joins in
       const int ka = draw(), kb = draw();
       ta = drawn_tile(ka);
       tb = drawn_tile(kb);
@@ -985,7 +943,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         if (ONE && NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
         if (!more) break;
         ta = tb;
-        tb = ONE ? after(tb) : drawn_tile(kd);
+        tb = dyn ? drawn_tile(kd) : deal.after(tb);
       }
     }
     // canonical partial of this wavefront: o[g][c], m[g], l[g]
@@ -1064,13 +1022,13 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     }
   };
 
-  if constexpr (JOIN) {
-    if (wi < TF) { fp_rows(wi, NW); hand_over(); }
+  if constexpr (PROG != APART) {
+    if (deal.takes_units(TF)) { fp_rows(deal.unit0, deal.unit_step); hand_over(); }
     quantized_rows();
-  } else if (gw >= NWF) {
+  } else if (deal.takes_tiles()) {
     quantized_rows();
   } else {
-    fp_rows(gw, NWF);
+    fp_rows(deal.unit0, deal.unit_step);
     const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
     if (lane < 4) { ml_lds[wave][g][0] = st.m; ml_lds[wave][g][1] = l_tot; }
 #pragma unroll

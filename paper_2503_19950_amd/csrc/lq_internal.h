@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/logquant.h"
+#include "lq_schedule.h"
 
 namespace lq {
 
@@ -75,7 +76,7 @@ int max_splits(const Shape& s);
 // head group) CTR_LINES cache lines of CTR_LINE ints, each holding one counter in
 // its first int: line 0 the ticket counter, lines 1..NSUB the tile pool counters.
 // The splits' partial results follow.
-constexpr int CTR_LINE = 32, NSUB = 8, CTR_LINES = 1 + NSUB;
+constexpr int CTR_LINE = 32, CTR_LINES = 1 + NSUB;
 inline size_t counter_bytes(const Shape& s) {
   return (size_t)s.B * s.Hkv * s.gh * CTR_LINES * CTR_LINE * sizeof(int);
 }

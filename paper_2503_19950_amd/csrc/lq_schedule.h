@@ -1,0 +1,71 @@
+// How the attention kernel's work is dealt to wavefronts: fp rows in units of 32, quantized rows in tiles of 64.
+// Integer arithmetic only, used by the kernel, by the choice of its program on the host, and by the host test.
+#pragma once
+#ifdef __HIP__
+#define LQ_HD __host__ __device__ __forceinline__
+#else
+#define LQ_HD inline
+#endif
+
+namespace lq {
+
+// Pools of tiles that wavefronts draw from, per head group.  Several, because atomics on one address are serialised at
+// a rate that a single counter could not sustain.
+constexpr int NSUB = 8;
+
+// Three programs, chosen per launch.  The wavefronts of all workgroups of a head group are numbered 0..NW-1.
+//  APART      a share of the wavefronts, NWF, keeps to the units, the others walk the tiles and have their first loads
+//             on the way before anything else.  For several splits with few tiles per wavefront, and for launches
+//             without tiles.  (With units and tiles in the same wavefronts and the deal worked out from the counts,
+//             every wavefront waited twice for kernel arguments before its first load, and those without tiles ran the
+//             whole prologue and epilogue of tiles: 8 rows of 8192 tokens, four layers, 75.9 instead of 73.4 us.)
+//  ONE_SPLIT  a single split: every wavefront takes its units and then tiles, with one set of sums for both.  (With a
+//             share kept for the units those wavefronts were done long before the others - after 40 of 240 us at 32768
+//             tokens x 16 rows x 32 kv heads - and idled.)  When the units do not come out even, the wavefronts with
+//             one unit less are a round of tiles ahead of the others (a unit takes about as long as a tile: a lead of
+//             0 or 2 rounds measured 1 to 2% slower).
+//  DRAWN      several splits, many tiles: the units fall on different compute units, the tiles are drawn from the pools,
+//             and the wavefronts with a unit join in when they are done with it.
+enum { APART, ONE_SPLIT, DRAWN };
+
+// Several splits: whether the tiles are drawn.  At least five tiles for each wavefront that an even deal would give
+// them to, and more wavefronts than pools, also of those that start without a unit.
+LQ_HD bool draws_tiles(int dynamic, int NW, int nwf, int TF, int TQ) {
+  return dynamic && NW - TF > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
+}
+
+template <int PROG, int NWB>
+struct Deal {
+  int NWF, NWQ;          // wavefronts that start with a unit, and with a tile (ONE_SPLIT: all of them count here)
+  int unit0, unit_step;  // this wavefront's units, if it takes any
+  int first;             // its first tile (DRAWN: negative for those that start with a unit)
+  int step1;             // from the first tile to the second, where they are not drawn
+
+  // split, wave: this wavefront; nwf: the share of wavefronts for the units in APART; TF: number of units
+  LQ_HD Deal(int splits, int split, int wave, int nwf, int TF) {
+    const int NW = PROG == ONE_SPLIT ? NWB : splits * NWB;
+    NWF = PROG == ONE_SPLIT ? 0 : PROG == DRAWN ? (TF < NW ? TF : NW) : nwf;
+    NWQ = NW - NWF;
+    unit0 = PROG == ONE_SPLIT ? wave : PROG == DRAWN ? wave * splits + split : split * NWB + wave;
+    unit_step = PROG == APART ? NWF : NW;
+    if (PROG == ONE_SPLIT) {
+      const int nh = TF % NWB, nl = NWB - nh;   // wavefronts with one unit more, and the others
+      const bool ahead = nh > 0 && wave >= nh;
+      first = nh == 0 ? wave : ahead ? wave - nh : 2 * nl + wave;
+      step1 = ahead ? nl : NWB;
+    } else {
+      first = unit0 - NWF;
+      step1 = NWQ;
+    }
+  }
+  LQ_HD bool takes_units(int TF) const { return unit0 < (PROG == APART ? NWF : TF); }
+  LQ_HD bool takes_tiles() const { return PROG != APART || unit0 >= NWF; }
+  // Tiles that are not drawn: the second, then every NWQ-th.
+  LQ_HD int second() const { return first + step1; }
+  LQ_HD int after(int t) const { return t + NWQ; }
+  // Tiles that are drawn: the first two of a wavefront without units are fixed, the v-th draw from its pool gives
+  LQ_HD int drawn(int v) const { return 2 * NWQ + v * NSUB + pool(); }
+  LQ_HD int pool() const { return (PROG == DRAWN ? unit0 : first) % NSUB; }
+};
+
+}  // namespace lq

@@ -1,26 +1,16 @@
-"""The static schedule of the attention kernel, restated on the host: with a single split every 64-slot tile of
-a head group is taken by exactly one wavefront, whatever the counts and the workgroup shape."""
-import random
+"""The deal of the attention kernel's work to wavefronts (units of fp rows, tiles of quantized rows): the kernel's own
+arithmetic, csrc/lq_schedule.h, compiled for the host and run for random launches of all three programs, the tiles
+that are drawn at run time in a random order.  A unit or tile that is left out would silently drop tokens."""
+import os
+import subprocess
 
-import pytest
-
-
-def tiles_of(wave, TQ, TF, NWB):
-    nh = TF % NWB
-    nl = NWB - nh
-    lead = nh > 0 and wave >= nh
-    t = wave if nh == 0 else wave - nh if wave >= nh else 2 * nl + wave
-    while t < TQ:
-        yield t
-        t += nl if lead else NWB
-        lead = False
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2503_19950_amd", "csrc")
 
 
-@pytest.mark.parametrize("NWB", [4, 8, 12])
-def test_every_tile_is_taken_once_with_a_single_split(NWB):
-    rng = random.Random(NWB)
-    for _ in range(1500):
-        TQ = rng.choice([0, 1, 2, 3, 63, 64, 65, rng.randint(0, 400)])
-        TF = rng.choice([0, 1, NWB - 1, NWB, NWB + 1, rng.randint(0, 24)])
-        tiles = [t for wave in range(NWB) for t in tiles_of(wave, TQ, TF, NWB)]
-        assert sorted(tiles) == list(range(TQ)), (TQ, TF)
+def test_every_unit_and_tile_is_taken_once(tmp_path):
+    exe = tmp_path / "schedule"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe),
+                    os.path.join(HERE, "host", "schedule.cpp")], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
