@@ -1084,19 +1084,21 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   }
   __syncthreads();
   if (!is_last) return;
-  // All wavefronts merge: those with wave % hb == h share the rows (splits) of head h.  (One wavefront per head, with
-  // NWB / hb times the loads and sums in a row, took 0.8 us longer from the ticket to the end at 32 splits.)  The
-  // partials are read past the caches (device-coherent loads), 16 bytes per lane so that the address unit sees few,
-  // wide instructions, and all of them are issued before anything is consumed: the merge then costs about one
-  // memory round trip.
+  // Up to NI * RPI splits one wavefront merges a head.  With more of them all wavefronts merge, those with wave % hb == h
+  // sharing the rows (splits) of head h, and their sums meet in LDS: 0.8 us less from the ticket to the end at 32 splits,
+  // but 0.6 us more at few (3 splits of 512 tokens 9.7 instead of 9.0 us a launch, 8 splits of 2048 tokens at d = 64
+  // 8.7 instead of 8.0).  The partials are read past the caches (device-coherent loads), 16 bytes per lane so that the
+  // address unit sees few, wide instructions, and the loads of a batch are issued before anything is consumed: the merge
+  // then costs about one memory round trip.
   static_assert(NWB % 4 == 0, "every head gets the same number of wavefronts");
   constexpr int PR = D + 4;                    // floats per partial row
   constexpr int C4 = D / 4;                    // 16-byte chunks per row
   constexpr int RPI = 64 / C4;                 // rows covered by one wave-level load
   constexpr int NI = 8;                        // loads in flight
-  static_assert(64 % RPI == 0, "the rows of one load have their weights in one register");
-  const int head = wave % P.hb, part = wave / P.hb, parts = NWB / P.hb;
   const int rows = P.splits;
+  const bool alone = rows <= NI * RPI;         // one wavefront per head: one batch of loads, no sum over wavefronts
+  if (alone && wave >= P.hb) return;
+  const int head = wave % P.hb, part = wave / P.hb, parts = alone ? 1 : NWB / P.hb;
   const int64_t gstride = (int64_t)P.gh * PR;  // floats between consecutive splits
   const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + head) * PR;
   // buffer descriptor over this head's rows of all splits: out-of-range lanes read 0
@@ -1112,13 +1114,14 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     const int sidx = lane + 64 * k;
     ml[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, sidx < rows ? (int)((sidx * gstride + D) * 4) : oob, 0, 16);
   }
+  // load i of this wavefront: rows (i * parts + part) * RPI + r; past the last row the descriptor's end makes it zeros
+  const int row0 = part * RPI + r, row_step = parts * RPI;
+  const uint32_t off0 = r < RPI ? (uint32_t)(row0 * gstride + 4 * c4) * 4 : (uint32_t)oob, off_step = (uint32_t)(row_step * gstride) * 4;
   u32x4 ov[NI];
   auto load_rows = [&](int i0) {               // the i0-th .. (i0 + NI - 1)-th load of this wavefront
+    uint32_t off = off0 + i0 * off_step;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int sidx = ((i0 + i) * parts + part) * RPI + r;
-      ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (r < RPI && sidx < rows) ? (int)((sidx * gstride + 4 * c4) * 4) : oob, 0, 16);
-    }
+    for (int i = 0; i < NI; ++i, off += off_step) ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 16);
   };
   load_rows(0);
   float w[4], mx = -INFINITY, ls = 0.f;
@@ -1128,25 +1131,26 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     mx = fmaxf(mx, w[k]);
   }
   mx = rows_max(row_max(mx));
+  float* weight = reinterpret_cast<float*>(&p_lds[wave][0][0][0]);   // this wavefront's copy, free again
+  static_assert(sizeof(p_lds[0]) >= 256 * sizeof(float), "a weight for each split");
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     w[k] = w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[k] - mx);
     ls += w[k] * __uint_as_float(ml[k][1]);    // (0 * 0 past the last row)
+    weight[lane + 64 * k] = w[k];
   }
   ls = rows_sum(row_sum(ls));
+  wave_lds_sync();
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int i0 = 0;;) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int s0 = ((i0 + i) * parts + part) * RPI;
-      const float wk = s0 < 64 ? w[0] : s0 < 128 ? w[1] : s0 < 192 ? w[2] : w[3];
-      const float ws = __shfl(wk, (s0 + r) & 63);
-      const float wi = (r < RPI && s0 + r < rows) ? ws : 0.f;
+      const float wi = weight[(row0 + (i0 + i) * row_step) & 255];   // (past the last row the loads are zeros)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, __uint_as_float(ov[i][e]), acc[e]);
     }
     i0 += NI;
-    if (i0 * parts * RPI >= rows) break;
+    if (i0 * row_step >= rows) break;
     load_rows(i0);
   }
   // add the RPI row classes (lanes c4, c4 + C4, ...), then the parts, in LDS (o_lds is free again)
@@ -1156,6 +1160,15 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 #pragma unroll
     for (int k = 1; k < RPI; ++k) t += __shfl(acc[e], (lane + k * C4) & 63);
     acc[e] = t;
+  }
+  if (alone) {
+    if (lane < C4) {
+      const float inv = 1.0f / ls;
+      *reinterpret_cast<uint2*>(P.out + ((int64_t)bh * P.gh + hsub * P.hb + head) * D + 4 * c4) =
+          make_uint2((uint32_t)f2t<BF16>(acc[0] * inv) | ((uint32_t)f2t<BF16>(acc[1] * inv) << 16),
+                     (uint32_t)f2t<BF16>(acc[2] * inv) | ((uint32_t)f2t<BF16>(acc[3] * inv) << 16));
+    }
+    return;
   }
   float* sum = &o_lds[0][0][0];                // [part][head][D]
   if (lane < C4) *reinterpret_cast<float4*>(sum + (part * P.hb + head) * D + 4 * c4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
