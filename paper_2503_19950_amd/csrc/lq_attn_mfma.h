@@ -378,7 +378,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   constexpr int QS_ROWS = 13;
   __shared__ __attribute__((aligned(16))) uint16_t qs_lds[NWB][NGRP][QS_ROWS][QS_ROW];   // rows 4*piece+head (three pieces), row 12 = zeros
   __shared__ __attribute__((aligned(16))) uint16_t p_lds[NWB][2][9][32];            // [wave][32-token step][row][token]: rows 0-3 p of head, 4 zeros, 5-8 p's fp16 rounding residual
-  __shared__ float o_lds[NWB][4][D];
+  __shared__ __attribute__((aligned(16))) float o_lds[NWB][4][D];                   // (the split merge stores 16 bytes at a time)
   __shared__ float ml_lds[NWB][4][2];
   __shared__ float zs_lds[NWB][4][4];
 
@@ -1171,6 +1171,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     return;
   }
   float* sum = &o_lds[0][0][0];                // [part][head][D]
+  static_assert(sizeof(o_lds) >= NWB * D * sizeof(float), "parts * hb = NWB rows of sums");
   if (lane < C4) *reinterpret_cast<float4*>(sum + (part * P.hb + head) * D + 4 * c4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
   if (part == 0 && lane == 0) ml_lds[0][head][1] = ls;
   __syncthreads();
