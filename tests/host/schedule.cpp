@@ -21,7 +21,7 @@ static void fail(const char* what, int prog, int NWB, int NS, int nwf, int TF, i
 
 template <int PROG, int NWB>
 static void check(int NS, int nwf, int TF, int TQ, bool dyn) {
-  std::vector<int> units(TF, 0), tiles(TQ, 0), counter(NSUB, 0), drawers(NSUB, 0);
+  std::vector<int> units(TF, 0), tiles(TQ, 0), counter(NSUB, 0), drawers(NSUB, 0), groups(NSUB, 0), last(NSUB, -1);
   std::vector<Wave> w;
   for (int split = 0; split < NS; ++split)
     for (int wave = 0; wave < NWB; ++wave) {
@@ -35,6 +35,7 @@ static void check(int NS, int nwf, int TF, int TQ, bool dyn) {
       if (dyn) {   // the kernel's loop, one step of a random wavefront at a time (below)
         if (d.pool() < 0 || d.pool() >= NSUB) fail("no such pool", PROG, NWB, NS, nwf, TF, TQ);
         ++drawers[d.pool()];
+        if (last[d.pool()] != split) { last[d.pool()] = split; ++groups[d.pool()]; }
         w.push_back({d.first, d.second(), 0, d.pool(), true});
         continue;
       }
@@ -42,8 +43,11 @@ static void check(int NS, int nwf, int TF, int TQ, bool dyn) {
       for (int ta = d.first, tb = d.second(); ta < TQ; ta = tb, tb = d.after(tb)) ++tiles[ta];
     }
   if (dyn) {
-    for (int p = 0; p < NSUB; ++p)
+    for (int p = 0; p < NSUB; ++p) {
       if (!drawers[p]) fail("a pool that nobody draws from", PROG, NWB, NS, nwf, TF, TQ);
+      // a workgroup that starts late can only be relieved by others that draw from its pools
+      if (PROG == DRAWN && NS * NWB >= 2 * NSUB && groups[p] < 2) fail("a pool of one workgroup", PROG, NWB, NS, nwf, TF, TQ);
+    }
     std::vector<Deal<PROG, NWB>> deal;
     for (int split = 0; split < NS; ++split)
       for (int wave = 0; wave < NWB; ++wave) {
