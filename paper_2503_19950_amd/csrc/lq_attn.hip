@@ -37,8 +37,9 @@ static double fp_unit_weight(const Shape& s) {
 
 // The fp rows' share of the wavefronts, as the plan reports it: the number that, given
 // every unit of 32 rows, would be done when the others are done with the tiles (whole
-// units counted).  The kernel keeps to it
-// where the context is split and the schedule static; else wavefronts take both.
+// units counted).  The kernel keeps to it where the context is split and the tiles are
+// not drawn, and where there are no tiles; it also enters the rule for drawing them
+// (lq_schedule.h).  Else wavefronts take both.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
   const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
   if (TF == 0) return 0;

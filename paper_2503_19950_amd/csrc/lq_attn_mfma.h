@@ -460,7 +460,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       if (!head_ok) qreg[kc] = make_uint4(0, 0, 0, 0);
     }
     // Fused append: the wavefront that owns the unit receiving the new row fetches the row
-    // right away, so that it has arrived by the time that unit is processed.
+    // first.  (The compiler waits for it before it issues the unit's own loads: one more
+    // latency for this wavefront.)
     const int new_unit = (n_fp - 1) >> 5, new_sx = (n_fp - 1) & 31, new_kx = kperm(new_sx);
     const bool owner = P.k_new && new_unit % unit_step == unit0;
     uint4 kn_r[NKC];
