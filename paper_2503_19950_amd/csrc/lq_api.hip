@@ -342,8 +342,13 @@ static SeqState seq_entry(const Shape& s, int n_fp, int n_q, int cur) {
 // Plan for the longest sequence; bytes over all of them, the fp share of the wavefronts for each.
 static void plan_seq(const Shape& s, const int* n_fp, const int* n_q, lq_plan* plan, SeqState* st) {
   int mf = 0, mq = 0;
-  for (int b = 0; b < s.B; ++b) { if (n_fp[b] > mf) mf = n_fp[b]; if (n_q[b] > mq) mq = n_q[b]; }
-  plan_decode(s, mf, mq, plan, true);
+  bool same = true;
+  for (int b = 0; b < s.B; ++b) {
+    if (n_fp[b] > mf) mf = n_fp[b];
+    if (n_q[b] > mq) mq = n_q[b];
+    same = same && n_fp[b] == n_fp[0] && n_q[b] == n_q[0];
+  }
+  plan_decode(s, mf, mq, plan, same ? SAME_LENGTH : DIFFERENT_LENGTHS);
   const int NW = plan->splits * plan->waves_per_block;
   int64_t bytes = 0;
   Shape one = s;
@@ -359,6 +364,10 @@ static void plan_seq(const Shape& s, const int* n_fp, const int* n_q, lq_plan* p
     std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) {
       return cache_bytes_read(one, n_fp[x], n_q[x]) > cache_bytes_read(one, n_fp[y], n_q[y]);
     });
+    if (pairs_workgroups(*plan)) {
+      const int per_row = plan->blocks / s.B, first = (compute_units() + per_row - 1) / per_row;
+      std::reverse(idx.begin() + std::min(first, s.B), idx.end());
+    }
     for (int b = 0; b < s.B; ++b) st[b].order = idx[b];
   }
 }

@@ -56,7 +56,7 @@ int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
   return best;
 }
 
-void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, bool per_sequence) {
+void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
   const double r = fp_unit_weight(s);
   const double units = TQ + r * TF;
@@ -68,11 +68,14 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, bool per_sequ
   const double fixed = 2.5, per_split = 0.02, merge_tail = 1.5;
   int best_wpb = 8, best_splits = 1;
   double best = 1e300;
-  // padding slots in the quantized region, per-sequence counts: 8-wavefront kernel only
-  const bool ragged = s.Wq != s.W || per_sequence;
-  for (int wpb = 8; wpb >= 4; wpb -= 4) {
-    if (ragged && wpb != 8) continue;   // (12 is derived from 8 below)
-    if (!ragged && force_wpb && force_wpb != 12 && wpb != force_wpb) continue;
+  for (int wpb = 8; wpb >= 4; wpb -= 4) {   // (12 is derived from 8 below)
+    if (force_wpb && force_wpb != 12 && wpb != force_wpb) continue;
+    // Rows of different lengths: 4 wavefronts win as they do for lock-step rows (two workgroups to a compute unit cover
+    // each other's start and end: 41 rows of up to 1238 tokens, 8 kv heads 44.4 -> 34.9 us a launch, 64 rows of up to
+    // 4096 44.5 -> 42), but not without tiles (9 rows of up to 540 tokens 9.6 -> 10.0).  Lock-step rows with padding
+    // slots, and equal rows through the per-sequence calls, keep to 8 and 12 (with padding, in several splits, 4 are no
+    // better on average: 6 rows of 125730 tokens 48.6 against 50.9 us, 11 of 27723 67.5 against 65.8).
+    if (wpb == 4 && !force_wpb && (rows == LOCK_STEP ? s.Wq != s.W : rows == SAME_LENGTH || TQ == 0)) continue;
     const int slots = cus * (8 / wpb);
     int smax = (int)ceil(units / wpb);            // at least one unit per wavefront
     if (smax > max_splits(s)) smax = max_splits(s);

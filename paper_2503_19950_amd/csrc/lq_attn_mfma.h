@@ -78,7 +78,7 @@ struct AttnParams {
   int seq_mode;           // 0: counts below hold for every sequence; 1: state in the kernel arguments
   int Hkv;
   int cap, qcap, n_fp, n_q, gh, hb, splits, nwf;
-  int cus;            // compute units the launch was planned for
+  int cus;            // workgroups of 4 from this index on are the younger of a pair (the compute units planned for)
   int W, Wq;          // of every Wq quantized slots (one filtering event) the first W hold tokens
   int n_tok_q;        // tokens in the n_q quantized slots
   int dynamic;        // 0: static tile schedule only
@@ -356,8 +356,8 @@ __device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float*
 // registers) for long contexts, where the extra wavefront hides more than the tighter
 // register budget costs.
 // GENERAL: the variant that also handles padding slots in the quantized region (group
-// size not dividing the window) and per-sequence counts; built for 8 and 12 wavefronts
-// per workgroup.  The other instantiations carry neither check.
+// size not dividing the window) and per-sequence counts.  The other instantiations carry
+// neither check.
 // per-sequence state in the kernel arguments: only the general instantiation has any
 template <bool GENERAL> struct SeqArgs {};
 template <> struct SeqArgs<true> { SeqState e[SEQ_CHUNK]; };
@@ -435,6 +435,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   // workgroups of 4, those dispatched when every compute unit already has one - take precedence for the first half
   // of their tiles, which lets both end together (206 -> 199 us; a batch of 64 x 4096 tokens 47.6 -> 46.6 us a step,
   // with rows of different lengths 46.4 -> 45.0; three and five eighths of the tiles measured up to 1% slower).
+  // (Not where the younger of a pair of workgroups has the shorter row: see pairs_workgroups.)
   const bool young = ONE && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)blockIdx.y >= P.cus);
   const int own_half = young ? (deal.first + TQ) / 2 : 0;
   if (young) __builtin_amdgcn_s_setprio(1);
@@ -1190,18 +1191,16 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
 
 template <bool BF16, int D, int NWB, int BITS, int PROG>
 static hipError_t launch_mfma_dg(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  if constexpr (NWB == 8 || NWB == 12) {
-    if (s.Wq != s.W || seq) {
-      SeqArgs<true> S;
-      if (seq && seq->in_args())
-        for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
-      switch (s.G) {
-        case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-        case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-        default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-      }
-      return launch_status(__func__);
+  if (s.Wq != s.W || seq) {
+    SeqArgs<true> S;
+    if (seq && seq->in_args())
+      for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
+    switch (s.G) {
+      case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+      case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+      default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
     }
+    return launch_status(__func__);
   }
   const SeqArgs<false> S;
   switch (s.G) {

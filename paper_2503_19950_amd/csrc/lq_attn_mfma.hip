@@ -36,16 +36,11 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.cap = s.cap; P.qcap = s.qcap; P.n_fp = c.n_fp; P.n_q = c.n_q; P.gh = s.gh;
   P.W = s.W; P.Wq = s.Wq; P.n_tok_q = quantized_tokens(s, c.n_q);
   P.hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
-  P.splits = plan.splits; P.nwf = plan.fp_waves; P.cus = compute_units();
+  P.splits = plan.splits; P.nwf = plan.fp_waves; P.cus = seq && pairs_workgroups(plan) ? 1 << 30 : compute_units();
   P.c = scale * 1.4426950408889634f;
   static const int dynamic = [] { const char* v = getenv("LOGQUANT_ATTN_DYNAMIC"); return v && *v ? atoi(v) : 1; }();
   P.dynamic = dynamic;
   dim3 grid(plan.splits, s.B * s.Hkv * (s.gh / P.hb));
-  if (s.Wq != s.W || seq) {   // padding slots, per-sequence counts: that kernel variant exists for 8 and 12 wavefronts
-    if (plan.waves_per_block == 12 && s.bits == 2) return launch_mfma_t<12, 2>(s, P, seq, grid, st);
-    if (plan.waves_per_block != 8) return hipErrorInvalidConfiguration;
-    return s.bits == 4 ? launch_mfma_t<8, 4>(s, P, seq, grid, st) : launch_mfma_t<8, 2>(s, P, seq, grid, st);
-  }
   if (plan.waves_per_block == 12 && s.bits == 2) return launch_mfma_t<12, 2>(s, P, seq, grid, st);
   if (plan.waves_per_block == 4)
     return s.bits == 4 ? launch_mfma_t<4, 4>(s, P, seq, grid, st) : launch_mfma_t<4, 2>(s, P, seq, grid, st);

@@ -191,3 +191,32 @@ def test_error_codes():
     assert (dc.cur[0], dc.cur[1], dc.n_fp[1], dc.n_q[1]) == (0, 1, 64, 32)
     assert B.logquant_compress_seq(dc.cfg, dc.cs) == B.LQ_OK            # nothing to do
     assert (dc.cur[1], dc.n_fp[1], dc.n_q[1]) == (1, 64, 32)
+
+
+# rows x 8 kv heads: workgroups of 4 wavefronts one more than compute units, two to each, and more than that; the last
+# one's rows in several splits
+PAIRED = [("b33", 33, 700, 1), ("b64", 64, 700, 1), ("b65", 65, 500, 1), ("b9_splits", 9, 4400, 7)]
+
+
+@pytest.mark.parametrize("name,B,L,splits", PAIRED, ids=[c[0] for c in PAIRED])
+def test_rows_of_different_lengths_with_two_workgroups_per_compute_unit(name, B, L, splits):
+    """The longest rows are dispatched first and share compute units with the shortest: every row's output against its
+    own oracle, for the rows at both ends and at the turn of that order, and some between."""
+    from paper_2503_19950_amd import binding
+    wl = U.make_wl(B=B, Hq=8, Hkv=8, d=64, G=32, F=64)
+    lengths = [int(x) for x in np.random.default_rng(B).permutation(np.linspace(L // 3, L, B).astype(int))]
+    K, V = inputs.batch_kv(790 + B, 0, L, wl)
+    dc = _new(wl, L)
+    dc.prefill_seq(U.to_dev(K, "f16"), U.to_dev(V, "f16"), lengths)
+    plan = binding.logquant_decode_plan_seq(dc.cfg, list(dc.n_fp), list(dc.n_q))
+    if not os.environ.get("LOGQUANT_ATTN_WPB"):
+        assert (plan.waves_per_block, plan.splits, plan.blocks) == (4, splits, B * 8 * splits)
+    order = sorted(range(B), key=lambda b: -lengths[b])
+    q = inputs.queries(790 + B, 0, wl)
+    out = dc.decode_attn_seq(U.to_dev(q, "f16"))
+    ocs = {}
+    for b in {order[i] for i in (0, B // 3, B // 2 - 1, B // 2, min(32, B - 2), B - 1)}:
+        for h in (0, 7):
+            ocs[(b, h)] = SliceCache(32, 32, 64, "f16", 2)
+            ocs[(b, h)].append_block(K[b, h, :lengths[b]], V[b, h, :lengths[b]])
+    _check_outputs(out, ocs, wl, q, name)
