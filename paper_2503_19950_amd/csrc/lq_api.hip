@@ -355,6 +355,7 @@ static void plan_seq(const Shape& s, const int* n_fp, const int* n_q, lq_plan* p
   one.B = 1;
   for (int b = 0; b < s.B; ++b) {
     bytes += cache_bytes_read(one, n_fp[b], n_q[b]);
+    if (st) st[b].item = tiles_of(s, n_q[b]);
     if (st) st[b].nwf = plan->splits == 1 && mq > 0 ? 0 : fp_wave_share(s, NW, n_fp[b], n_q[b]);   // (0: no share is kept)
   }
   plan->bytes_read = bytes;

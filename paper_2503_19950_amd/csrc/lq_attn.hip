@@ -41,7 +41,7 @@ static double fp_unit_weight(const Shape& s) {
 // not drawn, and where there are no tiles; it also enters the rule for drawing them
 // (lq_schedule.h).  Else wavefronts take both.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
-  const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
+  const int TQ = tiles_of(s, n_q), TF = (n_fp + 31) / 32;
   if (TF == 0) return 0;
   if (TQ == 0) return NW;
   const double r = fp_unit_weight(s);
@@ -57,7 +57,7 @@ int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
 }
 
 void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
-  const int TQ = (n_q + 63) / 64, TF = (n_fp + 31) / 32;
+  const int TQ = tiles_of(s, n_q), TF = (n_fp + 31) / 32;
   const double r = fp_unit_weight(s);
   const double units = TQ + r * TF;
   const int hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);

@@ -81,6 +81,9 @@ struct AttnParams {
   int cus;            // workgroups of 4 from this index on are the younger of a pair (the compute units planned for)
   int W, Wq;          // of every Wq quantized slots (one filtering event) the first W hold tokens
   int n_tok_q;        // tokens in the n_q quantized slots
+  int tiles;          // tiles_of(n_q)
+  LiveTiles live;     // key groups of 64 and 128: the tiles that hold tokens
+  uint32_t dead_bit;  // an offset past the end of every array of a slice (0: none; padding is then read)
   int dynamic;        // 0: static tile schedule only
   float c;  // softmax scale * log2(e)
 };
@@ -355,17 +358,18 @@ __device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float*
 // two workgroups on every compute unit; 12 (three wavefronts per SIMD, at most 168
 // registers) for long contexts, where the extra wavefront hides more than the tighter
 // register budget costs.
-// GENERAL: the variant that also handles padding slots in the quantized region (group
-// size not dividing the window) and per-sequence counts.  The other instantiations carry
-// neither check.
-// per-sequence state in the kernel arguments: only the general instantiation has any
-template <bool GENERAL> struct SeqArgs {};
-template <> struct SeqArgs<true> { SeqState e[SEQ_CHUNK]; };
+// KIND: EQUAL: rows of one length, no padding; PER_ROW: counts per row (per-sequence lengths); PADDED: padding slots in
+// the quantized region (group size not dividing the window), with either.  Each carries no more than it needs: as one
+// variant, the search for the tiles that hold tokens cost rows without padding 3% (scalar registers spill).
+enum { EQUAL, PER_ROW, PADDED };
+// per-sequence state in the kernel arguments
+template <int KIND> struct SeqArgs { SeqState e[SEQ_CHUNK]; };
+template <> struct SeqArgs<EQUAL> {};
 
 // PROG: how fp rows and tiles are dealt to the wavefronts, see lq_schedule.h.
-template <bool BF16, int D, int G, int NWB, int BITS, bool GENERAL, int PROG>
+template <bool BF16, int D, int G, int NWB, int BITS, int KIND, int PROG>
 __global__ void __launch_bounds__(64 * NWB, NWB == 12 ? 3 : 2)
-attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
+attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN;
   constexpr int NKC = D / 32, NNT = D / 16, NGC = (D + G - 1) / G;
   constexpr int WPL = NKC * (BITS / 2);           // code words per lane and 32-slot block
@@ -397,7 +401,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   }
   const int hsub = group % nhg;
   int bh = group / nhg;
-  if constexpr (GENERAL) {
+  if constexpr (KIND != EQUAL) {
     // per-sequence lengths: workgroups are dispatched in index order, so the rows are
     // taken longest first (seq[i].order = the row with the i-th most tokens)
     if (P.seq_mode) {
@@ -413,11 +417,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   // counts and live fp buffer: the same for every sequence, or (per-sequence lengths)
   // read from the sequence's entry of the state array
   int n_fp = P.n_fp, n_q = P.n_q, nwf = P.nwf, n_tok_q = P.n_tok_q, cur = 0;
-  if constexpr (GENERAL) {
+  int TQ = P.tiles;
+  if constexpr (KIND != EQUAL) {
     if (P.seq_mode) {
       const SeqState sq = P.seq_mode == 1 ? seq_load(seq_in_args(args_offset_after(sizeof(AttnParams))), bh / P.Hkv)
                                           : P.seq[bh / P.Hkv];
-      n_fp = sq.n_fp; n_q = sq.n_q; nwf = sq.nwf; n_tok_q = sq.n_tok_q; cur = sq.cur;
+      n_fp = sq.n_fp; n_q = sq.n_q; nwf = sq.nwf; n_tok_q = sq.n_tok_q; cur = sq.cur; TQ = sq.item;
     }
   }
   // (a select between two kernel arguments, not a load that depends on `cur`)
@@ -426,7 +431,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   int32_t* pos_fp = cur ? P.pos_fp[1] : P.pos_fp[0];
   const uint16_t* k_fp = k_fp_w;
   const uint16_t* v_fp = v_fp_w;
-  const int TQ = (n_q + 63) >> 6, TF = (n_fp + 31) >> 5;
+  const int TF = (n_fp + 31) >> 5;
   const Deal<PROG, NWB> deal(P.splits, split, wave, nwf, TF);
   const bool one_split = ONE || (!DRAW && P.splits == 1);
   // Of wavefronts that share a SIMD the older one wins the issue slots: with two to a SIMD and a static schedule the
@@ -678,6 +683,17 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       }
       return r;
     };
+    // Where tile t lies; dead: the bit that takes the loads of its second half out of range (they then return zeros and
+    // read nothing) when that half is padding.
+    struct Place { int t; uint32_t dead; int slot0; };
+    auto place = [&](int t) {
+      if constexpr (KIND == PADDED && G >= 64) {
+        const LiveTiles::Place p = P.live.place(t);
+        return Place{p.tile, p.slot0 + 32 >= P.W ? P.dead_bit : 0u, p.slot0};
+      } else {
+        return Place{t, 0u, 0};
+      }
+    };
     auto load_kmeta = [&](Tile& T, int t) {
 #pragma unroll
       for (int e = 0; e < NGRP; ++e) {
@@ -686,15 +702,18 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         T.kz8[e] = load16(rs_kz, km_off, (uint32_t)grp * (D * 2));
       }
     };
-    auto load_kcodes = [&](Tile& T, int t) {
+    auto load_kcodes = [&](Tile& T, const Place& pl) {
+      const int t = pl.t;
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2)
-        T.kc[b2] = load_words(rs_kc, code_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
+        T.kc[b2] = load_words(rs_kc, b2 ? code_off | pl.dead : code_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
     };
-    auto load_v = [&](Tile& T, int t, int b2) {
-      T.vc[b2] = load_words(rs_vc, code_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
-      T.vs[b2] = load16(rs_vs, vm_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
-      T.vz[b2] = load16(rs_vz, vm_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
+    auto load_v = [&](Tile& T, const Place& pl, int b2) {
+      const int t = pl.t;
+      const uint32_t c_off = b2 ? code_off | pl.dead : code_off, m_off = b2 ? vm_off | pl.dead : vm_off;
+      T.vc[b2] = load_words(rs_vc, c_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
+      T.vs[b2] = load16(rs_vs, m_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
+      T.vz[b2] = load16(rs_vz, m_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
     };
 
     // Tiles that are drawn.  The first two of a wavefront without units are fixed, and the loads of the first go out
@@ -711,7 +730,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
     // (per-sequence lengths) the atomic is aimed out of range.
     // A single split has no last workgroup that could re-arm the pool counters for the
     // next launch (it returns before the ticket): static as well.
-    constexpr bool MAY_DRAW = DRAW || (GENERAL && !ONE);
+    constexpr bool MAY_DRAW = DRAW || (KIND != EQUAL && !ONE);
     const bool dyn = DRAW || (MAY_DRAW && P.seq_mode && !one_split && draws_tiles(P.dynamic, P.splits * NWB, nwf, TF, TQ));
     const __amdgpu_buffer_rsrc_t pool = __builtin_amdgcn_make_buffer_rsrc(
         P.counters + (group * CTR_LINES + 1 + (MAY_DRAW ? deal.pool() : 0)) * CTR_LINE, 0, 4, 0x00020000);
@@ -727,11 +746,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       tb = drawn_tile(kb);
     }
     Tile A;
+    Place pa = place(ta);
     if (ta < TQ) {
-      load_kmeta(A, ta);
-      load_kcodes(A, ta);
-      load_v(A, ta, 0);
-      load_v(A, ta, 1);
+      load_kmeta(A, pa.t);
+      load_kcodes(A, pa);
+      load_v(A, pa, 0);
+      load_v(A, pa, 1);
     }
     // q of (head q4, channels 8*c8..+7): fp16 pairs for the bias dot products, and
     // fp16 pairs pre-multiplied by 2^(3-2v) (v = pair index) for the q*s operands
@@ -774,7 +794,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       if (lane < 32) { p_lds[wave][0][4][lane] = 0; p_lds[wave][1][4][lane] = 0; }
     }
 
-    auto process = [&](Tile& cur, int t, int tn) {   // tn: the tile to refill the registers with
+    auto process = [&](Tile& cur, const Place& pl, const Place& tn) {   // tn: the tile to refill the registers with
+      const int t = pl.t;
       // ---- q*s (fp16 head and tail) and bias = sum_c q_c z_c for each key group
       float bo[4];
       {
@@ -812,7 +833,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
           }
           bias[e] = row_sum(bp) * P.c;
         }
-        load_kmeta(cur, tn);
+        load_kmeta(cur, tn.t);
 #pragma unroll
         for (int u = 0; u < 4; ++u) bo[u] = bias[(u * NGRP) >> 2] + offs[u];
       }
@@ -848,11 +869,11 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
         for (int u = 0; u < 4; ++u)
           if (64 * t + 16 * u + n16 >= n_q) s[u] = -INFINITY;
       }
-      if (GENERAL && P.Wq != P.W) {
+      if constexpr (KIND == PADDED) {
         // padding slots behind a short key group (zero codes, zero value scales and
         // zero-points): a finite sentinel, so that a tile made of padding only leaves
         // a state whose weight in every later merge is exactly 0
-        const int r0 = (64 * t) % P.Wq;
+        const int r0 = G >= 64 ? pl.slot0 : (64 * t) % P.Wq;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           int r = r0 + 16 * u + n16;
@@ -941,10 +962,11 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
       while (true) {
         const bool more = tb < TQ;
         const int kd = draw();                 // for the tile after tb
-        process(A, ta, more ? tb : ta);
+        const Place pb = place(more ? tb : ta);
+        process(A, pa, pb);
         if (ONE && NWB != 12 && ta >= own_half) __builtin_amdgcn_s_setprio(0);
         if (!more) break;
-        ta = tb;
+        ta = tb; pa = pb;
         tb = dyn ? drawn_tile(kd) : deal.after(tb);
       }
     }
@@ -1189,36 +1211,36 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<GENERAL> S) {
   }
 }
 
-template <bool BF16, int D, int NWB, int BITS, int PROG>
-static hipError_t launch_mfma_dg(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  if (s.Wq != s.W || seq) {
-    SeqArgs<true> S;
+template <bool BF16, int D, int NWB, int BITS, int KIND, int PROG>
+static hipError_t launch_mfma_g(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
+  SeqArgs<KIND> S;
+  if constexpr (KIND != EQUAL)
     if (seq && seq->in_args())
       for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
-    switch (s.G) {
-      case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-      case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-      default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, true, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    }
-    return launch_status(__func__);
-  }
-  const SeqArgs<false> S;
   switch (s.G) {
-    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, false, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
   }
   return launch_status(__func__);
 }
 
+template <bool BF16, int D, int NWB, int BITS, int PROG>
+static hipError_t launch_mfma_k(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
+  if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, PADDED, PROG>(s, P, seq, grid, st);
+  if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws, in APART)
+    if (seq) return launch_mfma_g<BF16, D, NWB, BITS, PER_ROW, PROG>(s, P, seq, grid, st);
+  return launch_mfma_g<BF16, D, NWB, BITS, EQUAL, PROG>(s, P, seq, grid, st);
+}
+
 template <bool BF16, int D, int NWB, int BITS>
 static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = (P.n_q + 63) / 64;
-  if (P.splits == 1 && P.n_q > 0) return launch_mfma_dg<BF16, D, NWB, BITS, ONE_SPLIT>(s, P, seq, grid, st);
+  const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = P.tiles;
+  if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, ONE_SPLIT>(s, P, seq, grid, st);
   // (with counts per sequence each row decides for itself, in the kernel)
   if (P.splits > 1 && !seq && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
-    return launch_mfma_dg<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
-  return launch_mfma_dg<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
+    return launch_mfma_k<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
+  return launch_mfma_k<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
 }
 
 template <bool BF16, int NWB, int BITS>
@@ -1230,7 +1252,7 @@ static hipError_t launch_mfma_d(const Shape& s, const AttnParams& P, const SeqAr
   }
 }
 
-// One source file for each of these (lq_attn_mfma_w*.hip): 432 kernels in all, which as one file took four minutes.
+// One source file for each of these (lq_attn_mfma_w*.hip): several hundred kernels in all, which as one file took many minutes.
 template <int NWB, int BITS>
 hipError_t launch_mfma_t(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   return s.bf16 ? launch_mfma_d<true, NWB, BITS>(s, P, seq, grid, st)

@@ -34,7 +34,9 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.ws = ws.partials;
   P.out = (uint16_t*)out;
   P.cap = s.cap; P.qcap = s.qcap; P.n_fp = c.n_fp; P.n_q = c.n_q; P.gh = s.gh;
-  P.W = s.W; P.Wq = s.Wq; P.n_tok_q = quantized_tokens(s, c.n_q);
+  P.W = s.W; P.Wq = s.Wq; P.live.set(s.W, s.Wq);
+  P.dead_bit = (int64_t)s.qcap * s.d * s.bits / 8 <= ((int64_t)1 << 31) ? 0x80000000u : 0u;   // (codes: the largest array)
+  P.tiles = tiles_of(s, c.n_q); P.n_tok_q = quantized_tokens(s, c.n_q);
   P.hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
   P.splits = plan.splits; P.nwf = plan.fp_waves; P.cus = seq && pairs_workgroups(plan) ? 1 << 30 : compute_units();
   P.c = scale * 1.4426950408889634f;

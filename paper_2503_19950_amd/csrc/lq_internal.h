@@ -25,7 +25,7 @@ struct SeqState {
   int cur;            // which fp buffer is live
   int nwf;            // attention: wavefronts of a head group that keep to the fp rows where a share of them does
   int n_tok_q;        // tokens held in the n_q slots
-  int item;           // compress: the i-th entry names the i-th sequence that is compressed
+  int item;           // compress: the i-th entry names the i-th sequence that is compressed; attention: tiles_of(n_q)
   int flag;           // append: 1 if the sequence takes a token; prefill: prompt length
   int order;          // attention: the i-th entry names the row with the i-th most tokens
 };
@@ -132,6 +132,9 @@ int compute_units();   // of the device the launches are planned for
 inline bool pairs_workgroups(const lq_plan& plan) {
   return plan.waves_per_block == 4 && plan.blocks > compute_units() && plan.blocks <= 2 * compute_units();
 }
+// Tiles of n_q quantized slots that the attention kernel deals out: those that hold tokens, where padding comes in
+// whole tiles (LiveTiles), else all.
+inline int tiles_of(const Shape& s, int n_q) { return s.G >= 64 ? n_q / s.Wq * ((s.W + 63) / 64) : (n_q + 63) / 64; }
 // How many wavefronts' worth of time (of the NW a head group has) n_fp fp rows take beside
 // n_q quantized slots.
 int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q);

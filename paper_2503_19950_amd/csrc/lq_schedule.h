@@ -1,6 +1,7 @@
 // How the attention kernel's work is dealt to wavefronts: fp rows in units of 32, quantized rows in tiles of 64.
 // Integer arithmetic only, used by the kernel, by the choice of its program on the host, and by the host test.
 #pragma once
+#include <stdint.h>
 #ifdef __HIP__
 #define LQ_HD __host__ __device__ __forceinline__
 #else
@@ -12,6 +13,28 @@ namespace lq {
 // Pools of tiles that wavefronts draw from, per head group.  Several, because atomics on one address are serialised at
 // a rate that a single counter could not sustain.
 constexpr int NSUB = 8;
+
+// The tiles that hold tokens.  A filtering event takes Wq slots, its W tokens first; with key groups of 64 or 128 slots
+// that is a whole number of tiles, of which those behind the last token are padding: they are not dealt, and nothing of
+// them is read (17 rows of 17970 tokens, 8 kv heads, W = 39, groups of 128, d = 96: half of the tiles, 117 -> 68 us a
+// launch), nor of the second half of a tile where that is padding (2 rows of 28243 tokens, 32 kv heads, W = 212, groups
+// of 64, 4 bits: 46.4 -> 43.7).  Tiles are numbered through the live ones; place() finds a tile in the buffers.
+struct LiveTiles {
+  int per_event, pad;   // ceil(W / 64) tiles of an event that hold tokens, and the Wq / 64 - per_event that do not
+  uint32_t inv;         // ceil(2^31 / per_event)
+  void set(int W, int Wq) {
+    per_event = (W + 63) / 64;
+    pad = Wq / 64 - per_event;
+    inv = (uint32_t)(((uint64_t)1 << 31) / per_event + (((uint64_t)1 << 31) % per_event != 0));
+  }
+  struct Place { int tile, slot0; };   // index of the tile among all, padding included; its first slot within its event
+  LQ_HD Place place(int t) const {
+    int e = (int)(((uint64_t)(2u * (uint32_t)t) * inv) >> 32);   // t / per_event, or one more (t < 2^30)
+    int j = t - e * per_event;
+    if (j < 0) { --e; j += per_event; }
+    return Place{t + e * pad, 64 * j};
+  }
+};
 
 // Three programs, chosen per launch.  The wavefronts of all workgroups of a head group are numbered 0..NW-1.
 //  APART      a share of the wavefronts, NWF, keeps to the units, the others walk the tiles and have their first loads

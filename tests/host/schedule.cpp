@@ -99,7 +99,23 @@ static void all() {
   if (drawn < 300) exit(2);
 }
 
+// Every slot with a token lies in exactly one of the tiles that LiveTiles numbers, at the slot it says.
+static void live_tiles() {
+  for (int i = 0; i < 20000; ++i) {
+    const int G = one_of({64, 128}), W = one_of({1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, any(1, 700), any(1, 60000)});
+    const int Wq = (W + G - 1) / G * G, per_event = (W + 63) / 64;
+    LiveTiles l;
+    l.set(W, Wq);
+    for (int k = 0; k < 8; ++k) {
+      const int e = one_of({0, 1, 2, any(0, 50), (1 << 25) / (Wq / 64)}), j = one_of({0, per_event - 1, any(0, per_event - 1)});
+      const LiveTiles::Place p = l.place(e * per_event + j);
+      if (p.tile != e * (Wq / 64) + j || p.slot0 != 64 * j) { printf("W %d, Wq %d, event %d, tile %d\n", W, Wq, e, j); exit(3); }
+    }
+  }
+}
+
 int main() {
+  live_tiles();
   all<4>();
   all<8>();
   all<12>();

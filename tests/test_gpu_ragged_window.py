@@ -88,3 +88,24 @@ def test_decode_steps_across_events(name, wl, L0, steps):
             U.assert_outputs_close(out[b, h * gh:(h + 1) * gh], want, dt, "step %d (b=%d,h=%d)" % (s, b, h))
     for (b, h), oc in ocs.items():
         U.check_state(dc, oc, wl, b, h)
+
+
+@pytest.mark.parametrize("G,W", [(128, 1), (128, 32), (128, 33), (128, 64), (128, 65), (128, 97), (128, 129), (128, 193),
+                                 (64, 31), (64, 33), (64, 85), (64, 97)])
+def test_padding_in_whole_blocks_is_not_read(G, W):
+    """Blocks of 32 slots that hold nothing but padding are filled with NaN patterns: attention, which zeros there
+    would not show to have read them, gives the same output, and it is the oracle's."""
+    import torch
+    wl = U.make_wl(B=2, Hq=8, Hkv=2, d=64, G=G, F=2 * W, dtype="bf16" if W % 2 else "f16")
+    L = 3 * W + 9 * W + W // 2
+    dc = U.build_gpu_prefill(wl, 660 + W, L)
+    q = inputs.queries(660 + W, 0, wl)
+    ocs = {(b, h): U.build_oracle(wl, 660 + W, L, b, h) for b in range(2) for h in range(2)}
+    U.check_attention(dc, ocs, wl, q)
+    before = dc.decode_attn(U.to_dev(q, wl["dtype"]))
+    per_event = -(-W // G) * G // 32
+    dead = [i for i in range(dc.c.n_q // 32) if 32 * (i % per_event) >= W]
+    assert bool(dead) == (W % G <= G - 32)
+    for name in ("k_codes", "v_codes", "v_scale", "v_zero"):
+        getattr(dc, name).view(4, dc.cfg.q_capacity // 32, -1)[:, dead] = 0xFF
+    assert torch.equal(before, dc.decode_attn(U.to_dev(q, wl["dtype"])))
