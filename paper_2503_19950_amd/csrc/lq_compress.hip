@@ -20,8 +20,7 @@ namespace lq {
 template <bool BF16, int BITS>
 __device__ __forceinline__ void group_params(float mn, float mx, float* z, float* s, uint16_t* zt,
                                              uint16_t* st) {
-  if (mn == 0.f) mn = 0.f;  // -0 -> +0 (min/max do not order signed zeros)
-  if (mx == 0.f) mx = 0.f;
+  mn += 0.f;   // -0 -> +0 (of the difference below the signs of zeros change nothing)
   constexpr float STEPS = (float)((1 << BITS) - 1), y = 1.0f / STEPS;
   const float diff = mx - mn;
   const float q0 = diff * y;
@@ -74,25 +73,56 @@ __device__ __forceinline__ u16x2 keys_of(uint32_t w) {   // two T values -> two 
   const i16x2 flip = (x >> 15) | (i16x2)((short)0x8000);   // 0xFFFF for a negative value, 0x8000 otherwise
   return __builtin_bit_cast(u16x2, x ^ flip);
 }
-__device__ __forceinline__ uint32_t key_of(uint16_t bits) { return (bits & 0x8000u) ? (~(uint32_t)bits & 0xFFFFu) : (bits | 0x8000u); }
 __device__ __forceinline__ uint16_t bits_of_key(uint32_t key) { return (uint16_t)((key & 0x8000u) ? (key ^ 0x8000u) : (~key & 0xFFFFu)); }
 
-// key(smallest value of T that is >= t) - 1: a key above it belongs to a value that reaches t.
-// f = fp32(t) and "up" = [f < t] locate t between neighbouring fp32 numbers; h = T(f) is a
-// neighbour of f in T.  The smallest value of T at or above t is h, or the next one upwards
-// (the next key: keys step with the values whatever the sign) when h < f, or when h == f
-// and t lies above f.  A threshold of zero (either sign) is taken as -0, which both zeros
-// reach.  In a flat group (s == 0) every code is 0: 0xFFFF, which no key exceeds.
+// Thresholds as keys.  t = z + (k + 1/2) s rounded up to T, the smallest value of T that reaches t, is t rounded up to
+// fp32 and that rounded up to T (every T value is an fp32 value): one fused multiply-add and one conversion with the
+// wavefront's rounding mode set to "up" for them.  The mode changes inside one asm block and is back to nearest at its
+// end, so that no other instruction can run under it.  (In fp64, with the comparisons that tell on which side of t its
+// rounded value lies, an fp16 threshold took 45 instructions, most of them the conversion from fp64, which the hardware
+// does not have.  Prefill of 64 x 8 slices of 4096 tokens, G = 32, fp16, bound by vector issue at 19 instructions per
+// element, with 12 now: 296 -> 266 us; of 8 rows of up to 8192 tokens 65.3 -> 59.5; bf16, G = 64, 131072 tokens 124.7 -> 122.)
+__device__ __forceinline__ void sum_up(float z0, float s0, float k0, float z1, float s1, float k1, uint32_t* f0, uint32_t* f1) {
+  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"    // fp32 and fp16/fp64 towards +infinity
+      "v_fma_f32 %0, %2, %3, %4\n\t"
+      "v_fma_f32 %1, %5, %6, %7\n\t"
+      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
+      : "=&v"(*f0), "=&v"(*f1) : "v"(k0), "v"(s0), "v"(z0), "v"(k1), "v"(s1), "v"(z1));
+}
+__device__ __forceinline__ void sum_up_f16(float z0, float s0, float k0, float z1, float s1, float k1, uint32_t* f0, uint32_t* f1) {
+  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"
+      "v_fma_f32 %0, %2, %3, %4\n\t"
+      "v_fma_f32 %1, %5, %6, %7\n\t"
+      "v_cvt_f16_f32 %0, %0\n\t"
+      "v_cvt_f16_f32 %1, %1\n\t"
+      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
+      : "=&v"(*f0), "=&v"(*f1) : "v"(k0), "v"(s0), "v"(z0), "v"(k1), "v"(s1), "v"(z1));
+}
+// Two thresholds, z0 + k0 s0 (low half) and z1 + k1 s1, each as key(smallest value of T that reaches it) - 1: a key above
+// it belongs to a value that reaches the threshold.  A threshold of zero (either sign) is taken as -0, which both zeros
+// reach.  In a flat group (s == 0) every code is 0: its thresholds are infinite, the key below infinity's is exceeded by
+// no finite value's.
 template <bool BF16>
-__device__ __forceinline__ uint32_t threshold_key(float zf, float s, float k_plus_half) {
-  const double t = (double)zf + (double)k_plus_half * (double)s;   // exact
-  const float f = (float)t;
-  const bool up = (double)f < t;
-  const uint16_t h = f2t<BF16>(f);
-  const float hb = t2f<BF16>(h);
-  uint32_t key = key_of(h) + ((hb < f || (hb == f && up)) ? 1u : 0u);
-  if (key == 0x8000u) key = 0x7FFFu;
-  return s == 0.f ? 0xFFFFu : key - 1u;
+__device__ __forceinline__ u16x2 threshold_keys(float z0, float s0, float k0, float z1, float s1, float k1) {
+  s0 = s0 == 0.f ? INFINITY : s0;
+  s1 = s1 == 0.f ? INFINITY : s1;
+  uint32_t a, b, w;
+  if constexpr (BF16) {
+    sum_up(z0, s0, k0, z1, s1, k1, &a, &b);
+    // up to the upper 16 bits: a positive number with any of the lower bits set goes to the next, a negative one is cut
+    a += ~(uint32_t)((int32_t)a >> 31) & 0xFFFFu;
+    b += ~(uint32_t)((int32_t)b >> 31) & 0xFFFFu;
+    w = __builtin_amdgcn_perm(b, a, 0x07060302u);
+  } else {
+    sum_up_f16(z0, s0, k0, z1, s1, k1, &a, &b);
+    w = __builtin_amdgcn_perm(b, a, 0x05040100u);
+  }
+  const u16x2 key = keys_of(w);
+  const u16x2 not_zero = __builtin_elementwise_min(key ^ (u16x2)((unsigned short)0x8000), (u16x2)((unsigned short)1));
+  return key + not_zero - (u16x2)((unsigned short)2);   // +0: the key of -0, less one
+}
+__device__ __forceinline__ u16x2 both_halves(uint32_t w, int half) {
+  return __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(w, w, half ? 0x03020302u : 0x01000100u));
 }
 
 // codes of two keys; tk[k]: the two values' k-th thresholds (low half: first value).  [key > t] per half is
@@ -162,6 +192,21 @@ __device__ __forceinline__ void reduce_keys_over_parts(u16x2& mn, u16x2& mx) {
     a = lo(p[0], p[1]); b = hi(q[0], q[1]);
   }
   mn = __builtin_bit_cast(u16x2, a); mx = __builtin_bit_cast(u16x2, b);
+}
+
+// Minimum and maximum over groups of N = 1, 2, 4 or 8 neighbouring lanes: exchanges inside pairs and quads, then a mirrored
+// half row, which hands a quad the other's result.
+template <int CTRL>
+__device__ __forceinline__ void reduce_step(uint32_t* mn, uint32_t* mx) {
+  *mn = min(*mn, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)*mn, CTRL, 0xF, 0xF, false));
+  *mx = max(*mx, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)*mx, CTRL, 0xF, 0xF, false));
+}
+template <int N>
+__device__ __forceinline__ void reduce_over_neighbours(uint32_t* mn, uint32_t* mx) {
+  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "lanes of a group");
+  if constexpr (N >= 2) reduce_step<0xB1>(mn, mx);    // quad_perm:[1,0,3,2]
+  if constexpr (N >= 4) reduce_step<0x4E>(mn, mx);    // quad_perm:[2,3,0,1]
+  if constexpr (N >= 8) reduce_step<0x141>(mn, mx);   // row_half_mirror
 }
 
 // Eight codes (one byte each, in x: elements 0..3, y: elements 4..7) -> the operand
@@ -424,7 +469,7 @@ __device__ __forceinline__ void quantize_group_t(
         u16x2 tk[3];
         {
           const float kh = (float)(lane >> 4) + 0.5f;
-          const uint32_t x = threshold_key<BF16>(z0, s0, kh) | (threshold_key<BF16>(z1, s1, kh) << 16);
+          const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z0, s0, kh, z1, s1, kh));
           const auto eo = __builtin_amdgcn_permlane16_swap(x, x, false, false);       // rows 0 0 2 2 | 1 1 3 3
           const auto e = __builtin_amdgcn_permlane32_swap(eo[0], eo[0], false, false);  // rows 0 0 0 0 | 2 2 2 2
           const auto o = __builtin_amdgcn_permlane32_swap(eo[1], eo[1], false, false);  // rows 1 1 1 1 | 3 3 3 3
@@ -525,10 +570,7 @@ __device__ __forceinline__ void quantize_group_t(
           }
         }
         uint32_t mn = min((uint32_t)mn2.x, (uint32_t)mn2.y), mx = max((uint32_t)mx2.x, (uint32_t)mx2.y);
-        for (int o = 1; o < vp; o <<= 1) {
-          mn = min(mn, (uint32_t)__shfl_xor((int)mn, o));
-          mx = max(mx, (uint32_t)__shfl_xor((int)mx, o));
-        }
+        reduce_over_neighbours<vp>(&mn, &mx);
         float z, sc;
         uint16_t zt, st;
         group_params<BF16, BITS>(t2f<BF16>(bits_of_key(mn)), t2f<BF16>(bits_of_key(mx)), &z, &sc, &zt, &st);
@@ -540,18 +582,23 @@ __device__ __forceinline__ void quantize_group_t(
         // the lanes of a group share out the thresholds and hand them round inside their quad
         u16x2 tk[3];
         if constexpr (vp >= 4) {
-          const uint32_t x = threshold_key<BF16>(z, sc, (float)min(part & 3, 2) + 0.5f) * 0x10001u;
+          const float kh = (float)min(part & 3, 2) + 0.5f;
+          const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, kh, z, sc, kh));
           tk[0] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x00, 0xF, 0xF, false));   // quad_perm:[0,0,0,0]
           tk[1] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x55, 0xF, 0xF, false));   // quad_perm:[1,1,1,1]
           tk[2] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xAA, 0xF, 0xF, false));   // quad_perm:[2,2,2,2]
         } else if constexpr (vp == 2) {
-          const uint32_t x = threshold_key<BF16>(z, sc, (float)part + 0.5f) * 0x10001u;
-          tk[0] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xA0, 0xF, 0xF, false));   // quad_perm:[0,0,2,2]
-          tk[1] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xF5, 0xF, 0xF, false));   // quad_perm:[1,1,3,3]
-          tk[2] = __builtin_bit_cast(u16x2, threshold_key<BF16>(z, sc, 2.5f) * 0x10001u);
+          const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, (float)part + 0.5f, z, sc, 2.5f));
+          const uint32_t own = __builtin_bit_cast(uint32_t, both_halves(x, 0));
+          tk[0] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xA0, 0xF, 0xF, false));   // quad_perm:[0,0,2,2]
+          tk[1] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xF5, 0xF, 0xF, false));   // quad_perm:[1,1,3,3]
+          tk[2] = both_halves(x, 1);
         } else {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) tk[k] = __builtin_bit_cast(u16x2, threshold_key<BF16>(z, sc, (float)k + 0.5f) * 0x10001u);
+          const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, 0.5f, z, sc, 1.5f));
+          const uint32_t y = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, 2.5f, z, sc, 2.5f));
+          tk[0] = both_halves(x, 0);
+          tk[1] = both_halves(x, 1);
+          tk[2] = __builtin_bit_cast(u16x2, y);
         }
         const u16x2 t20 = tk[2] - tk[0];
 #pragma unroll
