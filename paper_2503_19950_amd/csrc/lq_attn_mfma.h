@@ -1046,7 +1046,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     }
   };
 
-  if constexpr (PROG != APART) {
+  if constexpr (ONE || DRAW) {
     if (deal.takes_units(TF)) { fp_rows(deal.unit0, deal.unit_step); hand_over(); }
     quantized_rows();
   } else if (deal.takes_tiles()) {
@@ -1228,7 +1228,7 @@ static hipError_t launch_mfma_g(const Shape& s, const AttnParams& P, const SeqAr
 template <bool BF16, int D, int NWB, int BITS, int PROG>
 static hipError_t launch_mfma_k(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, PADDED, PROG>(s, P, seq, grid, st);
-  if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws, in APART)
+  if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws)
     if (seq) return launch_mfma_g<BF16, D, NWB, BITS, PER_ROW, PROG>(s, P, seq, grid, st);
   return launch_mfma_g<BF16, D, NWB, BITS, EQUAL, PROG>(s, P, seq, grid, st);
 }
@@ -1240,7 +1240,10 @@ static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqAr
   // (with counts per sequence each row decides for itself, in the kernel)
   if (P.splits > 1 && !seq && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
     return launch_mfma_k<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
-  return launch_mfma_k<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
+  if constexpr (NWB == 8)
+    if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y >= compute_units()))
+      return launch_mfma_k<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
+  return launch_mfma_k<BF16, D, NWB, BITS, BY_SPLIT>(s, P, seq, grid, st);
 }
 
 template <bool BF16, int NWB, int BITS>

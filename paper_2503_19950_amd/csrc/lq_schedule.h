@@ -36,7 +36,11 @@ struct LiveTiles {
   }
 };
 
-// Three programs, chosen per launch.  The wavefronts of all workgroups of a head group are numbered 0..NW-1.
+// Four programs, chosen per launch.  The wavefronts of all workgroups of a head group are numbered 0..NW-1: place by place
+// (the first wavefronts of all splits, then the second ones, ..), so that those that get the most - units, or one tile
+// more than others - are the older ones of every compute unit, each with a lighter one on its SIMD.  (Numbered split by
+// split the first workgroups had all of it: 8 rows of 8192 tokens, 4 splits, wavefronts done between 11.5 and 17.6 us;
+// four layers 69.0 -> 66.5 us, 4 rows of 8192 48.5 -> 44.3, 1 of 20000 41.5 -> 39.4.)
 //  APART      a share of the wavefronts, NWF, keeps to the units, the others walk the tiles and have their first loads
 //             on the way before anything else.  For several splits with few tiles per wavefront, and for launches
 //             without tiles.  (With units and tiles in the same wavefronts and the deal worked out from the counts,
@@ -49,12 +53,24 @@ struct LiveTiles {
 //             0 or 2 rounds measured 1 to 2% slower).
 //  DRAWN      several splits, many tiles: the units fall on different compute units, the tiles are drawn from the pools,
 //             and the wavefronts with a unit join in when they are done with it.
-enum { APART, ONE_SPLIT, DRAWN };
+//  BY_SPLIT   APART with another numbering of the wavefronts.
+enum { APART, ONE_SPLIT, DRAWN, BY_SPLIT };
 
 // Several splits: whether the tiles are drawn.  At least five tiles for each wavefront that an even deal would give
 // them to, and more wavefronts than pools, also of those that start without a unit.
 LQ_HD bool draws_tiles(int dynamic, int NW, int nwf, int TF, int TQ) {
   return dynamic && NW - TF > NSUB && NW - nwf > NSUB && TQ >= 5 * (NW - nwf);
+}
+
+// APART or BY_SPLIT, for workgroups of 8: with fewer than two tiles for a wavefront, every compute unit in use and more
+// than an eighth of the wavefronts at the units, these are kept together in the first workgroups and leave the others to
+// nothing but tiles (8 rows of 2048 tokens, 9 of 32 wavefronts at the units, four layers 37.9 against 39.5 us; 4 of 3000
+// 35.2 against 36.1; but 1 row of 2048, 56 workgroups, 32.9 against 31.6).  A program of its own: a choice in the kernel
+// delays the first load (8 rows of 4096 tokens 47.7 -> 48.1 us).  Workgroups of 4 and 12 always are BY_SPLIT: of 4, two
+// share a compute unit, and place by place both would have their units on the same SIMD (38 rows of up to 10277 tokens
+// 162 against 143 us); of 12, none of the shapes measured gains (31898 tokens, 8 heads of 8, 72.5 against 71.5 us).
+LQ_HD bool keeps_units_together(int NW, int nwf, int TQ, bool chip_full) {
+  return chip_full && TQ < 2 * (NW - nwf) && 8 * nwf > NW;
 }
 
 template <int PROG, int NWB>
@@ -65,13 +81,13 @@ struct Deal {
   int step1;             // from the first tile to the second, where they are not drawn
   int pool_of;           // the pool it draws from
 
-  // split, wave: this wavefront; nwf: the share of wavefronts for the units in APART; TF: number of units
+  // split, wave: this wavefront; nwf: the share of wavefronts for the units in APART and BY_SPLIT; TF: number of units
   LQ_HD Deal(int splits, int split, int wave, int nwf, int TF) {
     const int NW = PROG == ONE_SPLIT ? NWB : splits * NWB;
     NWF = PROG == ONE_SPLIT ? 0 : PROG == DRAWN ? (TF < NW ? TF : NW) : nwf;
     NWQ = NW - NWF;
-    unit0 = PROG == ONE_SPLIT ? wave : PROG == DRAWN ? wave * splits + split : split * NWB + wave;
-    unit_step = PROG == APART ? NWF : NW;
+    unit0 = PROG == ONE_SPLIT ? wave : PROG == BY_SPLIT ? split * NWB + wave : wave * splits + split;
+    unit_step = PROG == APART || PROG == BY_SPLIT ? NWF : NW;
     if (PROG == ONE_SPLIT) {
       const int nh = TF % NWB, nl = NWB - nh;   // wavefronts with one unit more, and the others
       const bool ahead = nh > 0 && wave >= nh;
@@ -85,12 +101,13 @@ struct Deal {
       // wavefronts of a workgroup are faster.  (Numbered like the units, a pool belonged to one workgroup at 2, 4 and 8
       // splits, and one that started late kept all its tiles; with one place to a pool, 131072 tokens of 4-bit codes
       // took 144 instead of 137 us for four layers; with neighbouring places, shapes of 3, 5 and 9 splits 2 to 4% more.)
+      // In the others only wavefronts without units draw; any eight in a row cover all pools.
       const int gw = split * NWB + wave;
-      pool_of = (PROG == DRAWN ? 3 * gw + gw / NSUB : first) % NSUB;
+      pool_of = (PROG == DRAWN ? 3 * gw + gw / NSUB : PROG == APART ? first + 3 * (first / NSUB) : first) % NSUB;
     }
   }
-  LQ_HD bool takes_units(int TF) const { return unit0 < (PROG == APART ? NWF : TF); }
-  LQ_HD bool takes_tiles() const { return PROG != APART || unit0 >= NWF; }
+  LQ_HD bool takes_units(int TF) const { return unit0 < (PROG == APART || PROG == BY_SPLIT ? NWF : TF); }
+  LQ_HD bool takes_tiles() const { return PROG == ONE_SPLIT || PROG == DRAWN || unit0 >= NWF; }
   // Tiles that are not drawn: the second, then every NWQ-th.
   LQ_HD int second() const { return first + step1; }
   LQ_HD int after(int t) const { return t + NWQ; }

@@ -89,8 +89,10 @@ static void all() {
     const int NS = one_of({1, 2, 3, 4, 5, 8, 16, 32, any(1, 64)}), NW = NS * NWB;
     const int nwf = TQ == 0 ? NW : any(1, TF < NW - 1 ? TF : NW - 1);   // as fp_wave_share gives it
     check<APART, NWB>(NS, nwf, TF, TQ, false);
+    check<BY_SPLIT, NWB>(NS, nwf, TF, TQ, false);
     if (NS > 1 && draws_tiles(1, NW, nwf, TF, TQ)) {
       check<APART, NWB>(NS, nwf, TF, TQ, true);
+      check<BY_SPLIT, NWB>(NS, nwf, TF, TQ, true);
       check<DRAWN, NWB>(NS, nwf, TF, TQ, true);
       ++drawn;
     }
