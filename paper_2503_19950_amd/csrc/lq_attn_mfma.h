@@ -78,6 +78,8 @@ struct AttnParams {
   int seq_mode;           // 0: counts below hold for every sequence; 1: state in the kernel arguments
   int Hkv;
   int cap, qcap, n_fp, n_q, gh, hb, splits, nwf;
+  int across;         // groups side by side in the grid (its first dimension)
+  Divisor div_subgroups, div_kv_heads;   // by the head groups of a kv head (gh / hb), by the kv heads
   int cus;            // workgroups of 4 from this index on are the younger of a pair (the compute units planned for)
   int W, Wq;          // of every Wq quantized slots (one filtering event) the first W hold tokens
   int n_tok_q;        // tokens in the n_q quantized slots
@@ -388,26 +390,19 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nhg = P.gh / P.hb;
-  // Workgroups are handed to the eight XCDs in turn (linear index mod 8).  When the
-  // number of groups allows it, all splits of one group are placed on one XCD, so
-  // that the partials they exchange at the end meet in that XCD's L2.
-  int split = ONE ? 0 : blockIdx.x, group = blockIdx.y;
-  if (!ONE && gridDim.y % 8 == 0) {
-    const int L = blockIdx.y * gridDim.x + blockIdx.x;
-    const int r = L >> 3;
-    group = (L & 7) + 8 * (r / (int)gridDim.x);
-    split = r % (int)gridDim.x;
-  }
-  const int hsub = group % nhg;
-  int bh = group / nhg;
+  // Workgroups are handed to the eight XCDs in turn (linear index mod 8).  When the number of groups is a multiple of 8
+  // the grid is (8, splits, groups / 8): all splits of one group are placed on one XCD, so that the partials they
+  // exchange at the end meet in that XCD's L2.  Else it is (1, splits, groups).
+  const int split = ONE ? 0 : blockIdx.y, group = blockIdx.z * P.across + blockIdx.x;
+  int bh = P.div_subgroups.quotient(group);
+  const int hsub = group - bh * P.div_subgroups.n;
   if constexpr (KIND != EQUAL) {
     // per-sequence lengths: workgroups are dispatched in index order, so the rows are
     // taken longest first (seq[i].order = the row with the i-th most tokens)
     if (P.seq_mode) {
-      const int i = bh / P.Hkv;
+      const int i = P.div_kv_heads.quotient(bh);
       bh = (P.seq_mode == 1 ? seq_in_args(args_offset_after(sizeof(AttnParams)))[i].order : P.seq[i].order) * P.Hkv +
-           bh % P.Hkv;   // (the argument block is P, then S)
+           bh - i * P.Hkv;   // (the argument block is P, then S)
     }
   }
   const int q4 = lane >> 4, n16 = lane & 15, up = n16 >> 2, g = lane & 3;
@@ -420,8 +415,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   int TQ = P.tiles;
   if constexpr (KIND != EQUAL) {
     if (P.seq_mode) {
-      const SeqState sq = P.seq_mode == 1 ? seq_load(seq_in_args(args_offset_after(sizeof(AttnParams))), bh / P.Hkv)
-                                          : P.seq[bh / P.Hkv];
+      const int b = P.div_kv_heads.quotient(bh);
+      const SeqState sq = P.seq_mode == 1 ? seq_load(seq_in_args(args_offset_after(sizeof(AttnParams))), b) : P.seq[b];
       n_fp = sq.n_fp; n_q = sq.n_q; nwf = sq.nwf; n_tok_q = sq.n_tok_q; cur = sq.cur; TQ = sq.item;
     }
   }
@@ -441,7 +436,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   // of their tiles, which lets both end together (206 -> 199 us; a batch of 64 x 4096 tokens 47.6 -> 46.6 us a step,
   // with rows of different lengths 46.4 -> 45.0; three and five eighths of the tiles measured up to 1% slower).
   // (Not where the younger of a pair of workgroups has the shorter row: see pairs_workgroups.)
-  const bool young = ONE && (NWB == 8 ? wave >= 4 : NWB == 4 && (int)blockIdx.y >= P.cus);
+  const bool young = ONE && (NWB == 8 ? wave >= 4 : NWB == 4 && group >= P.cus);
   const int own_half = young ? (deal.first + TQ) / 2 : 0;
   if (young) __builtin_amdgcn_s_setprio(1);
   const int64_t part_base = (((int64_t)bh * P.splits + split) * P.gh + hsub * P.hb) * (D + 4);
@@ -789,8 +784,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     const uint16_t* p_hd = &p_lds[wave][0][!row_live ? 4 : g][4 * q4];
     uint16_t* p_wr = &p_lds[wave][0][q4][n16];
     {
+#pragma unroll
       for (int e = 0; e < NGRP; ++e)
-        for (int c = lane; c < QS_ROW; c += 64) qs_lds[wave][e][12][c] = 0;
+        if (lane < QS_ROW / 8) *reinterpret_cast<uint4*>(&qs_lds[wave][e][12][8 * lane]) = make_uint4(0, 0, 0, 0);
       if (lane < 32) { p_lds[wave][0][4][lane] = 0; p_lds[wave][1][4][lane] = 0; }
     }
 
@@ -1241,7 +1237,7 @@ static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqAr
   if (P.splits > 1 && !seq && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
     return launch_mfma_k<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
   if constexpr (NWB == 8)
-    if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y >= compute_units()))
+    if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y * grid.z >= compute_units()))
       return launch_mfma_k<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
   return launch_mfma_k<BF16, D, NWB, BITS, BY_SPLIT>(s, P, seq, grid, st);
 }

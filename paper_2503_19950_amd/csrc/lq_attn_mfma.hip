@@ -42,7 +42,10 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.c = scale * 1.4426950408889634f;
   static const int dynamic = [] { const char* v = getenv("LOGQUANT_ATTN_DYNAMIC"); return v && *v ? atoi(v) : 1; }();
   P.dynamic = dynamic;
-  dim3 grid(plan.splits, s.B * s.Hkv * (s.gh / P.hb));
+  const int groups = s.B * s.Hkv * (s.gh / P.hb);
+  P.across = groups % 8 == 0 ? 8 : 1;
+  P.div_subgroups.set(s.gh / P.hb); P.div_kv_heads.set(s.Hkv);
+  const dim3 grid(P.across, plan.splits, groups / P.across);
   if (plan.waves_per_block == 12 && s.bits == 2) return launch_mfma_t<12, 2>(s, P, seq, grid, st);
   if (plan.waves_per_block == 4)
     return s.bits == 4 ? launch_mfma_t<4, 4>(s, P, seq, grid, st) : launch_mfma_t<4, 2>(s, P, seq, grid, st);

@@ -116,7 +116,18 @@ static void live_tiles() {
   }
 }
 
+static void divisors() {
+  for (int i = 0; i < 200000; ++i) {
+    Divisor d;
+    const int n = one_of({1, 2, 3, 7, 8, 32, 255, 256, any(1, 300), any(1, 32767)}), top = 0x7FFFFFFF / n;
+    const int q = any(0, top / n > 65535 ? 65535 : top / n), x = one_of({q * n, q * n + n - 1, any(0, 65535)});
+    d.set(n);
+    if ((int64_t)x * n < 0x7FFFFFFF && d.quotient(x) != x / n) { printf("%d / %d\n", x, n); exit(4); }
+  }
+}
+
 int main() {
+  divisors();
   live_tiles();
   all<4>();
   all<8>();
