@@ -725,6 +725,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     // (per-sequence lengths) the atomic is aimed out of range.
     // A single split has no last workgroup that could re-arm the pool counters for the
     // next launch (it returns before the ticket): static as well.
+    // q goes out ahead of the first tile: loads return in order, so that its operands are ready when the key scales arrive,
+    // and not when the whole tile has (Q_FIRST).  Not with 12 wavefronts, whose registers are short.
+    constexpr bool Q_FIRST = NWB != 12;
     constexpr bool MAY_DRAW = DRAW || (KIND != EQUAL && !ONE);
     const bool dyn = DRAW || (MAY_DRAW && P.seq_mode && !one_split && draws_tiles(P.dynamic, P.splits * NWB, nwf, TF, TQ));
     const __amdgpu_buffer_rsrc_t pool = __builtin_amdgcn_make_buffer_rsrc(
@@ -740,6 +743,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       ta = drawn_tile(ka);
       tb = drawn_tile(kb);
     }
+    const int64_t qrow_q = ((int64_t)bh * P.gh + hsub * P.hb + (headq_ok ? q4 : 0)) * D;
+    uint4 raw;
+    if constexpr (Q_FIRST) raw = *reinterpret_cast<const uint4*>(P.q + qrow_q + (prep ? 8 * c8 : 0));
     Tile A;
     Place pa = place(ta);
     if (ta < TQ) {
@@ -753,9 +759,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     uint32_t qraw[4];
     half2_t qz[4], qh[4];
     {
-      const int64_t qrow_q = ((int64_t)bh * P.gh + hsub * P.hb + (headq_ok ? q4 : 0)) * D;
-      uint4 raw = *reinterpret_cast<const uint4*>(P.q + qrow_q + (prep ? 8 * c8 : 0));
-      if (!prep || !headq_ok) raw = make_uint4(0, 0, 0, 0);
+      if constexpr (!Q_FIRST) raw = *reinterpret_cast<const uint4*>(P.q + qrow_q + (prep ? 8 * c8 : 0));
+      const uint32_t keep = prep && headq_ok ? 0xFFFFFFFFu : 0u;   // (a branch here waits for the tile)
+      raw.x &= keep; raw.y &= keep; raw.z &= keep; raw.w &= keep;
       qraw[0] = raw.x; qraw[1] = raw.y; qraw[2] = raw.z; qraw[3] = raw.w;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
