@@ -36,7 +36,7 @@ __device__ __forceinline__ void group_params(float mn, float mx, float* z, float
 // Encoder of one group: round-half-up of (x - z)/s clamped to 0..2^BITS-1, by
 // threshold compares on the exact (fp64) difference; (k + 0.5) * s is exact in fp64.
 // The thresholds grow with k, so with 4 bits the number of them that x - z reaches is found
-// by bisection (BITS compares instead of 2^BITS - 1).
+// by bisection (BITS compares instead of 2^BITS - 1).  Only for 4-bit groups whose scale FourBit does not cover.
 template <int BITS>
 struct Encoder {
   double z, sd;
@@ -53,6 +53,39 @@ struct Encoder {
     return flat ? 0u : c;
   }
 };
+// The codes of four values of a 4-bit group.  w = (x - z) / s approximately, 1/8 too high: floor(w + 1/2) is the code or
+// one more than it, and which one the exact comparison with that code's threshold tells, z + (c - 1/2) s rounded up to
+// fp32 (x, a value of T, reaches the sum exactly when it reaches that).  The error of w stays far below 1/8: |z| / s is
+// at most 2 * 15 * 2^11 and three fp32 roundings make 0.02 of it.
+// (Bisection over fp64 thresholds, four comparisons a value, made prompts with 4-bit codes bound by vector issue: 131072
+// tokens, bf16, G = 64, 239 -> 139 us; 64 rows of 4096, fp16, G = 32, 479 -> 291; 8 of up to 8192 101 -> 66.)
+struct FourBit {
+  float z, s, r, b;
+  bool usual;   // s == 0 or far within the range of the fp32 reciprocal; else Encoder (bf16 only)
+  __device__ __forceinline__ FourBit(float zf, float sf) : z(zf), s(sf) {
+    usual = s == 0.f || (s >= 0x1p-100f && s <= 0x1p100f);
+    r = s == 0.f ? 0.f : __builtin_amdgcn_rcpf(s);   // (s == 0: every code is 0)
+    b = __fmaf_rn(-z, r, 0.625f);
+  }
+  __device__ __forceinline__ void operator()(const float (&x)[4], uint32_t (&c)[4]) const {
+    float f[4], t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f[i] = fminf(floorf(__fmaf_rn(x[i], r, b)), 15.f);
+      t[i] = f[i] - 0.5f;
+    }
+    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"    // as in sum_up
+        "v_fma_f32 %0, %0, %4, %5\n\t"
+        "v_fma_f32 %1, %1, %4, %5\n\t"
+        "v_fma_f32 %2, %2, %4, %5\n\t"
+        "v_fma_f32 %3, %3, %4, %5\n\t"
+        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
+        : "+&v"(t[0]), "+&v"(t[1]), "+&v"(t[2]), "+&v"(t[3]) : "v"(s), "v"(z));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] = (uint32_t)f[i] - (x[i] < t[i] ? 1u : 0u);
+  }
+};
+
 // ---- 2-bit groups: statistics and codes on order-preserving 16-bit keys, two values per
 // instruction.  The bits of a T value (sign, then magnitude) map to an unsigned key that
 // orders like the value: negative values have every bit flipped, the others the sign bit
@@ -506,12 +539,31 @@ __device__ __forceinline__ void quantize_group_t(
         *reinterpret_cast<uint32_t*>(k_scale + mi) = (uint32_t)st0 | ((uint32_t)st1 << 16);
         *reinterpret_cast<uint32_t*>(k_zero + mi) = (uint32_t)zt0 | ((uint32_t)zt1 << 16);
       }
-      const Encoder<BITS> enc0(z0, s0), enc1(z1, s1);
-#pragma unroll
-      for (int i = 0; i < per; ++i) {
-        const uint32_t c0 = enc0(t2f<BF16>((uint16_t)xv[i])), c1 = enc1(t2f<BF16>((uint16_t)(xv[i] >> 16)));
+      const FourBit q0(z0, s0), q1(z1, s1);
+      auto put = [&](int i, uint32_t c0, uint32_t c1) {
         *reinterpret_cast<uint16_t*>(cb + (e0 + i) * KP + 2 * cp) =
             (FULL || e0 + i < ng) ? (uint16_t)(c0 | (c1 << 8)) : (uint16_t)0;
+      };
+      if (q0.usual && q1.usual) {
+        static_assert(per % 4 == 0, "four tokens at a time");
+#pragma unroll
+        for (int i = 0; i < per; i += 4) {
+          float x0[4], x1[4];
+          uint32_t c0[4], c1[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) { x0[k] = t2f<BF16>((uint16_t)xv[i + k]); x1[k] = t2f<BF16>((uint16_t)(xv[i + k] >> 16)); }
+          q0(x0, c0);
+          q1(x1, c1);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) put(i + k, c0[k], c1[k]);
+        }
+      } else {
+        const Encoder<BITS> enc0(z0, s0), enc1(z1, s1);
+#pragma unroll 1
+        for (int i = 0; i < per; ++i) {
+          const uint32_t x = *reinterpret_cast<const uint32_t*>(sm + (e0 + i) * ldk + 2 * cp);
+          put(i, enc0(t2f<BF16>((uint16_t)x)), enc1(t2f<BF16>((uint16_t)(x >> 16))));
+        }
       }
       }
     }
@@ -635,15 +687,23 @@ __device__ __forceinline__ void quantize_group_t(
         v_scale[mi] = st;
         v_zero[mi] = zt;
       }
-      const Encoder<BITS> enc(z, sc);
+      const FourBit q4(z, sc);
+      if (q4.usual) {
 #pragma unroll
-      for (int k = 0; k < PER / 4; ++k)
-        if (4 * k < n) {
-          col[(4 * k + 0) * VP] = (uint8_t)enc(t2f<BF16>((uint16_t)xv[k].x));
-          col[(4 * k + 1) * VP] = (uint8_t)enc(t2f<BF16>((uint16_t)(xv[k].x >> 16)));
-          col[(4 * k + 2) * VP] = (uint8_t)enc(t2f<BF16>((uint16_t)xv[k].y));
-          col[(4 * k + 3) * VP] = (uint8_t)enc(t2f<BF16>((uint16_t)(xv[k].y >> 16)));
-        }
+        for (int k = 0; k < PER / 4; ++k)
+          if (4 * k < n) {
+            const float x[4] = {t2f<BF16>((uint16_t)xv[k].x), t2f<BF16>((uint16_t)(xv[k].x >> 16)),
+                                t2f<BF16>((uint16_t)xv[k].y), t2f<BF16>((uint16_t)(xv[k].y >> 16))};
+            uint32_t c[4];
+            q4(x, c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col[(4 * k + i) * VP] = (uint8_t)c[i];
+          }
+      } else {
+        const Encoder<BITS> enc(z, sc);
+#pragma unroll 1
+        for (int i = 0; i < n; ++i) col[i * VP] = (uint8_t)enc(t2f<BF16>(row[i]));
+      }
       }
     }
   }

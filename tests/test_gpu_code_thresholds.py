@@ -57,3 +57,18 @@ def test_codes_at_thresholds(dt, bits, d, G, W):
             dc.stream_in(Kd, Vd)
         U.check_state(dc, oc, wl, 0, 0)
     assert len({int(c) for c in np.unique(oc.K_codes)}) == 1 << bits and len({int(c) for c in np.unique(oc.V_codes)}) == 1 << bits
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("exponent", [-125, -112, -101, -99])
+def test_codes_of_tiny_bf16_values(bits, exponent):
+    """Scales on both sides of what the fp32 reciprocal covers."""
+    wl = U.make_wl(B=1, Hq=1, Hkv=1, d=64, G=32, F=64, dtype="bf16", bits=bits)
+    rng = np.random.default_rng([bits, -exponent])
+    K, V = (np.ldexp(rng.integers(-100, 101, (32 * 6, 64)), exponent - 3).astype(np.float32) for _ in range(2))
+    oc = SliceCache(32, 32, 64, "bf16", bits)
+    oc.append_block(K, V)
+    dc = U.new_cache(wl, len(K))
+    dc.prefill(U.to_dev(K[None, None], "bf16"), U.to_dev(V[None, None], "bf16"))
+    U.check_state(dc, oc, wl, 0, 0)
+    assert len(np.unique(oc.K_codes)) == 1 << bits
