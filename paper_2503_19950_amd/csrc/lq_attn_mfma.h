@@ -324,10 +324,12 @@ __device__ __forceinline__ void online_softmax(State<NNT>& st, const float* s, f
 // output step uses them, and the denominator sums these rounded values.  Numerator and
 // denominator then describe the same (slightly perturbed) weights, so that the rounding
 // cancels where one token dominates instead of scaling the whole output.
+// slack: by how much a logit may exceed the reference before that moves.  The token that moved it last has the probability
+// 2^PSHIFT, which rounds without error.
 template <int NNT, bool ROUND_P>
-__device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float* s, float* p, int g) {
+__device__ __forceinline__ void online_softmax_rows(State<NNT>& st, const float* s, float* p, int g, float slack) {
   float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-  if (__any(mx > st.m + MAX_SLACK)) {
+  if (__any(mx > st.m + slack)) {
     mx = row_max(mx);
     const float m_new = fmaxf(st.m, mx);
     const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);   // 0 on the first tile (m = -inf)
@@ -622,6 +624,14 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     // and its code is large) the part the rounding drops is carried as well: in the
     // residual rows when there are two pieces, in a second product otherwise.
     constexpr bool PROD_LO = !BF16;
+    // With one piece the rounding of p is the largest error before the output's own.  A wavefront's heaviest token has none
+    // of it if it is the one that the reference was taken from, so that a row with half the wavefronts, each with twice the
+    // tiles, is further off: 64 rows of up to 4096 tokens, fp16, against 64 bits and without the output's rounding
+    // 1.29e-4 (2-norm) with 8 wavefronts, 1.39e-4 with 4.  Rows of different lengths take workgroups of 4 where equal rows
+    // take 8 or 12: there the reference follows the maximum more closely (at a scale of 2 / sqrt(d), squares off 64 bits, the
+    // output's rounding included, as a multiple of those with 8: 1.034 with the usual slack, 1.004 with a slack of 2,
+    // 0.991 with 1; 64 rows of up to 4096 tokens, 16 steps 662 -> 667 us, ten shapes 1.2% on average).
+    constexpr float SLACK = VPIECES == 1 && NWB == 4 && KIND != EQUAL ? 1.f : MAX_SLACK;
     const bool row_live = up < VPIECES * NGC;
     const int upc = row_live ? up % NGC : 0;          // channel group of this lane's row
     const bool tail_row = VPIECES == 2 && up >= NGC;  // this lane feeds the residual piece
@@ -894,7 +904,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
           if (r >= P.W) s[u] = DEAD_LOGIT;
         }
       }
-      online_softmax_rows<NNT, VPIECES == 1>(st, s, p, g);
+      online_softmax_rows<NNT, VPIECES == 1>(st, s, p, g, SLACK);
 
       // ---- hand the probabilities (fp16) to the lanes that feed the output step
 #pragma unroll
