@@ -10,19 +10,20 @@
 
 namespace lq {
 
-// Division by a number that the host knows.  Exact for x * n < 2^31.  The attention kernel's start is one chain of scalar
-// operations up to its first load: of 180 instructions half were divisions by kernel arguments, and the grid's size for
-// them was a second argument load (now 60 to 90 and, without counts per row, one wait: 512 tokens 7.92 -> 7.77 us a
-// launch; 8 rows of 8192, four layers, 69.0 -> 67.0; 64 rows of up to 4096, 16 steps, 671 -> 664; 8 rows of 2048
-// 37.6 -> 36.7).
+// Division by a number that the host knows, exact for x >= 0 and (x + 1) * n <= 2^32: the reciprocal is rounded down, and
+// x + 1 taken instead of x makes up for it.  (B * Hq is at most 65535, and with it every x and n here.)  The attention
+// kernel's start is one chain of scalar operations up to its first load: of 180 instructions half were divisions by kernel
+// arguments, and the grid's size for them was a second argument load (now 60 to 90 and, without counts per row, one wait:
+// 512 tokens 7.92 -> 7.77 us a launch; 8 rows of 8192, four layers, 69.0 -> 67.0; 64 rows of up to 4096, 16 steps,
+// 671 -> 664; 8 rows of 2048 37.6 -> 36.7).
 struct Divisor {
   int n;
-  uint32_t inv;   // ceil(2^31 / n)
+  uint32_t inv;   // floor((2^32 - 1) / n)
   void set(int d) {
     n = d;
-    inv = (uint32_t)(((uint64_t)1 << 31) / d + (((uint64_t)1 << 31) % d != 0));
+    inv = 0xFFFFFFFFu / (uint32_t)d;
   }
-  LQ_HD int quotient(int x) const { return (int)(((uint64_t)(2u * (uint32_t)x) * inv) >> 32); }
+  LQ_HD int quotient(int x) const { return (int)(((uint64_t)((uint32_t)x + 1u) * inv) >> 32); }
 };
 
 // Pools of tiles that wavefronts draw from, per head group.  Several, because atomics on one address are serialised at

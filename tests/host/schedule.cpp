@@ -116,13 +116,14 @@ static void live_tiles() {
   }
 }
 
+// What the kernel divides: numbers below B * Hq <= 65535, by a factor of that product.
 static void divisors() {
-  for (int i = 0; i < 200000; ++i) {
+  for (int n = 1; n <= 65535; ++n) {
     Divisor d;
-    const int n = one_of({1, 2, 3, 7, 8, 32, 255, 256, any(1, 300), any(1, 32767)}), top = 0x7FFFFFFF / n;
-    const int q = any(0, top / n > 65535 ? 65535 : top / n), x = one_of({q * n, q * n + n - 1, any(0, 65535)});
     d.set(n);
-    if ((int64_t)x * n < 0x7FFFFFFF && d.quotient(x) != x / n) { printf("%d / %d\n", x, n); exit(4); }
+    const int last = 65535 / n * n - 1;   // the largest number there is with this divisor
+    for (int x : {0, 1, n - 1, n, n + 1, last / n * n, last, any(0, last), any(0, last)})
+      if (x <= last && d.quotient(x) != x / n) { printf("%d / %d\n", x, n); exit(4); }
   }
 }
 
