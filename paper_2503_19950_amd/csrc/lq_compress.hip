@@ -5,6 +5,7 @@
 // the front of the other fp buffer.
 #include "lq_device.h"
 #include "lq_internal.h"
+#include "lq_round_up.h"
 
 namespace lq {
 
@@ -74,13 +75,7 @@ struct FourBit {
       f[i] = fminf(floorf(__fmaf_rn(x[i], r, b)), 15.f);
       t[i] = f[i] - 0.5f;
     }
-    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"    // as in sum_up
-        "v_fma_f32 %0, %0, %4, %5\n\t"
-        "v_fma_f32 %1, %1, %4, %5\n\t"
-        "v_fma_f32 %2, %2, %4, %5\n\t"
-        "v_fma_f32 %3, %3, %4, %5\n\t"
-        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
-        : "+&v"(t[0]), "+&v"(t[1]), "+&v"(t[2]), "+&v"(t[3]) : "v"(s), "v"(z));
+    fma_up(t, s, z);
 #pragma unroll
     for (int i = 0; i < 4; ++i) c[i] = (uint32_t)f[i] - (x[i] < t[i] ? 1u : 0u);
   }
@@ -109,28 +104,11 @@ __device__ __forceinline__ u16x2 keys_of(uint32_t w) {   // two T values -> two 
 __device__ __forceinline__ uint16_t bits_of_key(uint32_t key) { return (uint16_t)((key & 0x8000u) ? (key ^ 0x8000u) : (~key & 0xFFFFu)); }
 
 // Thresholds as keys.  t = z + (k + 1/2) s rounded up to T, the smallest value of T that reaches t, is t rounded up to
-// fp32 and that rounded up to T (every T value is an fp32 value): one fused multiply-add and one conversion with the
-// wavefront's rounding mode set to "up" for them.  The mode changes inside one asm block and is back to nearest at its
-// end, so that no other instruction can run under it.  (In fp64, with the comparisons that tell on which side of t its
+// fp32 and that rounded up to T (every T value is an fp32 value): one fused multiply-add and one conversion (lq_round_up.h).
+// (In fp64, with the comparisons that tell on which side of t its
 // rounded value lies, an fp16 threshold took 45 instructions, most of them the conversion from fp64, which the hardware
 // does not have.  Prefill of 64 x 8 slices of 4096 tokens, G = 32, fp16, bound by vector issue at 19 instructions per
 // element, with 12 now: 296 -> 266 us; of 8 rows of up to 8192 tokens 65.3 -> 59.5; bf16, G = 64, 131072 tokens 124.7 -> 122.)
-__device__ __forceinline__ void sum_up(float z0, float s0, float k0, float z1, float s1, float k1, uint32_t* f0, uint32_t* f1) {
-  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"    // fp32 and fp16/fp64 towards +infinity
-      "v_fma_f32 %0, %2, %3, %4\n\t"
-      "v_fma_f32 %1, %5, %6, %7\n\t"
-      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
-      : "=&v"(*f0), "=&v"(*f1) : "v"(k0), "v"(s0), "v"(z0), "v"(k1), "v"(s1), "v"(z1));
-}
-__device__ __forceinline__ void sum_up_f16(float z0, float s0, float k0, float z1, float s1, float k1, uint32_t* f0, uint32_t* f1) {
-  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 5\n\t"
-      "v_fma_f32 %0, %2, %3, %4\n\t"
-      "v_fma_f32 %1, %5, %6, %7\n\t"
-      "v_cvt_f16_f32 %0, %0\n\t"
-      "v_cvt_f16_f32 %1, %1\n\t"
-      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 4), 0"
-      : "=&v"(*f0), "=&v"(*f1) : "v"(k0), "v"(s0), "v"(z0), "v"(k1), "v"(s1), "v"(z1));
-}
 // Two thresholds, z0 + k0 s0 (low half) and z1 + k1 s1, each as key(smallest value of T that reaches it) - 1: a key above
 // it belongs to a value that reaches the threshold.  A threshold of zero (either sign) is taken as -0, which both zeros
 // reach.  In a flat group (s == 0) every code is 0: its thresholds are infinite, the key below infinity's is exceeded by
