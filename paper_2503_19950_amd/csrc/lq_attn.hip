@@ -80,9 +80,16 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
     int smax = (int)ceil(units / wpb);            // at least one unit per wavefront
     if (smax > max_splits(s)) smax = max_splits(s);
     if (smax < 1) smax = 1;
+    const bool unsplit_8 = best < 1e300 && best_splits == 1;   // (wpb == 4: what the candidates of 8 came to)
     for (int sp = 1; sp <= smax; ++sp) {
       if (force_splits && sp != force_splits && force_splits <= smax) continue;
       const int rounds = (sp * groups + slots - 1) / slots;
+      // Rows of different lengths, more workgroups than fit at once: the last round is one of short rows and never full,
+      // so that 8 wavefronts are done sooner than their count of rounds says.  Where they would not split, 4 do not
+      // either (33 to 40 rows of up to 2000 or 3000 tokens, 8 kv heads, 45 tiles a row, 8 launches: 8 wavefronts unsplit
+      // 238-264 us, 4 in three splits 255-283, 4 unsplit 223-259); where 8 would split as well, three splits of 4 are
+      // the better ones (36 rows of 6000 352 against 370 us unsplit, 34 of 12000 536 against 594).
+      if (wpb == 4 && rows == DIFFERENT_LENGTHS && sp > 1 && rounds > 1 && unsplit_8) break;
       // more than one split adds the cross-workgroup merge: a chain of memory round trips
       // (store, ticket, fetch) worth about a tile and a half (measured on the smallest
       // workload: 8.4 us with three splits, 6.8 us with one)

@@ -197,6 +197,23 @@ def test_launch_plans_of_the_five_workloads():
     assert B.logquant_decode_plan(rag4, 200, 128 * 8).waves_per_block == 8
 
 
+def test_plans_of_rows_of_different_lengths_over_several_rounds():
+    """More workgroups than the chip holds at once: 4 wavefronts are not split where 8 would not be."""
+    def plan(rows, L, **kw):
+        cfg = _cfg(B=rows, q_capacity=16384, **kw)
+        W, G = cfg.fp_budget // 2, cfg.group
+        lengths = [L - L // 2 * b // rows for b in range(rows)]
+        events = [(x - 3 * W) // W + 1 for x in lengths]
+        p = B.logquant_decode_plan_seq(cfg, [x - e * W for x, e in zip(lengths, events)], [-(-W // G) * G * e for e in events])
+        return p.waves_per_block, p.splits
+    assert plan(33, 2000, fp_budget=84) == (4, 1)
+    assert plan(40, 2000, fp_budget=84) == (4, 1)
+    assert plan(40, 2000, fp_budget=84, group=64) == (4, 1)
+    assert plan(36, 3000, fp_budget=64) == (4, 1)
+    assert plan(36, 6000, fp_budget=256) == (4, 3)     # 8 wavefronts: 2 splits
+    assert plan(9, 4400, fp_budget=256) == (4, 7)      # one round
+
+
 def test_plan_counts_live_slots_only_and_state_checks_use_slots():
     # W = 42, G = 64: 64 slots per filtering event, 42 of them hold tokens; key scales and
     # zero-points exist once per 64 slots
