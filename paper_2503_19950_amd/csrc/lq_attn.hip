@@ -68,6 +68,7 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   const double fixed = 2.5, per_split = 0.02, merge_tail = 1.5;
   int best_wpb = 8, best_splits = 1;
   double best = 1e300;
+  bool keep_8 = false;
   for (int wpb = 8; wpb >= 4; wpb -= 4) {   // (12 is derived from 8 below)
     if (force_wpb && force_wpb != 12 && wpb != force_wpb) continue;
     // Rows of different lengths: 4 wavefronts win as they do for lock-step rows (two workgroups to a compute unit cover
@@ -89,11 +90,22 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
       // either (33 to 40 rows of up to 2000 or 3000 tokens, 8 kv heads, 45 tiles a row, 8 launches: 8 wavefronts unsplit
       // 238-264 us, 4 in three splits 255-283, 4 unsplit 223-259); where 8 would split as well, three splits of 4 are
       // the better ones (36 rows of 6000 352 against 370 us unsplit, 34 of 12000 536 against 594).
-      if (wpb == 4 && rows == DIFFERENT_LENGTHS && sp > 1 && rounds > 1 && unsplit_8) break;
+      const bool instead_of_unsplit_8 = wpb == 4 && rows == DIFFERENT_LENGTHS && sp > 1 && unsplit_8;
+      if (instead_of_unsplit_8 && rounds > 1) break;
       // more than one split adds the cross-workgroup merge: a chain of memory round trips
       // (store, ticket, fetch) worth about a tile and a half (measured on the smallest
       // workload: 8.4 us with three splits, 6.8 us with one)
       const double t = rounds * (units / ((double)sp * wpb) + fixed) + per_split * sp + (sp > 1 ? merge_tail : 0.0);
+      // At least four tiles to each of their wavefronts: with fewer there is little to split, and every row pays for the
+      // merge.  Of 160 shapes of 3 to 86 tiles, four layers, those with fewer than 48 take 8 unsplit 0.75 to 1.08 of the time
+      // of 4 in three splits, 0.95 on average (8 kv heads, d = 128: 20 rows of 1106 tokens, 12 tiles, 49 against 66 us, 21 of
+      // 878 50 against 60, 18 of 2261, 27 tiles, 4 bits 71 against 73), the others 0.96 to 1.15 (21 of 4196, 60 tiles, 90
+      // against 85).  8, and not the 12 below, which take up to 1.2 times as long there (20 of 1106 57, 18 of 2484, 34 tiles,
+      // 72 against 62).
+      if (instead_of_unsplit_8 && TQ < 4 * sp * wpb) {
+        keep_8 = keep_8 || t < best - 1e-9;
+        continue;
+      }
       if (t < best - 1e-9) { best = t; best_wpb = wpb; best_splits = sp; }
     }
   }
@@ -104,7 +116,7 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   // codes it was measured to make no difference: 37.3 against 37.2 us).
   // (and only when the launch fits the chip in one round: with more workgroups than
   // compute units, as in a batch of 64 rows with per-row counts, 8 is faster: 49 against 54 us)
-  if (s.bits == 2 && (force_wpb == 12 || (!force_wpb && best_wpb == 8 && units / (best_splits * 8.0) >= 6.0 &&
+  if (s.bits == 2 && (force_wpb == 12 || (!force_wpb && best_wpb == 8 && !keep_8 && units / (best_splits * 8.0) >= 6.0 &&
                                           (int64_t)best_splits * groups <= cus)))
     best_wpb = 12;
   const int splits = best_splits, WPB = best_wpb;

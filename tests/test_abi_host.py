@@ -214,6 +214,24 @@ def test_plans_of_rows_of_different_lengths_over_several_rounds():
     assert plan(9, 4400, fp_budget=256) == (4, 7)      # one round
 
 
+def test_plans_of_rows_of_different_lengths_with_few_tiles():
+    """4 wavefronts are not split where 8 would not be and a wavefront would have fewer than four tiles."""
+    def plan(rows, L, **kw):
+        cfg = _cfg(B=rows, q_capacity=64 * kw["fp_budget"] // 2, **kw)
+        W, G = cfg.fp_budget // 2, cfg.group
+        lengths = [L - L // 2 * b // rows for b in range(rows)]
+        events = [0 if x < 3 * W else (x - 3 * W) // W + 1 for x in lengths]
+        n_q = [-(-W // G) * G * e for e in events]
+        p = B.logquant_decode_plan_seq(cfg, [x - e * W for x, e in zip(lengths, events)], n_q)
+        return max(n_q) // 64, p.waves_per_block, p.splits
+    assert plan(20, 1106, fp_budget=256, group=64) == (12, 8, 1)
+    assert plan(21, 878, fp_budget=256, group=64, dtype="bf16") == (8, 8, 1)
+    assert plan(20, 793, fp_budget=448, bits=4) == (3, 8, 1)
+    assert plan(20, 3250, fp_budget=256) == (46, 8, 1)
+    assert plan(20, 3400, fp_budget=256) == (48, 4, 3)
+    assert plan(12, 621, fp_budget=256) == (4, 4, 5)   # 8 wavefronts: 2 splits
+
+
 def test_plan_counts_live_slots_only_and_state_checks_use_slots():
     # W = 42, G = 64: 64 slots per filtering event, 42 of them hold tokens; key scales and
     # zero-points exist once per 64 slots
