@@ -187,9 +187,8 @@ def test_launch_plans_of_the_five_workloads():
     assert (p4.waves_per_block, p4.splits) == (4, 1)
     # 4-bit codes are not built for 12-wavefront workgroups
     assert B.logquant_decode_plan(_cfg(bits=4, **shapes[3][0]), 512, 130560).waves_per_block == 8
-    # the variant that skips padding slots (window not a multiple of the group size) exists for 8 and
-    # 12 wavefronts (never 4): 12 when a wavefront gets six tiles or more and the launch fits the chip
-    # in one round, else 8
+    # lock-step rows with padding slots (window not a multiple of the group size) get 8 or 12 wavefronts, never 4 (on
+    # average they are slower): 12 when a wavefront gets six tiles or more and the launch fits the chip in one round
     rag = _cfg(fp_budget=84, group=64, dtype="bf16", q_capacity=3200 * 64)
     assert B.logquant_decode_plan(rag, 100, 3118 * 64).waves_per_block == 12
     rag4 = _cfg(B=64, fp_budget=170, group=64, q_capacity=128 * 48)

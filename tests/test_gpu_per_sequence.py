@@ -139,8 +139,8 @@ def test_equal_lengths_give_the_lock_step_result_bit_for_bit():
     oa, ob = a.decode_attn(q), b.decode_attn_seq(q)
     torch.cuda.synchronize()
     if os.environ.get("LOGQUANT_ATTN_WPB") == "4":
-        # a forced 4-wavefront shape applies to the lock-step launch only (the per-sequence kernel
-        # is built for 8 and 12 wavefronts): the tiles are then summed in another order
+        # forced workgroups of 4 wavefronts: rows with counts of their own then let the softmax reference follow the
+        # maximum more closely than lock-step rows do (d = 128, G = 32), and other probabilities are rounded
         assert (oa.float() - ob.float()).abs().max().item() <= U.TOL["f16"] / 2
     else:
         assert torch.equal(oa, ob)
