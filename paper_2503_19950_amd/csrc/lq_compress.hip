@@ -205,8 +205,7 @@ __device__ __forceinline__ void reduce_keys_over_parts(u16x2& mn, u16x2& mx) {
   mn = __builtin_bit_cast(u16x2, a); mx = __builtin_bit_cast(u16x2, b);
 }
 
-// Minimum and maximum over groups of N = 1, 2, 4 or 8 neighbouring lanes: exchanges inside pairs and quads, then a mirrored
-// half row, which hands a quad the other's result.
+// Minimum and maximum over pairs or quads of neighbouring lanes: exchanges inside them.
 template <int CTRL>
 __device__ __forceinline__ void reduce_step(uint32_t* mn, uint32_t* mx) {
   *mn = min(*mn, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)*mn, CTRL, 0xF, 0xF, false));
@@ -214,10 +213,9 @@ __device__ __forceinline__ void reduce_step(uint32_t* mn, uint32_t* mx) {
 }
 template <int N>
 __device__ __forceinline__ void reduce_over_neighbours(uint32_t* mn, uint32_t* mx) {
-  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "lanes of a group");
-  if constexpr (N >= 2) reduce_step<0xB1>(mn, mx);    // quad_perm:[1,0,3,2]
-  if constexpr (N >= 4) reduce_step<0x4E>(mn, mx);    // quad_perm:[2,3,0,1]
-  if constexpr (N >= 8) reduce_step<0x141>(mn, mx);   // row_half_mirror
+  static_assert(N == 2 || N == 4, "lanes of a group");
+  reduce_step<0xB1>(mn, mx);                          // quad_perm:[1,0,3,2]
+  if constexpr (N == 4) reduce_step<0x4E>(mn, mx);    // quad_perm:[2,3,0,1]
 }
 
 // Eight codes (one byte each, in x: elements 0..3, y: elements 4..7) -> the operand
@@ -576,7 +574,8 @@ __device__ __forceinline__ void quantize_group_t(
   // per (token, channel group): VP threads each scan a share of the channels; the
   // shares of one group sit in neighbouring lanes and are combined by lane shuffles
   {
-    constexpr int vp = 2 * G * ngc > 256 ? 1 : 4 * G * ngc > 256 ? 2 : 8 * G * ngc > 256 ? 4 : 8;
+    constexpr int vp = 4 * G * ngc > 256 ? 2 : 4;           // (G * ngc is 64, 96 or 128)
+    static_assert(2 * G * ngc <= 256 && 4 * G * ngc >= 256, "shares of one pass");
     constexpr int PER = ((G < d ? G : d) + vp - 1) / vp;    // channels per thread in a full group
     static_assert(PER % 4 == 0, "a thread's channels are read four at a time");
     for (int idx = tid; idx < G * ngc * vp; idx += 256) {   // a multiple of vp; all lanes of a group take the same trips
@@ -611,24 +610,18 @@ __device__ __forceinline__ void quantize_group_t(
         }
         // the lanes of a group share out the thresholds and hand them round inside their quad
         u16x2 tk[3];
-        if constexpr (vp >= 4) {
+        if constexpr (vp == 4) {
           const float kh = (float)min(part & 3, 2) + 0.5f;
           const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, kh, z, sc, kh));
           tk[0] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x00, 0xF, 0xF, false));   // quad_perm:[0,0,0,0]
           tk[1] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x55, 0xF, 0xF, false));   // quad_perm:[1,1,1,1]
           tk[2] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xAA, 0xF, 0xF, false));   // quad_perm:[2,2,2,2]
-        } else if constexpr (vp == 2) {
+        } else {
           const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, (float)part + 0.5f, z, sc, 2.5f));
           const uint32_t own = __builtin_bit_cast(uint32_t, both_halves(x, 0));
           tk[0] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xA0, 0xF, 0xF, false));   // quad_perm:[0,0,2,2]
           tk[1] = __builtin_bit_cast(u16x2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xF5, 0xF, 0xF, false));   // quad_perm:[1,1,3,3]
           tk[2] = both_halves(x, 1);
-        } else {
-          const uint32_t x = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, 0.5f, z, sc, 1.5f));
-          const uint32_t y = __builtin_bit_cast(uint32_t, threshold_keys<BF16>(z, sc, 2.5f, z, sc, 2.5f));
-          tk[0] = both_halves(x, 0);
-          tk[1] = both_halves(x, 1);
-          tk[2] = __builtin_bit_cast(u16x2, y);
         }
         const u16x2 t20 = tk[2] - tk[0];
 #pragma unroll
