@@ -1250,7 +1250,8 @@ static hipError_t launch_mfma_g(const Shape& s, const AttnParams& P, const SeqAr
 
 template <bool BF16, int D, int NWB, int BITS, int PROG>
 static hipError_t launch_mfma_k(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, PADDED, PROG>(s, P, seq, grid, st);
+  if constexpr (PROG != DRAWN || NWB != 4)
+    if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, PADDED, PROG>(s, P, seq, grid, st);
   if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws)
     if (seq) return launch_mfma_g<BF16, D, NWB, BITS, PER_ROW, PROG>(s, P, seq, grid, st);
   return launch_mfma_g<BF16, D, NWB, BITS, EQUAL, PROG>(s, P, seq, grid, st);
@@ -1260,8 +1261,9 @@ template <bool BF16, int D, int NWB, int BITS>
 static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = P.tiles;
   if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, ONE_SPLIT>(s, P, seq, grid, st);
-  // (with counts per sequence each row decides for itself, in the kernel)
-  if (P.splits > 1 && !seq && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
+  // (With counts per sequence each row decides for itself, in the kernel.  Padded rows of one length are not planned with
+  // 4 wavefronts: forced to, they take their tiles in a fixed order.)
+  if (P.splits > 1 && !seq && !(NWB == 4 && s.Wq != s.W) && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
     return launch_mfma_k<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
   if constexpr (NWB == 8)
     if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y * grid.z >= compute_units()))
