@@ -73,9 +73,10 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
     if (force_wpb && force_wpb != 12 && wpb != force_wpb) continue;
     // Rows of different lengths: 4 wavefronts win as they do for lock-step rows (two workgroups to a compute unit cover
     // each other's start and end: 41 rows of up to 1238 tokens, 8 kv heads 44.4 -> 34.9 us a launch, 64 rows of up to
-    // 4096 44.5 -> 42), but not without tiles (9 rows of up to 540 tokens 9.6 -> 10.0).  Lock-step rows with padding
-    // slots, and equal rows through the per-sequence calls, keep to 8 and 12 (with padding, in several splits, 4 are no
-    // better on average: 6 rows of 125730 tokens 48.6 against 50.9 us, 11 of 27723 67.5 against 65.8).
+    // 4096 44.5 -> 42; with padding, W = 85, G = 64, 52 of 2963, 4 bits, four layers 182 -> 175, W = 42, 19 of 3807 94 -> 79),
+    // but not without tiles (9 rows of up to 540 tokens 9.6 -> 10.0).  Lock-step rows with padding slots, and equal rows
+    // through the per-sequence calls, keep to 8 and 12 (with padding 4 are no better on average: of 100 shapes 0.85 to 1.28
+    // times as long, 1.02 on average, with one split and with several).
     if (wpb == 4 && !force_wpb && (rows == LOCK_STEP ? s.Wq != s.W : rows == SAME_LENGTH || TQ == 0)) continue;
     const int slots = cus * (8 / wpb);
     int smax = (int)ceil(units / wpb);            // at least one unit per wavefront

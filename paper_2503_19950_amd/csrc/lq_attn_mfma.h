@@ -747,7 +747,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     // A single split has no last workgroup that could re-arm the pool counters for the
     // next launch (it returns before the ticket): static as well.
     // q goes out ahead of the first tile: loads return in order, so that its operands are ready when the key scales arrive,
-    // and not when the whole tile has (Q_FIRST).  Not with 12 wavefronts, whose registers are short.
+    // and not when the whole tile has (Q_FIRST).  Not with 12 wavefronts, whose registers are short.  (8 rows of 2048 tokens,
+    // four layers, 41.5 -> 40.5 us, 4 of 8192 44.4 -> 43.3; 54 shapes 0.985 to 1.026 times as fast, 1.002 on average, those
+    // with 4-bit codes among them.)
     constexpr bool Q_FIRST = NWB != 12;
     constexpr bool MAY_DRAW = DRAW || (KIND != EQUAL && !ONE);
     const bool dyn = DRAW || (MAY_DRAW && P.seq_mode && !one_split && draws_tiles(P.dynamic, P.splits * NWB, nwf, TF, TQ));

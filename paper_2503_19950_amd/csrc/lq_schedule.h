@@ -81,7 +81,9 @@ LQ_HD bool draws_tiles(int dynamic, int NW, int nwf, int TF, int TQ) {
 // APART or BY_SPLIT, for workgroups of 8: with fewer than two tiles for a wavefront, every compute unit in use and more
 // than an eighth of the wavefronts at the units, these are kept together in the first workgroups and leave the others to
 // nothing but tiles (8 rows of 2048 tokens, 9 of 32 wavefronts at the units, four layers 37.9 against 39.5 us; 4 of 3000
-// 35.2 against 36.1; but 1 row of 2048, 56 workgroups, 32.9 against 31.6).  A program of its own: a choice in the kernel
+// 35.2 against 36.1; but 1 row of 2048, 56 workgroups, 32.9 against 31.6).  Of 100 shapes with several splits of 8 and tiles
+// that are not drawn, the 9 inside the rule take 0.93 to 1.02 of the time of APART, 0.986 on average, the 91 outside it
+// would take 0.96 to 1.13, 1.028 on average.  A program of its own: a choice in the kernel
 // delays the first load (8 rows of 4096 tokens 47.7 -> 48.1 us).  Workgroups of 4 and 12 always are BY_SPLIT: of 4, two
 // share a compute unit, and place by place both would have their units on the same SIMD (38 rows of up to 10277 tokens
 // 162 against 143 us); of 12, none of the shapes measured gains (31898 tokens, 8 heads of 8, 72.5 against 71.5 us).
@@ -117,7 +119,7 @@ struct Deal {
       // wavefronts of a workgroup are faster.  (Numbered like the units, a pool belonged to one workgroup at 2, 4 and 8
       // splits, and one that started late kept all its tiles; with one place to a pool, 131072 tokens of 4-bit codes
       // took 144 instead of 137 us for four layers; with neighbouring places, shapes of 3, 5 and 9 splits 2 to 4% more.)
-      // In the others only wavefronts without units draw; any eight in a row cover all pools.
+      // In the others only wavefronts without units draw: the first eight cover all pools, and more than eight draw.
       const int gw = split * NWB + wave;
       pool_of = (PROG == DRAWN ? 3 * gw + gw / NSUB : PROG == APART ? first + 3 * (first / NSUB) : first) % NSUB;
     }

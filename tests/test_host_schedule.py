@@ -1,5 +1,5 @@
 """The deal of the attention kernel's work to wavefronts (units of fp rows, tiles of quantized rows): the kernel's own
-arithmetic, csrc/lq_schedule.h, compiled for the host and run for random launches of all three programs, the tiles
+arithmetic, csrc/lq_schedule.h, compiled for the host and run for random launches of all four programs, the tiles
 that are drawn at run time in a random order.  A unit or tile that is left out would silently drop tokens."""
 import os
 import subprocess
