@@ -108,7 +108,7 @@ __device__ __forceinline__ uint16_t bits_of_key(uint32_t key) { return (uint16_t
 // (In fp64, with the comparisons that tell on which side of t its
 // rounded value lies, an fp16 threshold took 45 instructions, most of them the conversion from fp64, which the hardware
 // does not have.  Prefill of 64 x 8 slices of 4096 tokens, G = 32, fp16, bound by vector issue at 19 instructions per
-// element, with 12 now: 296 -> 266 us; of 8 rows of up to 8192 tokens 65.3 -> 59.5; bf16, G = 64, 131072 tokens 124.7 -> 122.)
+// element, with 13 now: 296 -> 266 us; of 8 rows of up to 8192 tokens 65.3 -> 59.5; bf16, G = 64, 131072 tokens 124.7 -> 122.)
 // Two thresholds, z0 + k0 s0 (low half) and z1 + k1 s1, each as key(smallest value of T that reaches it) - 1: a key above
 // it belongs to a value that reaches the threshold.  A threshold of zero (either sign) is taken as -0, which both zeros
 // reach.  In a flat group (s == 0) every code is 0: its thresholds are infinite, the key below infinity's is exceeded by
