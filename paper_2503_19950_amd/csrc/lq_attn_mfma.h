@@ -181,6 +181,11 @@ __device__ __forceinline__ float dot2_h(half2_t a, half2_t b, float c) {
   return __builtin_amdgcn_fdot2(a, b, c, false);
 }
 
+// v of lane `src` (__shfl adds the lane's wavefront to the index, one more register that lives through the kernel)
+__device__ __forceinline__ float from_lane(float v, int src) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * src, __float_as_int(v)));
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
@@ -264,6 +269,15 @@ __device__ __forceinline__ float ld_dev(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void buffer_store16(uint4 x, __amdgpu_buffer_rsrc_t rs, int voff, int soff) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4{x.x, x.y, x.z, x.w}, rs, voff, soff, 0);
+}
+
 template <int N>
 struct Words { uint32_t w[N]; };
 
@@ -300,7 +314,7 @@ __device__ __forceinline__ void online_softmax(State<NNT>& st, const float* s, f
     }
     float a4[4];
 #pragma unroll
-    for (int gg = 0; gg < 4; ++gg) a4[gg] = __shfl(alpha, (threadIdx.x & 60) | gg);
+    for (int gg = 0; gg < 4; ++gg) a4[gg] = from_lane(alpha, (threadIdx.x & 60) | gg);
 #pragma unroll
     for (int nt = 0; nt < NNT; ++nt) {
 #pragma unroll
@@ -426,8 +440,6 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   uint16_t* k_fp_w = cur ? P.k_fp[1] : P.k_fp[0];
   uint16_t* v_fp_w = cur ? P.v_fp[1] : P.v_fp[0];
   int32_t* pos_fp = cur ? P.pos_fp[1] : P.pos_fp[0];
-  const uint16_t* k_fp = k_fp_w;
-  const uint16_t* v_fp = v_fp_w;
   const int TF = (n_fp + 31) >> 5;
   const Deal<PROG, NWB> deal(P.splits, split, wave, nwf, TF);
   const bool one_split = ONE || (!DRAW && P.splits == 1);
@@ -454,12 +466,11 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   // ------------------------- original-precision rows -------------------------
   auto fp_rows = [&](const int unit0, const int unit_step) __attribute__((always_inline)) {
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
-    const uint16_t* kb = k_fp + fp_slice + lane * 8;
-    const uint16_t* vb = v_fp + fp_slice + lane * 8;
+    const int lane16 = lane * 16;
     uint4 qreg[NKC];
 #pragma unroll
     for (int kc = 0; kc < NKC; ++kc) {
-      qreg[kc] = *reinterpret_cast<const uint4*>(P.q + qrow + 32 * kc + 8 * q4);
+      qreg[kc] = *reinterpret_cast<const uint4*>((const char*)P.q + (uint32_t)((qrow + 32 * kc + 8 * q4) * 2));
       if (!head_ok) qreg[kc] = make_uint4(0, 0, 0, 0);
     }
     // Fused append: the wavefront that owns the unit receiving the new row fetches the row
@@ -470,23 +481,29 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     uint4 kn_r[NKC];
     uint32_t vn_r[NNT];
     if (owner) {
-      const uint16_t* kn = P.k_new + (int64_t)bh * D;
-      const uint16_t* vn = P.v_new + (int64_t)bh * D;
+      const char* kn = (const char*)(P.k_new + (int64_t)bh * D);
+      const char* vn = (const char*)(P.v_new + (int64_t)bh * D);
 #pragma unroll
-      for (int kc = 0; kc < NKC; ++kc) kn_r[kc] = *reinterpret_cast<const uint4*>(kn + 32 * kc + 8 * q4);
+      for (int kc = 0; kc < NKC; ++kc) kn_r[kc] = *reinterpret_cast<const uint4*>(kn + 64 * kc + (uint32_t)(16 * q4));
 #pragma unroll
-      for (int nt = 0; nt < NNT; ++nt) vn_r[nt] = vn[16 * nt + n16];
+      for (int nt = 0; nt < NNT; ++nt) vn_r[nt] = *reinterpret_cast<const uint16_t*>(vn + 32 * nt + (uint32_t)(2 * n16));
     }
     for (int unit = unit0; unit < TF; unit += unit_step) {
+      // Buffer accesses, one descriptor for the keys of a unit and one for its values: as 64-bit lane addresses the
+      // compiler kept a pair of registers for each load and store, and with 12 wavefronts spilled up to 20 for d = 128.
+      // A kernel with scratch memory starts later (29 rows x 8 kv heads x 1548 tokens, one launch 21.9 -> 18.1 us, 26 of
+      // 4206, one head per kv head 32.5 -> 26.8, 15 of 21020 51.4 -> 48.3, one of 131072 24.0 -> 23.5).
+      const auto rs_kf = __builtin_amdgcn_make_buffer_rsrc(k_fp_w + fp_slice + (int64_t)unit * (32 * D), 0, 32 * D * 2, 0x00020000);
+      const auto rs_vf = __builtin_amdgcn_make_buffer_rsrc(v_fp_w + fp_slice + (int64_t)unit * (32 * D), 0, 32 * D * 2, 0x00020000);
       uint4 ka[2][NKC], va[NNT];
 #pragma unroll
       for (int uu = 0; uu < 2; ++uu)
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc)
-          ka[uu][kc] = *reinterpret_cast<const uint4*>(kb + ((int64_t)(2 * unit + uu) * NKC + kc) * 512);
+          ka[uu][kc] = buffer_load16(rs_kf, lane16, (uu * NKC + kc) * 1024);
 #pragma unroll
       for (int nt = 0; nt < NNT; ++nt)
-        va[nt] = *reinterpret_cast<const uint4*>(vb + ((int64_t)unit * NNT + nt) * 512);
+        va[nt] = buffer_load16(rs_vf, lane16, nt * 1024);
 
       if (owner && unit == new_unit) {
         // Fused append.  This wavefront is the only reader of the unit that receives
@@ -500,7 +517,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
             const uint4 x = kn_r[kc];
             if (uu_ == 0) ka[0][kc] = x; else ka[1][kc] = x;
             if (hsub == 0)
-              *reinterpret_cast<uint4*>(k_fp_w + fp_slice + lane * 8 + ((int64_t)(2 * unit + uu_) * NKC + kc) * 512) = x;
+              buffer_store16(x, rs_kf, lane16 + kc * 1024, uu_ * (NKC * 1024));
           }
         }
         const int kx = new_kx;         // element kx & 7 of the lanes of token octet kx >> 3
@@ -515,7 +532,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
               if (i == wi) w[i] = (w[i] & ~(0xFFFFu << sh)) | (e << sh);
             va[nt] = make_uint4(w[0], w[1], w[2], w[3]);
             if (hsub == 0)
-              v_fp_w[fp_slice + (((int64_t)unit * NNT + nt) * 64 + lane) * 8 + (kx & 7)] = (uint16_t)e;
+              __builtin_amdgcn_raw_buffer_store_b16((uint16_t)e, rs_vf, lane16 + nt * 1024, 2 * (kx & 7), 0);
           }
         }
         if (hsub == 0 && bh % P.Hkv == 0 && lane == 0)
@@ -541,8 +558,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       const int src0 = (lane & 0x33), src1 = (lane & 0x33) | 4;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        pv[j] = __shfl(p[j], src0);
-        pv[4 + j] = __shfl(p[j], src1);
+        pv[j] = from_lane(p[j], src0);
+        pv[4 + j] = from_lane(p[j], src1);
       }
       // rows 0..3: p rounded to T; rows 4..7: the rounding residual, again in T (masks: as a choice between the two
       // the compiler made eight branches of it; 512 tokens, 8 kv heads 10.2 instead of 9.9 us)
@@ -584,8 +601,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     // value scales of 2^-8.5, were off by 1.3e-2 of the output; now within the output's own rounding.)
     const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
     const float m_g = st.m;
-    st.m = __shfl(m_g, q4) - (float)FP_LEAD;
-    const float l_q = __shfl(l_tot, q4) * __builtin_ldexpf(1.f, FP_LEAD + pos_exp<BITS>(0));
+    st.m = from_lane(m_g, q4) - (float)FP_LEAD;
+    const float l_q = from_lane(l_tot, q4) * __builtin_ldexpf(1.f, FP_LEAD + pos_exp<BITS>(0));
     st.l[0] = n16 == 0 ? l_q : 0.f;
     st.l[1] = st.l[2] = st.l[3] = 0.f;
 #pragma unroll
@@ -668,10 +685,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     const auto rs_kz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kzb), 0, kmeta_bytes, 0x00020000);
     const auto rs_vs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vsb), 0, vmeta_bytes, 0x00020000);
     const auto rs_vz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vzb), 0, vmeta_bytes, 0x00020000);
-    auto load16 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
-      const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
-      return make_uint4(v[0], v[1], v[2], v[3]);
-    };
+    auto load16 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) { return buffer_load16(rs, (int)voff, (int)soff); };
     auto load_words = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
       Words<WPL> r;
 #pragma unroll
@@ -1207,7 +1221,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   for (int e = 0; e < 4; ++e) {
     float t = acc[e];
 #pragma unroll
-    for (int k = 1; k < RPI; ++k) t += __shfl(acc[e], (lane + k * C4) & 63);
+    for (int k = 1; k < RPI; ++k) t += from_lane(acc[e], (lane + k * C4) & 63);
     acc[e] = t;
   }
   if (alone) {
