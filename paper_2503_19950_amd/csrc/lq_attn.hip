@@ -60,7 +60,8 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   const int TQ = tiles_of(s, n_q), TF = (n_fp + 31) / 32;
   const double r = fp_unit_weight(s);
   const double units = TQ + r * TF;
-  const int hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
+  const int64_t bytes_read = cache_bytes_read(s, n_fp, n_q);
+  const int hb = heads_per_group(s, bytes_read);
   const int groups = s.B * s.Hkv * (s.gh / hb);
   const int cus = compute_units();
   static const int force_wpb = env_int("LOGQUANT_ATTN_WPB", 0);
@@ -117,7 +118,8 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   // codes it was measured to make no difference: 37.3 against 37.2 us).
   // (and only when the launch fits the chip in one round: with more workgroups than
   // compute units, as in a batch of 64 rows with per-row counts, 8 is faster: 49 against 54 us)
-  if (s.bits == 2 && (force_wpb == 12 || (!force_wpb && best_wpb == 8 && !keep_8 && units / (best_splits * 8.0) >= 6.0 &&
+  // (and not for more than four query heads, whose registers would not fit)
+  if (s.bits == 2 && hb <= 4 && (force_wpb == 12 || (!force_wpb && best_wpb == 8 && !keep_8 && units / (best_splits * 8.0) >= 6.0 &&
                                           (int64_t)best_splits * groups <= cus)))
     best_wpb = 12;
   const int splits = best_splits, WPB = best_wpb;
@@ -127,7 +129,7 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   plan->waves_per_block = WPB;
   plan->blocks = splits * groups;
   plan->fp_waves = nwf;
-  plan->bytes_read = cache_bytes_read(s, n_fp, n_q);
+  plan->bytes_read = bytes_read;
 }
 
 hipError_t launch_decode_attn(const Shape& s, const lq_cache& c, const void* q, float scale,

@@ -385,7 +385,12 @@ template <int KIND> struct SeqArgs { SeqState e[SEQ_CHUNK]; };
 template <> struct SeqArgs<EQUAL> {};
 
 // PROG: how fp rows and tiles are dealt to the wavefronts, see lq_schedule.h.
-template <bool BF16, int D, int G, int NWB, int BITS, int KIND, int PROG>
+// NH: sets of four query heads that a workgroup works on side by side, P.hb heads in all.  Two sets share the loads of a
+// tile and the codes once they are unpacked; each has its own q*s, probabilities and sums (250 registers for d = 128, none
+// spilled but 4 to 5 with padding, 4 bits and G = 32).  Eight heads per kv head in two workgroups of four were bound by
+// unpacking and by reading every byte twice: 8 kv heads x 9 rows x 49079 tokens, d = 96, 104 -> 83 us a launch, 64 x 8192,
+// d = 128, 24.8 -> 20.5 (heads_per_group says when).
+template <bool BF16, int D, int G, int NWB, int BITS, int KIND, int PROG, int NH>
 __global__ void __launch_bounds__(64 * NWB, NWB == 12 ? 3 : 2)
 attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN;
@@ -397,12 +402,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   // pitch that is an odd number of 16-byte units puts those on different banks.
   constexpr int QS_ROW = D + 8;
   static_assert((QS_ROW * 2 / 16) % 2 == 1, "q*s row pitch");
-  constexpr int QS_ROWS = 13;
-  __shared__ __attribute__((aligned(16))) uint16_t qs_lds[NWB][NGRP][QS_ROWS][QS_ROW];   // rows 4*piece+head (three pieces), row 12 = zeros
-  __shared__ __attribute__((aligned(16))) uint16_t p_lds[NWB][2][9][32];            // [wave][32-token step][row][token]: rows 0-3 p of head, 4 zeros, 5-8 p's fp16 rounding residual
-  __shared__ __attribute__((aligned(16))) float o_lds[NWB][4][D];                   // (the split merge stores 16 bytes at a time)
-  __shared__ float ml_lds[NWB][4][2];
-  __shared__ float zs_lds[NWB][4][4];
+  constexpr int QS_ROWS = 12 * NH + 1;
+  __shared__ __attribute__((aligned(16))) uint16_t qs_lds[NWB][NGRP][QS_ROWS][QS_ROW];   // rows 12*set+4*piece+head (three pieces), the last row = zeros
+  __shared__ __attribute__((aligned(16))) uint16_t p_lds[NWB][NH][2][9][32];        // [wave][set][32-token step][row][token]: rows 0-3 p of head, 4 zeros, 5-8 p's fp16 rounding residual
+  __shared__ __attribute__((aligned(16))) float o_lds[NWB][4 * NH][D];                   // (the split merge stores 16 bytes at a time)
+  __shared__ float ml_lds[NWB][4 * NH][2];
+  __shared__ float zs_lds[NWB][4][4 * NH];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -422,8 +427,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     }
   }
   const int q4 = lane >> 4, n16 = lane & 15, up = n16 >> 2, g = lane & 3;
-  const bool head_ok = g < P.hb;
-  const int64_t qrow = ((int64_t)bh * P.gh + hsub * P.hb + (head_ok ? g : 0)) * D;
+  const int64_t head0 = (int64_t)bh * P.gh + hsub * P.hb;   // this workgroup's first query head
 
   // counts and live fp buffer: the same for every sequence, or (per-sequence lengths)
   // read from the sequence's entry of the state array
@@ -454,24 +458,32 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   const int own_half = young ? (deal.first + TQ) / 2 : 0;
   if (young) __builtin_amdgcn_s_setprio(1);
   const int64_t part_base = (((int64_t)bh * P.splits + split) * P.gh + hsub * P.hb) * (D + 4);
-  State<NNT> st;
+  State<NNT> st[NH];
 #pragma unroll
-  for (int nt = 0; nt < NNT; ++nt) st.acc[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  st.m = -INFINITY;
+  for (int hs = 0; hs < NH; ++hs) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) st.l[j] = 0.f;
+    for (int nt = 0; nt < NNT; ++nt) st[hs].acc[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    st[hs].m = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) st.zacc[i] = 0.f;
+    for (int j = 0; j < 4; ++j) st[hs].l[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) st[hs].zacc[i] = 0.f;
+  }
 
   // ------------------------- original-precision rows -------------------------
   auto fp_rows = [&](const int unit0, const int unit_step) __attribute__((always_inline)) {
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
     const int lane16 = lane * 16;
-    uint4 qreg[NKC];
+    uint4 qreg[NH][NKC];
 #pragma unroll
-    for (int kc = 0; kc < NKC; ++kc) {
-      qreg[kc] = *reinterpret_cast<const uint4*>((const char*)P.q + (uint32_t)((qrow + 32 * kc + 8 * q4) * 2));
-      if (!head_ok) qreg[kc] = make_uint4(0, 0, 0, 0);
+    for (int hs = 0; hs < NH; ++hs) {
+      const bool head_ok = 4 * hs + g < P.hb;
+      const int64_t qrow = (head0 + (head_ok ? 4 * hs + g : 0)) * D;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        qreg[hs][kc] = *reinterpret_cast<const uint4*>((const char*)P.q + (uint32_t)((qrow + 32 * kc + 8 * q4) * 2));
+        if (!head_ok) qreg[hs][kc] = make_uint4(0, 0, 0, 0);
+      }
     }
     // Fused append: the wavefront that owns the unit receiving the new row fetches the row
     // first.  (The compiler waits for it before it issues the unit's own loads: one more
@@ -539,54 +551,57 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
           pos_fp[(bh / P.Hkv) * P.cap + n_fp - 1] = n_fp - 1 + n_tok_q;
       }
 
-      floatx4 Du[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int kc = 0; kc < NKC; ++kc) {
-        Du[0] = mfma_T<BF16>(ka[0][kc], qreg[kc], Du[0]);
-        Du[1] = mfma_T<BF16>(ka[1][kc], qreg[kc], Du[1]);
-      }
-      float s[4], p[4];
-      {
-        const floatx4 d = up == 0 ? Du[0] : Du[1];
-        const int tok0 = 32 * unit + 16 * up + 4 * q4;
+      for (int hs = 0; hs < NH; ++hs) {
+        floatx4 Du[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s[j] = (up < 2 && tok0 + j < n_fp) ? d[j] * P.c : -INFINITY;
-      }
-      online_softmax<NNT, false>(st, s, p);
+        for (int kc = 0; kc < NKC; ++kc) {
+          Du[0] = mfma_T<BF16>(ka[0][kc], qreg[hs][kc], Du[0]);
+          Du[1] = mfma_T<BF16>(ka[1][kc], qreg[hs][kc], Du[1]);
+        }
+        float s[4], p[4];
+        {
+          const floatx4 d = up == 0 ? Du[0] : Du[1];
+          const int tok0 = 32 * unit + 16 * up + 4 * q4;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) s[j] = (up < 2 && tok0 + j < n_fp) ? d[j] * P.c : -INFINITY;
+        }
+        online_softmax<NNT, false>(st[hs], s, p);
 
-      float pv[8];
-      const int src0 = (lane & 0x33), src1 = (lane & 0x33) | 4;
+        float pv[8];
+        const int src0 = (lane & 0x33), src1 = (lane & 0x33) | 4;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        pv[j] = from_lane(p[j], src0);
-        pv[4 + j] = from_lane(p[j], src1);
-      }
-      // rows 0..3: p rounded to T; rows 4..7: the rounding residual, again in T (masks: as a choice between the two
-      // the compiler made eight branches of it; 512 tokens, 8 kv heads 10.2 instead of 9.9 us)
-      const uint32_t hi_row = up == 0 ? 0xFFFFFFFFu : 0u, lo_row = up == 1 ? 0xFFFFFFFFu : 0u;
-      uint32_t aw[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t hi = pack_T<BF16>(pv[2 * r], pv[2 * r + 1]);
-        const uint32_t lo = pack_T<BF16>(pv[2 * r] - lo_T<BF16>(hi), pv[2 * r + 1] - hi_T<BF16>(hi));
-        aw[r] = (hi & hi_row) | (lo & lo_row);
-      }
-      const uint4 a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
-      if (32 * unit + 32 > n_fp) {   // slots beyond n_fp hold unspecified bits
-        uint32_t keep[4];
+        for (int j = 0; j < 4; ++j) {
+          pv[j] = from_lane(p[j], src0);
+          pv[4 + j] = from_lane(p[j], src1);
+        }
+        // rows 0..3: p rounded to T; rows 4..7: the rounding residual, again in T (masks: as a choice between the two
+        // the compiler made eight branches of it; 512 tokens, 8 kv heads 10.2 instead of 9.9 us)
+        const uint32_t hi_row = up == 0 ? 0xFFFFFFFFu : 0u, lo_row = up == 1 ? 0xFFFFFFFFu : 0u;
+        uint32_t aw[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i0 = 2 * r, i1 = 2 * r + 1;
-          const int x0 = 16 * ((i0 >> 2) & 1) + 4 * q4 + (i0 & 3), x1 = 16 * ((i1 >> 2) & 1) + 4 * q4 + (i1 & 3);
-          keep[r] = (32 * unit + x0 < n_fp ? 0x0000FFFFu : 0u) | (32 * unit + x1 < n_fp ? 0xFFFF0000u : 0u);
+          const uint32_t hi = pack_T<BF16>(pv[2 * r], pv[2 * r + 1]);
+          const uint32_t lo = pack_T<BF16>(pv[2 * r] - lo_T<BF16>(hi), pv[2 * r + 1] - hi_T<BF16>(hi));
+          aw[r] = (hi & hi_row) | (lo & lo_row);
+        }
+        const uint4 a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
+        if (hs == 0 && 32 * unit + 32 > n_fp) {   // slots beyond n_fp hold unspecified bits
+          uint32_t keep[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i0 = 2 * r, i1 = 2 * r + 1;
+            const int x0 = 16 * ((i0 >> 2) & 1) + 4 * q4 + (i0 & 3), x1 = 16 * ((i1 >> 2) & 1) + 4 * q4 + (i1 & 3);
+            keep[r] = (32 * unit + x0 < n_fp ? 0x0000FFFFu : 0u) | (32 * unit + x1 < n_fp ? 0xFFFF0000u : 0u);
+          }
+#pragma unroll
+          for (int nt = 0; nt < NNT; ++nt) {
+            va[nt].x &= keep[0]; va[nt].y &= keep[1]; va[nt].z &= keep[2]; va[nt].w &= keep[3];
+          }
         }
 #pragma unroll
-        for (int nt = 0; nt < NNT; ++nt) {
-          va[nt].x &= keep[0]; va[nt].y &= keep[1]; va[nt].z &= keep[2]; va[nt].w &= keep[3];
-        }
+        for (int nt = 0; nt < NNT; ++nt) st[hs].acc[nt] = mfma_T<BF16>(a, va[nt], st[hs].acc[nt]);
       }
-#pragma unroll
-      for (int nt = 0; nt < NNT; ++nt) st.acc[nt] = mfma_T<BF16>(a, va[nt], st.acc[nt]);
     }
   };
   auto hand_over = [&]() __attribute__((always_inline)) {
@@ -599,22 +614,25 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     // further below weigh under 2^-30 a token, 2^17 tokens under 2^-13 of the output, and down to 2^-40 their operands
     // are still normal numbers.  (With the fp rows' maximum as the reference, 16384 tokens 2^14 below 10 heavy rows,
     // value scales of 2^-8.5, were off by 1.3e-2 of the output; now within the output's own rounding.)
-    const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
-    const float m_g = st.m;
-    st.m = from_lane(m_g, q4) - (float)FP_LEAD;
-    const float l_q = from_lane(l_tot, q4) * __builtin_ldexpf(1.f, FP_LEAD + pos_exp<BITS>(0));
-    st.l[0] = n16 == 0 ? l_q : 0.f;
-    st.l[1] = st.l[2] = st.l[3] = 0.f;
 #pragma unroll
-    for (int nt = 0; nt < NNT; ++nt) {
-      const int gc = (16 * nt) / G;
+    for (int hs = 0; hs < NH; ++hs) {
+      const float l_tot = head_sum((st[hs].l[0] + st[hs].l[1]) + (st[hs].l[2] + st[hs].l[3]));
+      const float m_g = st[hs].m;
+      st[hs].m = from_lane(m_g, q4) - (float)FP_LEAD;
+      const float l_q = from_lane(l_tot, q4) * __builtin_ldexpf(1.f, FP_LEAD + pos_exp<BITS>(0));
+      st[hs].l[0] = n16 == 0 ? l_q : 0.f;
+      st[hs].l[1] = st[hs].l[2] = st[hs].l[3] = 0.f;
 #pragma unroll
-      for (int gg = 0; gg < 4; ++gg) {
-        float x, y;
-        xor16_pair(st.acc[nt][gg], &x, &y);
-        float tot = x + y;
-        if (gc >= 2) { xor32_pair(tot, &x, &y); tot = x + y; }
-        st.acc[nt][gg] = q4 == gc ? tot * (__builtin_ldexpf(1.f, FP_LEAD) / CODE_SCALE<BITS>) : 0.f;
+      for (int nt = 0; nt < NNT; ++nt) {
+        const int gc = (16 * nt) / G;
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {
+          float x, y;
+          xor16_pair(st[hs].acc[nt][gg], &x, &y);
+          float tot = x + y;
+          if (gc >= 2) { xor32_pair(tot, &x, &y); tot = x + y; }
+          st[hs].acc[nt][gg] = q4 == gc ? tot * (__builtin_ldexpf(1.f, FP_LEAD) / CODE_SCALE<BITS>) : 0.f;
+        }
       }
     }
   };
@@ -661,7 +679,6 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     const int c8 = n16;
     const bool prep = 8 * c8 < D;
     const uint32_t km_off = (prep ? 8 * c8 : 0) * 2;
-    const bool headq_ok = q4 < P.hb;
 
     struct Tile {
       Words<WPL> kc[2], vc[2];
@@ -780,9 +797,13 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       ta = drawn_tile(ka);
       tb = drawn_tile(kb);
     }
-    const int64_t qrow_q = ((int64_t)bh * P.gh + hsub * P.hb + (headq_ok ? q4 : 0)) * D;
-    uint4 raw;
-    if constexpr (Q_FIRST) raw = *reinterpret_cast<const uint4*>(P.q + qrow_q + (prep ? 8 * c8 : 0));
+    uint4 raw[NH];
+    auto load_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int hs = 0; hs < NH; ++hs)
+        raw[hs] = *reinterpret_cast<const uint4*>(P.q + (head0 + (4 * hs + q4 < P.hb ? 4 * hs + q4 : 0)) * D + (prep ? 8 * c8 : 0));
+    };
+    if constexpr (Q_FIRST) load_q();
     Tile A;
     Place pa = place(ta);
     if (ta < TQ) {
@@ -793,18 +814,17 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     }
     // q of (head q4, channels 8*c8..+7): fp16 pairs for the bias dot products, and
     // fp16 pairs pre-multiplied by 2^(3-2v) (v = pair index) for the q*s operands
-    uint32_t qraw[4];
-    half2_t qz[4], qh[4];
-    {
-      if constexpr (!Q_FIRST) raw = *reinterpret_cast<const uint4*>(P.q + qrow_q + (prep ? 8 * c8 : 0));
-      const uint32_t keep = prep && headq_ok ? 0xFFFFFFFFu : 0u;   // (a branch here waits for the tile)
-      raw.x &= keep; raw.y &= keep; raw.z &= keep; raw.w &= keep;
-      qraw[0] = raw.x; qraw[1] = raw.y; qraw[2] = raw.z; qraw[3] = raw.w;
+    half2_t qz[NH][4], qh[NH][4];
+    if constexpr (!Q_FIRST) load_q();
+#pragma unroll
+    for (int hs = 0; hs < NH; ++hs) {
+      const uint32_t keep = prep && 4 * hs + q4 < P.hb ? 0xFFFFFFFFu : 0u;   // (a branch here waits for the tile)
+      const uint32_t qraw[4] = {raw[hs].x & keep, raw[hs].y & keep, raw[hs].z & keep, raw[hs].w & keep};
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float f = __builtin_ldexpf(1.f, pos_exp<BITS>(v));
-        qh[v] = half2_t{(_Float16)(lo_T<BF16>(qraw[v]) * f), (_Float16)(hi_T<BF16>(qraw[v]) * f)};
-        qz[v] = pair_to_f16<BF16>(qraw[v]);
+        qh[hs][v] = half2_t{(_Float16)(lo_T<BF16>(qraw[v]) * f), (_Float16)(hi_T<BF16>(qraw[v]) * f)};
+        qz[hs][v] = pair_to_f16<BF16>(qraw[v]);
       }
     }
     const float c_codes = P.c * CODE_SCALE<BITS>;   // codes and the pre-scaled q*s together carry 1 / CODE_SCALE
@@ -819,31 +839,34 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     }
 
     // rows of the q*s operand: matrix row n16 = 4*head + piece, piece 3 is zero
-    const uint16_t* qs_rd = &qs_lds[wave][0][(n16 & 3) < 3 ? 4 * (n16 & 3) + (n16 >> 2) : 12][8 * q4];
+    const uint16_t* qs_rd[NH];
+#pragma unroll
+    for (int hs = 0; hs < NH; ++hs) qs_rd[hs] = &qs_lds[wave][0][(n16 & 3) < 3 ? 12 * hs + 4 * (n16 & 3) + (n16 >> 2) : QS_ROWS - 1][8 * q4];
     uint16_t* qs_wr = &qs_lds[wave][0][q4][8 * c8];
     // probabilities: written per (head q4, token), read per (head g, token octet q4);
     // lanes of absent channel groups read the zero row
-    const uint16_t* p_rd = &p_lds[wave][0][!row_live ? 4 : tail_row ? 5 + g : g][4 * q4];
-    const uint16_t* p_hd = &p_lds[wave][0][!row_live ? 4 : g][4 * q4];
-    uint16_t* p_wr = &p_lds[wave][0][q4][n16];
+    const uint16_t* p_rd = &p_lds[wave][0][0][!row_live ? 4 : tail_row ? 5 + g : g][4 * q4];
+    const uint16_t* p_hd = &p_lds[wave][0][0][!row_live ? 4 : g][4 * q4];
+    uint16_t* p_wr = &p_lds[wave][0][0][q4][n16];
     {
 #pragma unroll
       for (int e = 0; e < NGRP; ++e)
-        if (lane < QS_ROW / 8) *reinterpret_cast<uint4*>(&qs_lds[wave][e][12][8 * lane]) = make_uint4(0, 0, 0, 0);
-      if (lane < 32) { p_lds[wave][0][4][lane] = 0; p_lds[wave][1][4][lane] = 0; }
+        if (lane < QS_ROW / 8) *reinterpret_cast<uint4*>(&qs_lds[wave][e][QS_ROWS - 1][8 * lane]) = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int hs = 0; hs < NH; ++hs)
+        if (lane < 32) { p_lds[wave][hs][0][4][lane] = 0; p_lds[wave][hs][1][4][lane] = 0; }
     }
 
     auto process = [&](Tile& cur, const Place& pl, const Place& tn) {   // tn: the tile to refill the registers with
       const int t = pl.t;
       // ---- q*s (fp16 head and tail) and bias = sum_c q_c z_c for each key group
-      float bo[4];
+      float bo[NH][4];
       {
-        float bias[NGRP];
+        float bias[NH][NGRP];
 #pragma unroll
         for (int e = 0; e < NGRP; ++e) {
           const uint32_t sw[4] = {cur.ks8[e].x, cur.ks8[e].y, cur.ks8[e].z, cur.ks8[e].w};
           const uint32_t zw[4] = {cur.kz8[e].x, cur.kz8[e].y, cur.kz8[e].z, cur.kz8[e].w};
-          float bp = 0.f;
           // q*s in three pieces whose sum is the exact product: the top six significant
           // bits of the rounded product, its other five bits, and what the rounding dropped.
           // The code operands are fp16 subnormals; the matrix unit aligns the addends of a
@@ -853,103 +876,110 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
           // channel of the block has a q*s a few times larger.  A six-bit piece has 5 bits
           // of room more, and the two small pieces lose nothing that matters (they may be
           // subnormal themselves: single products of two subnormals were measured exact).
-          uint32_t h[4], r[4], l[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
+          for (int hs = 0; hs < NH; ++hs) {
+            float bp = 0.f;
+            uint32_t h[4], r[4], l[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
 #pragma clang fp contract(off)   // hi - top must subtract from the ROUNDED product: fused into fma(q, s, -top) it would hold lo as well
-            bp = dot2_h(qz[v], meta_pair(zw[v]), bp);
-            const half2_t sh = meta_pair(sw[v]);
-            const half2_t hi = qh[v] * sh;
-            const half2_t lo = __builtin_elementwise_fma(qh[v], sh, -hi);
-            h[v] = __builtin_bit_cast(uint32_t, hi) & 0xFFE0FFE0u;
-            r[v] = __builtin_bit_cast(uint32_t, hi - __builtin_bit_cast(half2_t, h[v]));
-            l[v] = __builtin_bit_cast(uint32_t, lo);
+              bp = dot2_h(qz[hs][v], meta_pair(zw[v]), bp);
+              const half2_t sh = meta_pair(sw[v]);
+              const half2_t hi = qh[hs][v] * sh;
+              const half2_t lo = __builtin_elementwise_fma(qh[hs][v], sh, -hi);
+              h[v] = __builtin_bit_cast(uint32_t, hi) & 0xFFE0FFE0u;
+              r[v] = __builtin_bit_cast(uint32_t, hi - __builtin_bit_cast(half2_t, h[v]));
+              l[v] = __builtin_bit_cast(uint32_t, lo);
+            }
+            if (prep) {
+              uint16_t* wr = qs_wr + (e * QS_ROWS + 12 * hs) * QS_ROW;
+              *reinterpret_cast<uint4*>(wr) = make_uint4(h[0], h[1], h[2], h[3]);
+              *reinterpret_cast<uint4*>(wr + 4 * QS_ROW) = make_uint4(r[0], r[1], r[2], r[3]);
+              *reinterpret_cast<uint4*>(wr + 8 * QS_ROW) = make_uint4(l[0], l[1], l[2], l[3]);
+            }
+            bias[hs][e] = row_sum(bp) * P.c;
           }
-          if (prep) {
-            *reinterpret_cast<uint4*>(qs_wr + e * (QS_ROWS * QS_ROW)) = make_uint4(h[0], h[1], h[2], h[3]);
-            *reinterpret_cast<uint4*>(qs_wr + e * (QS_ROWS * QS_ROW) + 4 * QS_ROW) = make_uint4(r[0], r[1], r[2], r[3]);
-            *reinterpret_cast<uint4*>(qs_wr + e * (QS_ROWS * QS_ROW) + 8 * QS_ROW) = make_uint4(l[0], l[1], l[2], l[3]);
-          }
-          bias[e] = row_sum(bp) * P.c;
         }
         load_kmeta(cur, tn.t);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) bo[u] = bias[(u * NGRP) >> 2] + offs[u];
+        for (int hs = 0; hs < NH; ++hs)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) bo[hs][u] = bias[hs][(u * NGRP) >> 2] + offs[u];
       }
       wave_lds_sync();
 
       // ---- logits: rows (head, piece) x four 16-token tiles, NKC channel chunks each
-      floatx4 Du[4];
+      floatx4 Du[NH][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) Du[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int hs = 0; hs < NH; ++hs)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) Du[hs][u] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < NGRP; ++e) {
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc) {
-          const uint4 qa = *reinterpret_cast<const uint4*>(qs_rd + e * (QS_ROWS * QS_ROW) + 32 * kc);
+          uint4 qa[NH];
+#pragma unroll
+          for (int hs = 0; hs < NH; ++hs) qa[hs] = *reinterpret_cast<const uint4*>(qs_rd[hs] + e * (QS_ROWS * QS_ROW) + 32 * kc);
 #pragma unroll
           for (int u = e * (4 / NGRP); u < (e + 1) * (4 / NGRP); ++u) {
             const int o = (u & 1) * NKC + kc;
             const uint4 b = operand_codes<BITS>(cur.kc[u >> 1].w, o);
-            Du[u] = mfma_f16(qa, b, Du[u]);
+#pragma unroll
+            for (int hs = 0; hs < NH; ++hs) Du[hs][u] = mfma_f16(qa[hs], b, Du[hs][u]);
           }
         }
       }
 
       load_kcodes(cur, tn);
 
-      // this lane: head q4, token 16*u + n16 of the tile; the three pieces are rows j = 0, 1, 2
-      float s[4], p[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s[u] = fmaf(Du[u][0] + (Du[u][1] + Du[u][2]), c_codes, bo[u]);
+      // this lane: head q4 of each set, token 16*u + n16 of the tile; the three pieces are rows j = 0, 1, 2
       const bool partial = 64 * t + 64 > n_q;
-      if (partial) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (64 * t + 16 * u + n16 >= n_q) s[u] = -INFINITY;
-      }
-      if constexpr (KIND == PADDED) {
-        // padding slots behind a short key group (zero codes, zero value scales and
-        // zero-points): a finite sentinel, so that a tile made of padding only leaves
-        // a state whose weight in every later merge is exactly 0
-        const int r0 = G >= 64 ? pl.slot0 : (64 * t) % P.Wq;
+      for (int hs = 0; hs < NH; ++hs) {
+        float s[4], p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] = fmaf(Du[hs][u][0] + (Du[hs][u][1] + Du[hs][u][2]), c_codes, bo[hs][u]);
+        if (partial) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (64 * t + 16 * u + n16 >= n_q) s[u] = -INFINITY;
+        }
+        if constexpr (KIND == PADDED) {
+          // padding slots behind a short key group (zero codes, zero value scales and
+          // zero-points): a finite sentinel, so that a tile made of padding only leaves
+          // a state whose weight in every later merge is exactly 0
+          const int r0 = G >= 64 ? pl.slot0 : (64 * t) % P.Wq;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            int r = r0 + 16 * u + n16;
+            r = r >= P.Wq ? r - P.Wq : r;
+            if (r >= P.W) s[u] = DEAD_LOGIT;
+          }
+        }
+        online_softmax_rows<NNT, VPIECES == 1>(st[hs], s, p, g, SLACK);
+
+        // ---- hand the probabilities (fp16) to the lanes that feed the output step
+        uint16_t* wr = p_wr + hs * (2 * 9 * 32);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          int r = r0 + 16 * u + n16;
-          r = r >= P.Wq ? r - P.Wq : r;
-          if (r >= P.W) s[u] = DEAD_LOGIT;
+          _Float16 ph16 = (_Float16)p[u];
+          // Two pieces and no carried product residual (bf16 caches): the head piece keeps only the three
+          // leading significant bits of p, so that its product with a value scale - a bf16 number, 8
+          // significant bits - is exact in fp16; the rounding of the product then hits the second piece
+          // only, which is at most a quarter of p.
+          if constexpr (VPIECES == 2 && !PROD_LO)
+            ph16 = __builtin_bit_cast(_Float16, (uint16_t)(__builtin_bit_cast(uint16_t, ph16) & 0xFF00u));
+          wr[(u >> 1) * (9 * 32) + 16 * (u & 1)] = __builtin_bit_cast(uint16_t, ph16);
+          if constexpr (VPIECES == 2)   // what the head piece leaves out, for the residual rows
+            wr[(u >> 1) * (9 * 32) + 16 * (u & 1) + 5 * 32] = __builtin_bit_cast(uint16_t, (_Float16)(p[u] - (float)ph16));
         }
-      }
-      online_softmax_rows<NNT, VPIECES == 1>(st, s, p, g, SLACK);
-
-      // ---- hand the probabilities (fp16) to the lanes that feed the output step
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        _Float16 ph16 = (_Float16)p[u];
-        // Two pieces and no carried product residual (bf16 caches): the head piece keeps only the three
-        // leading significant bits of p, so that its product with a value scale - a bf16 number, 8
-        // significant bits - is exact in fp16; the rounding of the product then hits the second piece
-        // only, which is at most a quarter of p.
-        if constexpr (VPIECES == 2 && !PROD_LO)
-          ph16 = __builtin_bit_cast(_Float16, (uint16_t)(__builtin_bit_cast(uint16_t, ph16) & 0xFF00u));
-        p_wr[(u >> 1) * (9 * 32) + 16 * (u & 1)] = __builtin_bit_cast(uint16_t, ph16);
-        if constexpr (VPIECES == 2)   // what the head piece leaves out, for the residual rows
-          p_wr[(u >> 1) * (9 * 32) + 16 * (u & 1) + 5 * 32] = __builtin_bit_cast(uint16_t, (_Float16)(p[u] - (float)ph16));
       }
       wave_lds_sync();
 
       // ---- output: two 32-token steps x NNT channel tiles
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const uint2 pa = *reinterpret_cast<const uint2*>(p_rd + ks * (9 * 32));        // tokens 4*q4 .. +3
-        const uint2 pb = *reinterpret_cast<const uint2*>(p_rd + ks * (9 * 32) + 16);   // tokens 16 + 4*q4 .. +3
-        const uint32_t ph[4] = {pa.x, pa.y, pb.x, pb.y};      // slots (0,1) (2,3) (4,5) (6,7)
-        uint32_t hd[4] = {pa.x, pa.y, pb.x, pb.y};            // the head piece of the same slots
-        if constexpr (PROD_LO && VPIECES == 2) {
-          const uint2 ha = *reinterpret_cast<const uint2*>(p_hd + ks * (9 * 32));
-          const uint2 hb = *reinterpret_cast<const uint2*>(p_hd + ks * (9 * 32) + 16);
-          hd[0] = ha.x; hd[1] = ha.y; hd[2] = hb.x; hd[3] = hb.y;
-        }
         uint4 vsr = cur.vs[ks], vzr = cur.vz[ks];
         if (partial) {   // slots beyond n_q hold unspecified bits: keep them out of the sums
           uint32_t keep[4];
@@ -964,33 +994,51 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
           vzr.x &= keep[0]; vzr.y &= keep[1]; vzr.z &= keep[2]; vzr.w &= keep[3];
         }
         const uint32_t vsw[4] = {vsr.x, vsr.y, vsr.z, vsr.w}, vzw[4] = {vzr.x, vzr.y, vzr.z, vzr.w};
-        uint32_t aw[4], al[4];
+        uint4 a[NH], al[NH];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const half2_t pp = __builtin_bit_cast(half2_t, ph[v]);
-          const half2_t sv = meta_pair(vsw[v]);
-          if constexpr (!PROD_LO) {
-            aw[v] = __builtin_bit_cast(uint32_t, pp * sv);
-          } else if constexpr (VPIECES == 2) {
-            // head rows: p_hi * vs rounded; residual rows: what that rounding dropped plus p_lo * vs
-            const half2_t hh = __builtin_bit_cast(half2_t, hd[v]);
-            const half2_t hi = hh * sv;
-            const half2_t lo = __builtin_elementwise_fma(pp, sv, __builtin_elementwise_fma(hh, sv, -hi));
-            aw[v] = __builtin_bit_cast(uint32_t, tail_row ? lo : hi);
-          } else {
-            const half2_t hi = pp * sv;
-            aw[v] = __builtin_bit_cast(uint32_t, hi);
-            al[v] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(pp, sv, -hi));
+        for (int hs = 0; hs < NH; ++hs) {
+          const int at = hs * (2 * 9 * 32) + ks * (9 * 32);
+          const uint2 pa = *reinterpret_cast<const uint2*>(p_rd + at);        // tokens 4*q4 .. +3
+          const uint2 pb = *reinterpret_cast<const uint2*>(p_rd + at + 16);   // tokens 16 + 4*q4 .. +3
+          const uint32_t ph[4] = {pa.x, pa.y, pb.x, pb.y};      // slots (0,1) (2,3) (4,5) (6,7)
+          uint32_t hd[4] = {pa.x, pa.y, pb.x, pb.y};            // the head piece of the same slots
+          if constexpr (PROD_LO && VPIECES == 2) {
+            const uint2 ha = *reinterpret_cast<const uint2*>(p_hd + at);
+            const uint2 hb = *reinterpret_cast<const uint2*>(p_hd + at + 16);
+            hd[0] = ha.x; hd[1] = ha.y; hd[2] = hb.x; hd[3] = hb.y;
           }
-          st.zacc[v] = __builtin_amdgcn_fdot2(pp, meta_pair(vzw[v]), st.zacc[v], false);
+          uint32_t aw[4], lw[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const half2_t pp = __builtin_bit_cast(half2_t, ph[v]);
+            const half2_t sv = meta_pair(vsw[v]);
+            if constexpr (!PROD_LO) {
+              aw[v] = __builtin_bit_cast(uint32_t, pp * sv);
+            } else if constexpr (VPIECES == 2) {
+              // head rows: p_hi * vs rounded; residual rows: what that rounding dropped plus p_lo * vs
+              const half2_t hh = __builtin_bit_cast(half2_t, hd[v]);
+              const half2_t hi = hh * sv;
+              const half2_t lo = __builtin_elementwise_fma(pp, sv, __builtin_elementwise_fma(hh, sv, -hi));
+              aw[v] = __builtin_bit_cast(uint32_t, tail_row ? lo : hi);
+            } else {
+              const half2_t hi = pp * sv;
+              aw[v] = __builtin_bit_cast(uint32_t, hi);
+              lw[v] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(pp, sv, -hi));
+            }
+            st[hs].zacc[v] = __builtin_amdgcn_fdot2(pp, meta_pair(vzw[v]), st[hs].zacc[v], false);
+          }
+          a[hs] = make_uint4(aw[0], aw[1], aw[2], aw[3]);
+          if constexpr (PROD_LO && VPIECES == 1) al[hs] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
         }
-        const uint4 a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
 #pragma unroll
         for (int nt = 0; nt < NNT; ++nt) {
           const uint4 b = operand_codes<BITS>(cur.vc[ks].w, nt);
-          st.acc[nt] = mfma_f16(a, b, st.acc[nt]);
-          if constexpr (PROD_LO && VPIECES == 1)   // no spare rows: the dropped part takes a product of its own
-            st.acc[nt] = mfma_f16(make_uint4(al[0], al[1], al[2], al[3]), b, st.acc[nt]);
+#pragma unroll
+          for (int hs = 0; hs < NH; ++hs) {
+            st[hs].acc[nt] = mfma_f16(a[hs], b, st[hs].acc[nt]);
+            if constexpr (PROD_LO && VPIECES == 1)   // no spare rows: the dropped part takes a product of its own
+              st[hs].acc[nt] = mfma_f16(al[hs], b, st[hs].acc[nt]);
+          }
         }
         load_v(cur, tn, ks);
       }
@@ -1010,76 +1058,82 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       }
     }
     // canonical partial of this wavefront: o[g][c], m[g], l[g]
-    float lsum = 0.f;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) lsum += st.l[u] * __builtin_amdgcn_exp2f(-offs[u]);
-    const float l_tot = row_sum(lsum);
-    float zs = 0.f;
-    {
+    for (int hs = 0; hs < NH; ++hs) {
+      float lsum = 0.f;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) zs += st.zacc[v] * __builtin_ldexpf(1.f, -pos_exp<BITS>(v));
+      for (int u = 0; u < 4; ++u) lsum += st[hs].l[u] * __builtin_amdgcn_exp2f(-offs[u]);
+      const float l_tot = row_sum(lsum);
+      float zs = 0.f;
+      {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) zs += st[hs].zacc[v] * __builtin_ldexpf(1.f, -pos_exp<BITS>(v));
+      }
+      zs = rows_sum(zs);
+      if (q4 == 0) zs_lds[wave][up][4 * hs + g] = zs;       // the residual rows hold the residual's share of sum_t p_t vz_t
+      if (n16 == 0) { ml_lds[wave][4 * hs + q4][0] = st[hs].m; ml_lds[wave][4 * hs + q4][1] = l_tot; }
     }
-    zs = rows_sum(zs);
-    if (q4 == 0) zs_lds[wave][up][g] = zs;       // the residual rows hold the residual's share of sum_t p_t vz_t
-    if (n16 == 0) { ml_lds[wave][q4][0] = st.m; ml_lds[wave][q4][1] = l_tot; }
     wave_lds_sync();
-    // the accumulators of lane group q4 are the rows of channel group q4 (and of its
-    // residual piece, q4 + NGC): sum_t p_t vz_t of that group, both pieces, per head
-    if constexpr (VPIECES == 2 && NGC == 2) {
-      // Two channel groups, two pieces: lane groups 0 and 2 hold the two pieces of
-      // channel group 0, lane groups 1 and 3 those of channel group 1.  One swap of
-      // the 32-lane halves of two registers sums the pieces of FOUR channel tiles at
-      // once - lane group 0 ends up with the total of tile a, 2 with that of tile b
-      // (both of channel group 0), 1 and 3 with tiles c and d of channel group 1 - and
-      // every lane group writes its own.
-      constexpr int T0 = G / 16;                 // channel tiles of group 0 (group 1: the rest, at most as many)
-      const int grp = q4 & 1;
-      float zsv[4];
 #pragma unroll
-      for (int gg = 0; gg < 4; ++gg) zsv[gg] = zs_lds[wave][grp][gg] + zs_lds[wave][grp + NGC][gg];
+    for (int hs = 0; hs < NH; ++hs) {
+      // the accumulators of lane group q4 are the rows of channel group q4 (and of its
+      // residual piece, q4 + NGC): sum_t p_t vz_t of that group, both pieces, per head
+      if constexpr (VPIECES == 2 && NGC == 2) {
+        // Two channel groups, two pieces: lane groups 0 and 2 hold the two pieces of
+        // channel group 0, lane groups 1 and 3 those of channel group 1.  One swap of
+        // the 32-lane halves of two registers sums the pieces of FOUR channel tiles at
+        // once - lane group 0 ends up with the total of tile a, 2 with that of tile b
+        // (both of channel group 0), 1 and 3 with tiles c and d of channel group 1 - and
+        // every lane group writes its own.
+        constexpr int T0 = G / 16;                 // channel tiles of group 0 (group 1: the rest, at most as many)
+        const int grp = q4 & 1;
+        float zsv[4];
 #pragma unroll
-      for (int k = 0; k < (T0 + 1) / 2; ++k) {
-        constexpr int NONE = -1;
-        const int ta = 2 * k, tb = 2 * k + 1 < T0 ? 2 * k + 1 : NONE;
-        const int tc = T0 + 2 * k < NNT ? T0 + 2 * k : NONE, td = T0 + 2 * k + 1 < NNT ? T0 + 2 * k + 1 : NONE;
-        const int mine = grp ? (q4 >> 1 ? td : tc) : (q4 >> 1 ? tb : ta);
+        for (int gg = 0; gg < 4; ++gg) zsv[gg] = zs_lds[wave][grp][4 * hs + gg] + zs_lds[wave][grp + NGC][4 * hs + gg];
 #pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-          const float xa = st.acc[ta][gg], xb = st.acc[tb == NONE ? ta : tb][gg];
-          const float xc = st.acc[tc == NONE ? ta : tc][gg], xd = st.acc[td == NONE ? ta : td][gg];
-          const unsigned X = __float_as_uint(grp ? xc : xa), Y = __float_as_uint(grp ? xd : xb);
-          const auto r = __builtin_amdgcn_permlane32_swap(X, Y, false, false);
-          const float tot = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-          if (mine != NONE) o_lds[wave][gg][16 * mine + n16] = tot * CODE_SCALE<BITS> + zsv[gg];
-        }
-      }
-    } else {
-      const int gq = q4 < NGC ? q4 : 0;
-      float zsv[4];
-#pragma unroll
-      for (int gg = 0; gg < 4; ++gg) {
-        zsv[gg] = zs_lds[wave][gq][gg];
-        if constexpr (VPIECES == 2) zsv[gg] += zs_lds[wave][gq + NGC][gg];
-      }
-#pragma unroll
-      for (int nt = 0; nt < NNT; ++nt) {
-        const int gc = (16 * nt) / G;
-        if constexpr (VPIECES == 2) {   // add the residual piece's row: lane group q4 + NGC
-          float a[4];
+        for (int k = 0; k < (T0 + 1) / 2; ++k) {
+          constexpr int NONE = -1;
+          const int ta = 2 * k, tb = 2 * k + 1 < T0 ? 2 * k + 1 : NONE;
+          const int tc = T0 + 2 * k < NNT ? T0 + 2 * k : NONE, td = T0 + 2 * k + 1 < NNT ? T0 + 2 * k + 1 : NONE;
+          const int mine = grp ? (q4 >> 1 ? td : tc) : (q4 >> 1 ? tb : ta);
 #pragma unroll
           for (int gg = 0; gg < 4; ++gg) {
-            float x, y;
-            xor16_pair(st.acc[nt][gg], &x, &y);   // (NGC == 1)
-            a[gg] = x + y;
+            const float xa = st[hs].acc[ta][gg], xb = st[hs].acc[tb == NONE ? ta : tb][gg];
+            const float xc = st[hs].acc[tc == NONE ? ta : tc][gg], xd = st[hs].acc[td == NONE ? ta : td][gg];
+            const unsigned X = __float_as_uint(grp ? xc : xa), Y = __float_as_uint(grp ? xd : xb);
+            const auto r = __builtin_amdgcn_permlane32_swap(X, Y, false, false);
+            const float tot = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            if (mine != NONE) o_lds[wave][4 * hs + gg][16 * mine + n16] = tot * CODE_SCALE<BITS> + zsv[gg];
           }
-          if (q4 == gc) {
+        }
+      } else {
+        const int gq = q4 < NGC ? q4 : 0;
+        float zsv[4];
 #pragma unroll
-            for (int gg = 0; gg < 4; ++gg) o_lds[wave][gg][16 * nt + n16] = a[gg] * CODE_SCALE<BITS> + zsv[gg];
+        for (int gg = 0; gg < 4; ++gg) {
+          zsv[gg] = zs_lds[wave][gq][4 * hs + gg];
+          if constexpr (VPIECES == 2) zsv[gg] += zs_lds[wave][gq + NGC][4 * hs + gg];
+        }
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt) {
+          const int gc = (16 * nt) / G;
+          if constexpr (VPIECES == 2) {   // add the residual piece's row: lane group q4 + NGC
+            float a[4];
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg) {
+              float x, y;
+              xor16_pair(st[hs].acc[nt][gg], &x, &y);   // (NGC == 1)
+              a[gg] = x + y;
+            }
+            if (q4 == gc) {
+#pragma unroll
+              for (int gg = 0; gg < 4; ++gg) o_lds[wave][4 * hs + gg][16 * nt + n16] = a[gg] * CODE_SCALE<BITS> + zsv[gg];
+            }
+          } else {
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg)
+              if (q4 == gc) o_lds[wave][4 * hs + gg][16 * nt + n16] = st[hs].acc[nt][gg] * CODE_SCALE<BITS> + zsv[gg];
           }
-        } else {
-#pragma unroll
-          for (int gg = 0; gg < 4; ++gg)
-            if (q4 == gc) o_lds[wave][gg][16 * nt + n16] = st.acc[nt][gg] * CODE_SCALE<BITS> + zsv[gg];
         }
       }
     }
@@ -1092,14 +1146,17 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     quantized_rows();
   } else {
     fp_rows(deal.unit0, deal.unit_step);
-    const float l_tot = head_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
-    if (lane < 4) { ml_lds[wave][g][0] = st.m; ml_lds[wave][g][1] = l_tot; }
 #pragma unroll
-    for (int nt = 0; nt < NNT; ++nt) {
+    for (int hs = 0; hs < NH; ++hs) {
+      const float l_tot = head_sum((st[hs].l[0] + st[hs].l[1]) + (st[hs].l[2] + st[hs].l[3]));
+      if (lane < 4) { ml_lds[wave][4 * hs + g][0] = st[hs].m; ml_lds[wave][4 * hs + g][1] = l_tot; }
 #pragma unroll
-      for (int gg = 0; gg < 4; ++gg) {   // the sum of head and residual rows
-        const float v = st.acc[nt][gg] + __shfl_xor(st.acc[nt][gg], 16);
-        if (q4 == 0) o_lds[wave][gg][16 * nt + n16] = v;
+      for (int nt = 0; nt < NNT; ++nt) {
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {   // the sum of head and residual rows
+          const float v = st[hs].acc[nt][gg] + __shfl_xor(st[hs].acc[nt][gg], 16);
+          if (q4 == 0) o_lds[wave][4 * hs + gg][16 * nt + n16] = v;
+        }
       }
     }
   }
@@ -1119,7 +1176,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       L += a * ml_lds[w][gg][1];
     }
     if (one_split) {   // nothing to merge across workgroups: this is the result
-      P.out[((int64_t)bh * P.gh + hsub * P.hb + gg) * D + c] = f2t<BF16>(acc / L);
+      P.out[(head0 + gg) * D + c] = f2t<BF16>(acc / L);
       continue;
     }
     const int64_t base = part_base + gg * (D + 4);
@@ -1147,7 +1204,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   }
   __syncthreads();
   if (!is_last) return;
-  // Up to NI * RPI splits one wavefront merges a head.  With more of them all wavefronts merge, those with wave % hb == h
+  // Up to NI * RPI splits one wavefront merges a head (several in turn where there are fewer wavefronts).  With more of them all wavefronts merge, those with wave % hb == h
   // sharing the rows (splits) of head h, and their sums meet in LDS: 0.8 us less from the ticket to the end at 32 splits,
   // but 0.6 us more at few (3 splits of 512 tokens 9.7 instead of 9.0 us a launch, 8 splits of 2048 tokens at d = 64
   // 8.7 instead of 8.0).  The partials are read past the caches (device-coherent loads), 16 bytes per lane so that the
@@ -1159,84 +1216,86 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   constexpr int RPI = 64 / C4;                 // rows covered by one wave-level load
   constexpr int NI = 8;                        // loads in flight
   const int rows = P.splits;
-  const bool alone = rows <= NI * RPI;         // one wavefront per head: one batch of loads, no sum over wavefronts
-  if (alone && wave >= P.hb) return;
-  const int head = wave % P.hb, part = wave / P.hb, parts = alone ? 1 : NWB / P.hb;
+  // one wavefront per head, no sum over wavefronts: where one batch of loads will do, or there are no more wavefronts
+  const bool alone = rows <= NI * RPI || NWB <= P.hb;
+  const int parts = alone ? 1 : NWB / P.hb;
   const int64_t gstride = (int64_t)P.gh * PR;  // floats between consecutive splits
-  const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + head) * PR;
-  // buffer descriptor over this head's rows of all splits: out-of-range lanes read 0
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(gbase), 0, (int)(((int64_t)(rows - 1) * gstride + PR) * 4), 0x00020000);
-  const int r = lane / C4, c4 = lane % C4;
-  const int oob = 0x7FFFFFF0;
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  u32x2 ml[4];
+  float* sum = &o_lds[0][0][0];                // [part][head][D] (o_lds is free again)
+  static_assert(sizeof(o_lds) >= NWB * D * sizeof(float), "parts * hb = NWB rows of sums");
+  for (int hp = wave; hp < P.hb * parts; hp += NWB) {   // (head, part): several heads in turn where there are fewer wavefronts
+    const int head = hp % P.hb, part = hp / P.hb;
+    const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + head) * PR;
+    // buffer descriptor over this head's rows of all splits: out-of-range lanes read 0
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(gbase), 0, (int)(((int64_t)(rows - 1) * gstride + PR) * 4), 0x00020000);
+    const int r = lane / C4, c4 = lane % C4;
+    const int oob = 0x7FFFFFF0;
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 ml[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int sidx = lane + 64 * k;
-    ml[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, sidx < rows ? (int)((sidx * gstride + D) * 4) : oob, 0, 16);
-  }
-  // load i of this wavefront: rows (i * parts + part) * RPI + r; past the last row the descriptor's end makes it zeros
-  const int row0 = part * RPI + r, row_step = parts * RPI;
-  const uint32_t off0 = r < RPI ? (uint32_t)(row0 * gstride + 4 * c4) * 4 : (uint32_t)oob, off_step = (uint32_t)(row_step * gstride) * 4;
-  u32x4 ov[NI];
-  auto load_rows = [&](int i0) {               // the i0-th .. (i0 + NI - 1)-th load of this wavefront
-    uint32_t off = off0 + i0 * off_step;
-#pragma unroll
-    for (int i = 0; i < NI; ++i, off += off_step) ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 16);
-  };
-  load_rows(0);
-  float w[4], mx = -INFINITY, ls = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    w[k] = lane + 64 * k < rows ? __uint_as_float(ml[k][0]) : -INFINITY;
-    mx = fmaxf(mx, w[k]);
-  }
-  mx = rows_max(row_max(mx));
-  float* weight = reinterpret_cast<float*>(&p_lds[wave][0][0][0]);   // this wavefront's copy, free again
-  static_assert(sizeof(p_lds[0]) >= 256 * sizeof(float), "a weight for each split");
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    w[k] = w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[k] - mx);
-    ls += w[k] * __uint_as_float(ml[k][1]);    // (0 * 0 past the last row)
-    weight[lane + 64 * k] = w[k];
-  }
-  ls = rows_sum(row_sum(ls));
-  wave_lds_sync();
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = 0;;) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const float wi = weight[(row0 + (i0 + i) * row_step) & 255];   // (past the last row the loads are zeros)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, __uint_as_float(ov[i][e]), acc[e]);
+    for (int k = 0; k < 4; ++k) {
+      const int sidx = lane + 64 * k;
+      ml[k] = __builtin_amdgcn_raw_buffer_load_b64(rs, sidx < rows ? (int)((sidx * gstride + D) * 4) : oob, 0, 16);
     }
-    i0 += NI;
-    if (i0 * row_step >= rows) break;
-    load_rows(i0);
-  }
-  // add the RPI row classes (lanes c4, c4 + C4, ...), then the parts, in LDS (o_lds is free again)
+    // load i of this wavefront: rows (i * parts + part) * RPI + r; past the last row the descriptor's end makes it zeros
+    const int row0 = part * RPI + r, row_step = parts * RPI;
+    const uint32_t off0 = r < RPI ? (uint32_t)(row0 * gstride + 4 * c4) * 4 : (uint32_t)oob, off_step = (uint32_t)(row_step * gstride) * 4;
+    u32x4 ov[NI];
+    auto load_rows = [&](int i0) {               // the i0-th .. (i0 + NI - 1)-th load of this wavefront
+      uint32_t off = off0 + i0 * off_step;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float t = acc[e];
+      for (int i = 0; i < NI; ++i, off += off_step) ov[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 16);
+    };
+    load_rows(0);
+    float w[4], mx = -INFINITY, ls = 0.f;
 #pragma unroll
-    for (int k = 1; k < RPI; ++k) t += from_lane(acc[e], (lane + k * C4) & 63);
-    acc[e] = t;
-  }
-  if (alone) {
-    if (lane < C4) {
+    for (int k = 0; k < 4; ++k) {
+      w[k] = lane + 64 * k < rows ? __uint_as_float(ml[k][0]) : -INFINITY;
+      mx = fmaxf(mx, w[k]);
+    }
+    mx = rows_max(row_max(mx));
+    float* weight = reinterpret_cast<float*>(&p_lds[wave][0][0][0]);   // this wavefront's copy, free again
+    static_assert(sizeof(p_lds[0]) >= 256 * sizeof(float), "a weight for each split");
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      w[k] = w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[k] - mx);
+      ls += w[k] * __uint_as_float(ml[k][1]);    // (0 * 0 past the last row)
+      weight[lane + 64 * k] = w[k];
+    }
+    ls = rows_sum(row_sum(ls));
+    wave_lds_sync();
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0;;) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const float wi = weight[(row0 + (i0 + i) * row_step) & 255];   // (past the last row the loads are zeros)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, __uint_as_float(ov[i][e]), acc[e]);
+      }
+      i0 += NI;
+      if (i0 * row_step >= rows) break;
+      load_rows(i0);
+    }
+    // add the RPI row classes (lanes c4, c4 + C4, ...), then the parts, in LDS
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float t = acc[e];
+#pragma unroll
+      for (int k = 1; k < RPI; ++k) t += from_lane(acc[e], (lane + k * C4) & 63);
+      acc[e] = t;
+    }
+    if (!alone) {
+      if (lane < C4) *reinterpret_cast<float4*>(sum + (part * P.hb + head) * D + 4 * c4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      if (part == 0 && lane == 0) ml_lds[0][head][1] = ls;
+    } else if (lane < C4) {
       const float inv = 1.0f / ls;
-      *reinterpret_cast<uint2*>(P.out + ((int64_t)bh * P.gh + hsub * P.hb + head) * D + 4 * c4) =
+      *reinterpret_cast<uint2*>(P.out + (head0 + head) * D + 4 * c4) =
           make_uint2((uint32_t)f2t<BF16>(acc[0] * inv) | ((uint32_t)f2t<BF16>(acc[1] * inv) << 16),
                      (uint32_t)f2t<BF16>(acc[2] * inv) | ((uint32_t)f2t<BF16>(acc[3] * inv) << 16));
     }
-    return;
   }
-  float* sum = &o_lds[0][0][0];                // [part][head][D]
-  static_assert(sizeof(o_lds) >= NWB * D * sizeof(float), "parts * hb = NWB rows of sums");
-  if (lane < C4) *reinterpret_cast<float4*>(sum + (part * P.hb + head) * D + 4 * c4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-  if (part == 0 && lane == 0) ml_lds[0][head][1] = ls;
+  if (alone) return;
   __syncthreads();
   for (int idx = threadIdx.x; idx < P.hb * D / 2; idx += 64 * NWB) {
     float2 t = *reinterpret_cast<const float2*>(sum + 2 * idx);
@@ -1245,62 +1304,62 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       t.x += x.x; t.y += x.y;
     }
     const float inv = 1.0f / ml_lds[0][2 * idx / D][1];
-    *reinterpret_cast<uint32_t*>(P.out + ((int64_t)bh * P.gh + hsub * P.hb) * D + 2 * idx) =
+    *reinterpret_cast<uint32_t*>(P.out + head0 * D + 2 * idx) =
         (uint32_t)f2t<BF16>(t.x * inv) | ((uint32_t)f2t<BF16>(t.y * inv) << 16);
   }
 }
 
-template <bool BF16, int D, int NWB, int BITS, int KIND, int PROG>
+template <bool BF16, int D, int NWB, int BITS, int NH, int KIND, int PROG>
 static hipError_t launch_mfma_g(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   SeqArgs<KIND> S;
   if constexpr (KIND != EQUAL)
     if (seq && seq->in_args())
       for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
   switch (s.G) {
-    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, KIND, PROG>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
   }
   return launch_status(__func__);
 }
 
-template <bool BF16, int D, int NWB, int BITS, int PROG>
+template <bool BF16, int D, int NWB, int BITS, int NH, int PROG>
 static hipError_t launch_mfma_k(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   if constexpr (PROG != DRAWN || NWB != 4)
-    if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, PADDED, PROG>(s, P, seq, grid, st);
+    if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, NH, PADDED, PROG>(s, P, seq, grid, st);
   if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws)
-    if (seq) return launch_mfma_g<BF16, D, NWB, BITS, PER_ROW, PROG>(s, P, seq, grid, st);
-  return launch_mfma_g<BF16, D, NWB, BITS, EQUAL, PROG>(s, P, seq, grid, st);
+    if (seq) return launch_mfma_g<BF16, D, NWB, BITS, NH, PER_ROW, PROG>(s, P, seq, grid, st);
+  return launch_mfma_g<BF16, D, NWB, BITS, NH, EQUAL, PROG>(s, P, seq, grid, st);
 }
 
-template <bool BF16, int D, int NWB, int BITS>
+template <bool BF16, int D, int NWB, int BITS, int NH>
 static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = P.tiles;
-  if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, ONE_SPLIT>(s, P, seq, grid, st);
+  if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, NH, ONE_SPLIT>(s, P, seq, grid, st);
   // (With counts per sequence each row decides for itself, in the kernel.  Padded rows of one length are not planned with
   // 4 wavefronts: forced to, they take their tiles in a fixed order.)
   if (P.splits > 1 && !seq && !(NWB == 4 && s.Wq != s.W) && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
-    return launch_mfma_k<BF16, D, NWB, BITS, DRAWN>(s, P, seq, grid, st);
+    return launch_mfma_k<BF16, D, NWB, BITS, NH, DRAWN>(s, P, seq, grid, st);
   if constexpr (NWB == 8)
     if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y * grid.z >= compute_units()))
-      return launch_mfma_k<BF16, D, NWB, BITS, APART>(s, P, seq, grid, st);
-  return launch_mfma_k<BF16, D, NWB, BITS, BY_SPLIT>(s, P, seq, grid, st);
+      return launch_mfma_k<BF16, D, NWB, BITS, NH, APART>(s, P, seq, grid, st);
+  return launch_mfma_k<BF16, D, NWB, BITS, NH, BY_SPLIT>(s, P, seq, grid, st);
 }
 
-template <bool BF16, int NWB, int BITS>
+template <bool BF16, int NWB, int BITS, int NH>
 static hipError_t launch_mfma_d(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   switch (s.d) {
-    case 64: return launch_mfma_p<BF16, 64, NWB, BITS>(s, P, seq, grid, st);
-    case 96: return launch_mfma_p<BF16, 96, NWB, BITS>(s, P, seq, grid, st);
-    default: return launch_mfma_p<BF16, 128, NWB, BITS>(s, P, seq, grid, st);
+    case 64: return launch_mfma_p<BF16, 64, NWB, BITS, NH>(s, P, seq, grid, st);
+    case 96: return launch_mfma_p<BF16, 96, NWB, BITS, NH>(s, P, seq, grid, st);
+    default: return launch_mfma_p<BF16, 128, NWB, BITS, NH>(s, P, seq, grid, st);
   }
 }
 
 // One source file for each of these (lq_attn_mfma_w*.hip): several hundred kernels in all, which as one file took many minutes.
-template <int NWB, int BITS>
+template <int NWB, int BITS, int NH>
 hipError_t launch_mfma_t(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  return s.bf16 ? launch_mfma_d<true, NWB, BITS>(s, P, seq, grid, st)
-                : launch_mfma_d<false, NWB, BITS>(s, P, seq, grid, st);
+  return s.bf16 ? launch_mfma_d<true, NWB, BITS, NH>(s, P, seq, grid, st)
+                : launch_mfma_d<false, NWB, BITS, NH>(s, P, seq, grid, st);
 }
 
 }  // namespace lq

@@ -5,11 +5,24 @@
 
 namespace lq {
 
-extern template hipError_t launch_mfma_t<12, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 4>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 4>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<12, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 4, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 4, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 4, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 4, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+
+template <int NH>
+static hipError_t launch_heads(const Shape& s, const AttnParams& P, int waves_per_block, const SeqArg* seq, dim3 grid, hipStream_t st) {
+  if constexpr (NH == 1)
+    if (waves_per_block == 12) return launch_mfma_t<12, 2, 1>(s, P, seq, grid, st);
+  if (waves_per_block == 4)
+    return s.bits == 4 ? launch_mfma_t<4, 4, NH>(s, P, seq, grid, st) : launch_mfma_t<4, 2, NH>(s, P, seq, grid, st);
+  return s.bits == 4 ? launch_mfma_t<8, 4, NH>(s, P, seq, grid, st) : launch_mfma_t<8, 2, NH>(s, P, seq, grid, st);
+}
 
 // seq == nullptr: every sequence has the counts of `c` and the live buffer c.cur;
 // otherwise the kernel reads counts, live buffer and fp-wavefront share per sequence
@@ -37,19 +50,16 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.W = s.W; P.Wq = s.Wq; P.live.set(s.W, s.Wq);
   P.dead_bit = (int64_t)s.qcap * s.d * s.bits / 8 <= ((int64_t)1 << 31) ? 0x80000000u : 0u;   // (codes: the largest array)
   P.tiles = tiles_of(s, c.n_q); P.n_tok_q = quantized_tokens(s, c.n_q);
-  P.hb = s.gh % 4 == 0 ? 4 : (s.gh % 2 == 0 ? 2 : 1);
+  const int groups = plan.blocks / plan.splits;   // B * Hkv * (gh / hb), as planned
+  P.hb = s.gh / (groups / (s.B * s.Hkv));
   P.splits = plan.splits; P.nwf = plan.fp_waves; P.cus = seq && pairs_workgroups(plan) ? 1 << 30 : compute_units();
   P.c = scale * 1.4426950408889634f;
   static const int dynamic = [] { const char* v = getenv("LOGQUANT_ATTN_DYNAMIC"); return v && *v ? atoi(v) : 1; }();
   P.dynamic = dynamic;
-  const int groups = s.B * s.Hkv * (s.gh / P.hb);
   P.across = groups % 8 == 0 ? 8 : 1;
   P.div_subgroups.set(s.gh / P.hb); P.div_kv_heads.set(s.Hkv);
   const dim3 grid(P.across, plan.splits, groups / P.across);
-  if (plan.waves_per_block == 12 && s.bits == 2) return launch_mfma_t<12, 2>(s, P, seq, grid, st);
-  if (plan.waves_per_block == 4)
-    return s.bits == 4 ? launch_mfma_t<4, 4>(s, P, seq, grid, st) : launch_mfma_t<4, 2>(s, P, seq, grid, st);
-  return s.bits == 4 ? launch_mfma_t<8, 4>(s, P, seq, grid, st) : launch_mfma_t<8, 2>(s, P, seq, grid, st);
+  return P.hb > 4 ? launch_heads<2>(s, P, plan.waves_per_block, seq, grid, st) : launch_heads<1>(s, P, plan.waves_per_block, seq, grid, st);
 }
 
 }  // namespace lq

@@ -1,0 +1,6 @@
+// Decode attention kernels with 8 wavefronts per workgroup, 2-bit codes, five to eight query heads.
+#include "lq_attn_mfma.h"
+
+namespace lq {
+template hipError_t launch_mfma_t<8, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+}  // namespace lq

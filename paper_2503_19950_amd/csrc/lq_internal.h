@@ -69,6 +69,24 @@ inline int seq_mode(const SeqArg* a) { return !a ? 0 : a->in_args() ? 1 : 2; }
 // Fills `s`; returns LQ_OK or the config error.  Pure host arithmetic.
 lq_status make_shape(const lq_config* cfg, Shape* s);
 
+// Query heads of a kv head that one workgroup works on.  Up to eight share the loads and the unpacked codes; beyond four
+// they are two sets, each with its own softmax and matrix operands, and a tile or unit takes a wavefront longer.  With
+// eight heads per kv head two workgroups of four win in small launches, where latency counts and twice the wavefronts
+// share it, and one of eight in large ones, which read every byte once.  Of 110 shapes with eight heads per kv head, the 66
+// that read less than 24 MB take 0.91 to 1.54 of the time with one set of eight (1.2 on average), the 44 others 0.68 to 1.10
+// (0.88): 30 kv heads x 7872 slots, bf16, 27 MB, 19.8 -> 15.1 us; 184 x 3700, 4 bits, 116 MB, 42.9 -> 29.0; but
+// 4 x 46000, 19 MB, 14.5 -> 16.2.  Numbers that four does not come close to dividing (5, 7: one head at a time) always
+// are one set (7 heads, 16 kv heads of 4096 tokens, 17.2 -> 12.8 us; 6, 32 of 8192, 21.0 -> 12.4).
+inline int most_heads(const Shape& s, int limit) {
+  int hb = s.gh < limit ? s.gh : limit;
+  while (s.gh % hb) --hb;
+  return hb;
+}
+inline int heads_per_group(const Shape& s, int64_t bytes_read) {
+  const int many = most_heads(s, 8), few = most_heads(s, 4);
+  return 2 * few >= many && bytes_read < 24000000 ? few : many;
+}
+
 // Upper bound on context splits per (b, kv head) that decode_attn may use.
 int max_splits(const Shape& s);
 
