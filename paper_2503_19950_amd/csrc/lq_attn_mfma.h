@@ -428,6 +428,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   }
   const int q4 = lane >> 4, n16 = lane & 15, up = n16 >> 2, g = lane & 3;
   const int64_t head0 = (int64_t)bh * P.gh + hsub * P.hb;   // this workgroup's first query head
+  constexpr uint32_t OUT_OF_RANGE = 0x40000000u;            // an offset past the end of its heads' q
+  const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(P.q) + head0 * D, 0, P.hb * (D * 2), 0x00020000);
 
   // counts and live fp buffer: the same for every sequence, or (per-sequence lengths)
   // read from the sequence's entry of the state array
@@ -474,20 +476,19 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   auto fp_rows = [&](const int unit0, const int unit_step) __attribute__((always_inline)) {
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
     const int lane16 = lane * 16;
+    // q is loaded out of range (zeros, nothing read) for absent heads: as a choice after the load it became a branch, and
+    // with fewer heads than four a wait for each of these loads before the next was issued.
     uint4 qreg[NH][NKC];
 #pragma unroll
     for (int hs = 0; hs < NH; ++hs) {
-      const bool head_ok = 4 * hs + g < P.hb;
-      const int64_t qrow = (head0 + (head_ok ? 4 * hs + g : 0)) * D;
+      const uint32_t q_off = 4 * hs + g < P.hb ? (uint32_t)((4 * hs + g) * D + 8 * q4) * 2 : OUT_OF_RANGE;
 #pragma unroll
-      for (int kc = 0; kc < NKC; ++kc) {
-        qreg[hs][kc] = *reinterpret_cast<const uint4*>((const char*)P.q + (uint32_t)((qrow + 32 * kc + 8 * q4) * 2));
-        if (!head_ok) qreg[hs][kc] = make_uint4(0, 0, 0, 0);
-      }
+      for (int kc = 0; kc < NKC; ++kc) qreg[hs][kc] = buffer_load16(rs_q, (int)q_off, 64 * kc);
     }
     // Fused append: the wavefront that owns the unit receiving the new row fetches the row
     // first.  (The compiler waits for it before it issues the unit's own loads: one more
-    // latency for this wavefront.)
+    // latency for this wavefront.  As loads of all wavefronts, out of range for the others, without that wait: 1 to 1.5% slower
+    // steps at 8 rows of 8192 and 64 of 4096 tokens.)
     const int new_unit = (n_fp - 1) >> 5, new_sx = (n_fp - 1) & 31, new_kx = kperm(new_sx);
     const bool owner = P.k_new && new_unit % unit_step == unit0;
     uint4 kn_r[NKC];
@@ -702,7 +703,6 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     const auto rs_kz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kzb), 0, kmeta_bytes, 0x00020000);
     const auto rs_vs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vsb), 0, vmeta_bytes, 0x00020000);
     const auto rs_vz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vzb), 0, vmeta_bytes, 0x00020000);
-    auto load16 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) { return buffer_load16(rs, (int)voff, (int)soff); };
     auto load_words = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
       Words<WPL> r;
 #pragma unroll
@@ -745,8 +745,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
 #pragma unroll
       for (int e = 0; e < NGRP; ++e) {
         const int grp = t * NGRP / (G <= 64 ? 1 : G / 64) + e;
-        T.ks8[e] = load16(rs_ks, km_off, (uint32_t)grp * (D * 2));
-        T.kz8[e] = load16(rs_kz, km_off, (uint32_t)grp * (D * 2));
+        T.ks8[e] = buffer_load16(rs_ks, (int)km_off, (int)((uint32_t)grp * (D * 2)));
+        T.kz8[e] = buffer_load16(rs_kz, (int)km_off, (int)((uint32_t)grp * (D * 2)));
       }
     };
     auto load_kcodes = [&](Tile& T, const Place& pl) {
@@ -759,10 +759,9 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       const int t = pl.t;
       const uint32_t c_off = b2 ? v_off2 | pl.dead : code_off, m_off = b2 ? vm_off2 | pl.dead : vm_off;
       T.vc[b2] = load_words(rs_vc, c_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
-      T.vs[b2] = load16(rs_vs, m_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
-      T.vz[b2] = load16(rs_vz, m_off, (uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2));
+      T.vs[b2] = buffer_load16(rs_vs, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
+      T.vz[b2] = buffer_load16(rs_vz, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
     };
-
     // Tiles that are drawn.  The first two of a wavefront without units are fixed, and the loads of the first go out
     // before anything else touches memory.  The later tiles are dealt out dynamically, so that wavefronts that start
     // late or see slower memory take fewer of them.
@@ -797,11 +796,11 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       ta = drawn_tile(ka);
       tb = drawn_tile(kb);
     }
-    uint4 raw[NH];
+    uint4 raw[NH];   // zeros for absent heads and past the last channel
     auto load_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int hs = 0; hs < NH; ++hs)
-        raw[hs] = *reinterpret_cast<const uint4*>(P.q + (head0 + (4 * hs + q4 < P.hb ? 4 * hs + q4 : 0)) * D + (prep ? 8 * c8 : 0));
+        raw[hs] = buffer_load16(rs_q, (int)(prep && 4 * hs + q4 < P.hb ? (uint32_t)((4 * hs + q4) * D + 8 * c8) * 2 : OUT_OF_RANGE), 0);
     };
     if constexpr (Q_FIRST) load_q();
     Tile A;
@@ -818,8 +817,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     if constexpr (!Q_FIRST) load_q();
 #pragma unroll
     for (int hs = 0; hs < NH; ++hs) {
-      const uint32_t keep = prep && 4 * hs + q4 < P.hb ? 0xFFFFFFFFu : 0u;   // (a branch here waits for the tile)
-      const uint32_t qraw[4] = {raw[hs].x & keep, raw[hs].y & keep, raw[hs].z & keep, raw[hs].w & keep};
+      const uint32_t qraw[4] = {raw[hs].x, raw[hs].y, raw[hs].z, raw[hs].w};
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float f = __builtin_ldexpf(1.f, pos_exp<BITS>(v));
@@ -980,6 +978,20 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       // ---- output: two 32-token steps x NNT channel tiles
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
+        // (the probabilities are on their way from LDS before the branch)
+        uint32_t ph[NH][4], hd[NH][4];   // slots (0,1) (2,3) (4,5) (6,7); the head piece of the same slots
+#pragma unroll
+        for (int hs = 0; hs < NH; ++hs) {
+          const int at = hs * (2 * 9 * 32) + ks * (9 * 32);
+          const uint2 pa = *reinterpret_cast<const uint2*>(p_rd + at);        // tokens 4*q4 .. +3
+          const uint2 pb = *reinterpret_cast<const uint2*>(p_rd + at + 16);   // tokens 16 + 4*q4 .. +3
+          ph[hs][0] = pa.x; ph[hs][1] = pa.y; ph[hs][2] = pb.x; ph[hs][3] = pb.y;
+          if constexpr (PROD_LO && VPIECES == 2) {
+            const uint2 ha = *reinterpret_cast<const uint2*>(p_hd + at);
+            const uint2 hb = *reinterpret_cast<const uint2*>(p_hd + at + 16);
+            hd[hs][0] = ha.x; hd[hs][1] = ha.y; hd[hs][2] = hb.x; hd[hs][3] = hb.y;
+          }
+        }
         uint4 vsr = cur.vs[ks], vzr = cur.vz[ks];
         if (partial) {   // slots beyond n_q hold unspecified bits: keep them out of the sums
           uint32_t keep[4];
@@ -997,26 +1009,16 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
         uint4 a[NH], al[NH];
 #pragma unroll
         for (int hs = 0; hs < NH; ++hs) {
-          const int at = hs * (2 * 9 * 32) + ks * (9 * 32);
-          const uint2 pa = *reinterpret_cast<const uint2*>(p_rd + at);        // tokens 4*q4 .. +3
-          const uint2 pb = *reinterpret_cast<const uint2*>(p_rd + at + 16);   // tokens 16 + 4*q4 .. +3
-          const uint32_t ph[4] = {pa.x, pa.y, pb.x, pb.y};      // slots (0,1) (2,3) (4,5) (6,7)
-          uint32_t hd[4] = {pa.x, pa.y, pb.x, pb.y};            // the head piece of the same slots
-          if constexpr (PROD_LO && VPIECES == 2) {
-            const uint2 ha = *reinterpret_cast<const uint2*>(p_hd + at);
-            const uint2 hb = *reinterpret_cast<const uint2*>(p_hd + at + 16);
-            hd[0] = ha.x; hd[1] = ha.y; hd[2] = hb.x; hd[3] = hb.y;
-          }
           uint32_t aw[4], lw[4];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            const half2_t pp = __builtin_bit_cast(half2_t, ph[v]);
+            const half2_t pp = __builtin_bit_cast(half2_t, ph[hs][v]);
             const half2_t sv = meta_pair(vsw[v]);
             if constexpr (!PROD_LO) {
               aw[v] = __builtin_bit_cast(uint32_t, pp * sv);
             } else if constexpr (VPIECES == 2) {
               // head rows: p_hi * vs rounded; residual rows: what that rounding dropped plus p_lo * vs
-              const half2_t hh = __builtin_bit_cast(half2_t, hd[v]);
+              const half2_t hh = __builtin_bit_cast(half2_t, hd[hs][v]);
               const half2_t hi = hh * sv;
               const half2_t lo = __builtin_elementwise_fma(pp, sv, __builtin_elementwise_fma(hh, sv, -hi));
               aw[v] = __builtin_bit_cast(uint32_t, tail_row ? lo : hi);
