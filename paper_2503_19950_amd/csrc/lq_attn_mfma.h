@@ -476,6 +476,8 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   auto fp_rows = [&](const int unit0, const int unit_step) __attribute__((always_inline)) {
     const int64_t fp_slice = (int64_t)bh * P.cap * D;
     const int lane16 = lane * 16;
+    const uint16_t* kb = k_fp_w + fp_slice + lane * 8;
+    const uint16_t* vb = v_fp_w + fp_slice + lane * 8;
     // q is loaded out of range (zeros, nothing read) for absent heads: as a choice after the load it became a branch, and
     // with fewer heads than four a wait for each of these loads before the next was issued.
     uint4 qreg[NH][NKC];
@@ -502,10 +504,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       for (int nt = 0; nt < NNT; ++nt) vn_r[nt] = *reinterpret_cast<const uint16_t*>(vn + 32 * nt + (uint32_t)(2 * n16));
     }
     for (int unit = unit0; unit < TF; unit += unit_step) {
-      // Buffer accesses, one descriptor for the keys of a unit and one for its values: as 64-bit lane addresses the
-      // compiler kept a pair of registers for each load and store, and with 12 wavefronts spilled up to 20 for d = 128.
-      // A kernel with scratch memory starts later (29 rows x 8 kv heads x 1548 tokens, one launch 21.9 -> 18.1 us, 26 of
-      // 4206, one head per kv head 32.5 -> 26.8, 15 of 21020 51.4 -> 48.3, one of 131072 24.0 -> 23.5).
+      // The stores of the new row, and with 12 wavefronts the loads, are buffer accesses, one descriptor for the keys of a
+      // unit and one for its values: with 64-bit lane addresses for all of them 12 wavefronts spilled up to 20 registers
+      // for d = 128, and a kernel with scratch memory starts later (29 rows x 8 kv heads x 1548 tokens, one launch
+      // 21.9 -> 18.1 us, 26 of 4206, one head per kv head 32.5 -> 26.8, 15 of 21020 51.4 -> 48.3, one of 131072
+      // 24.0 -> 23.5).  With 4 and 8, which have the registers, lane addresses are 1% faster (8 rows of 8192, four layers,
+      // 65.5 against 64.8 us).
       const auto rs_kf = __builtin_amdgcn_make_buffer_rsrc(k_fp_w + fp_slice + (int64_t)unit * (32 * D), 0, 32 * D * 2, 0x00020000);
       const auto rs_vf = __builtin_amdgcn_make_buffer_rsrc(v_fp_w + fp_slice + (int64_t)unit * (32 * D), 0, 32 * D * 2, 0x00020000);
       uint4 ka[2][NKC], va[NNT];
@@ -513,10 +517,11 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       for (int uu = 0; uu < 2; ++uu)
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc)
-          ka[uu][kc] = buffer_load16(rs_kf, lane16, (uu * NKC + kc) * 1024);
+          ka[uu][kc] = NWB == 12 ? buffer_load16(rs_kf, lane16, (uu * NKC + kc) * 1024)
+                                 : *reinterpret_cast<const uint4*>(kb + ((int64_t)(2 * unit + uu) * NKC + kc) * 512);
 #pragma unroll
       for (int nt = 0; nt < NNT; ++nt)
-        va[nt] = buffer_load16(rs_vf, lane16, nt * 1024);
+        va[nt] = NWB == 12 ? buffer_load16(rs_vf, lane16, nt * 1024) : *reinterpret_cast<const uint4*>(vb + ((int64_t)unit * NNT + nt) * 512);
 
       if (owner && unit == new_unit) {
         // Fused append.  This wavefront is the only reader of the unit that receives
