@@ -1,0 +1,6 @@
+// Decode attention kernels with 8 wavefronts per workgroup, 2-bit codes, up to four query heads, values read past the caches.
+#include "lq_attn_mfma.h"
+
+namespace lq {
+template hipError_t launch_mfma_t<8, 2, 1, NT>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+}  // namespace lq
