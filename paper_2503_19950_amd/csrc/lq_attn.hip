@@ -111,6 +111,18 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
       if (t < best - 1e-9) { best = t; best_wpb = wpb; best_splits = sp; }
     }
   }
+  // At most two items (units of fp rows, tiles) to a wavefront of 8, or nothing but fp rows: one split.  The estimate above
+  // divides the work evenly, but an item is not shared, and what a split saves is less than the merge costs (72 kv heads
+  // with 15 units and no tile 9.3 us a launch in seven splits of 4, 7.4 in one of 8; 16 with 11 units and 4 tiles 6.8 and
+  // 6.3; of 33 shapes inside the rule those in one split take 0.77 to 1.04 of the time, 0.90 on average, of the 25 others
+  // with up to 32 items 0.76 to 1.48, 1.12).  Not fp16 caches of three or four channel groups with tiles: their
+  // probabilities are rounded, all but a wavefront's heaviest, and with fewer wavefronts outputs are further off (520
+  // tokens, d = 128, G = 32, 2.319e-4 of the 2-norm in three splits, 2.329e-4 in one, though 5.9 instead of 7.5 us).
+  if (rows != DIFFERENT_LENGTHS && best_splits > 1 && !force_wpb && !force_splits &&
+      (TQ == 0 ? TF <= 24 : TF + TQ <= 16 && (s.bf16 || s.ngc <= 2))) {
+    best_wpb = 8;
+    best_splits = 1;
+  }
   // Twelve wavefronts per workgroup (three per SIMD) pay off for long contexts on few
   // groups: measured on 131072 tokens x 8 kv heads 25.7 against 27.3 us, but slower
   // than 8 with fewer than ~6 tiles per wavefront and slower than 4 when every
