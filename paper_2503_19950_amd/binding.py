@@ -332,7 +332,9 @@ class DeviceCache:
 
     def _stream(self):
         # the current stream's handle alone: as an attribute of a torch.cuda.Stream made for the purpose it was 1.9 of the
-        # 7.3 us of a call
+        # 7.3 us of a call.  A device of another type is refused, as by current_stream: its addresses are not the GPU's
+        if self.device.type != "cuda":
+            raise ValueError("Expected a cuda device, but got: %s" % self.device)
         i = self.device.index
         return self.torch._C._cuda_getCurrentRawStream(self.torch.cuda.current_device() if i is None else i)
 

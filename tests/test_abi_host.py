@@ -293,3 +293,13 @@ def test_static_scratch_entry_point_rejects_configs_beyond_its_array():
             setattr(cache, name, 1)
     cache.n_fp, cache.n_q = 10, 0
     assert B.logquant_decode_attn_static(big, cache, 1, 0.0, 1) == B.LQ_ERR_CAPACITY
+
+
+def test_a_cache_off_the_gpu_is_refused(monkeypatch):
+    """Where there is a GPU, a cache on another device must not reach the library: its kernels would take host addresses."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda i: 0)
+    monkeypatch.setattr(B, "logquant_workspace_init", lambda *a: pytest.fail("the library was called"))
+    with pytest.raises(ValueError, match="cuda device"):
+        B.DeviceCache(_cfg(), device="cpu")
