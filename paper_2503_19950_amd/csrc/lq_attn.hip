@@ -115,11 +115,12 @@ void plan_decode(const Shape& s, int n_fp, int n_q, int64_t bytes_read, lq_plan*
   // divides the work evenly, but an item is not shared, and what a split saves is less than the merge costs (72 kv heads
   // with 15 units and no tile 9.3 us a launch in seven splits of 4, 7.4 in one of 8; 16 with 11 units and 4 tiles 6.8 and
   // 6.3; of 33 shapes inside the rule those in one split take 0.77 to 1.04 of the time, 0.90 on average, of the 25 others
-  // with up to 32 items 0.76 to 1.48, 1.12).  Not fp16 caches of three or four channel groups with tiles: their
-  // probabilities are rounded, all but a wavefront's heaviest, and with fewer wavefronts outputs are further off (520
-  // tokens, d = 128, G = 32, 2.319e-4 of the 2-norm in three splits, 2.329e-4 in one, though 5.9 instead of 7.5 us).
+  // with up to 32 items 0.76 to 1.48, 1.12).  Not caches of three or four channel groups with tiles: their probabilities
+  // are rounded, all but a wavefront's heaviest, and with fewer wavefronts outputs are further off (520 tokens, d = 128,
+  // G = 32, fp16 2.319e-4 of the 2-norm in three splits, 2.329e-4 in one, though 5.9 instead of 7.5 us; bf16 1.6614e-3
+  // and 1.6688e-3, d = 96 1.6583e-3 and 1.6748e-3).
   if (rows != DIFFERENT_LENGTHS && best_splits > 1 && !force_wpb && !force_splits &&
-      (TQ == 0 ? TF <= 24 : TF + TQ <= 16 && (s.bf16 || s.ngc <= 2))) {
+      (TQ == 0 ? TF <= 24 : TF + TQ <= 16 && s.ngc <= 2)) {
     best_wpb = 8;
     best_splits = 1;
   }

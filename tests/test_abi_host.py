@@ -231,6 +231,15 @@ def test_plans_of_rows_of_different_lengths_with_few_tiles():
     assert plan(12, 621, fp_budget=256) == (4, 4, 5)   # 8 wavefronts: 2 splits
 
 
+def test_few_items_of_three_or_four_channel_groups_stay_split():
+    """One split has fewer wavefronts, and with three or four channel groups only a wavefront's heaviest token keeps an
+    unrounded probability: outputs were further off, with bf16 as with fp16."""
+    for d in (96, 128):
+        for dtype in ("f16", "bf16"):
+            assert B.logquant_decode_plan(_cfg(d=d, dtype=dtype), 136, 384).splits > 1           # 5 units, 6 tiles
+            assert B.logquant_decode_plan(_cfg(d=d, dtype=dtype, group=64), 136, 384).splits == 1
+
+
 def test_head_groups_of_rows_of_different_lengths_follow_the_bytes_read():
     """Eight query heads are one set from 24 MB: what the rows read, not the longest row times their number."""
     def heads_per_workgroup(lengths):
