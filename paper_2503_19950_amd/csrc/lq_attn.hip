@@ -111,18 +111,23 @@ void plan_decode(const Shape& s, int n_fp, int n_q, int64_t bytes_read, lq_plan*
       if (t < best - 1e-9) { best = t; best_wpb = wpb; best_splits = sp; }
     }
   }
-  // At most two items (units of fp rows, tiles) to a wavefront of 8, or nothing but fp rows: one split.  The estimate above
-  // divides the work evenly, but an item is not shared, and what a split saves is less than the merge costs (72 kv heads
-  // with 15 units and no tile 9.3 us a launch in seven splits of 4, 7.4 in one of 8; 16 with 11 units and 4 tiles 6.8 and
-  // 6.3; of 33 shapes inside the rule those in one split take 0.77 to 1.04 of the time, 0.90 on average, of the 25 others
-  // with up to 32 items 0.76 to 1.48, 1.12).  Not caches of three or four channel groups with tiles: their probabilities
-  // are rounded, all but a wavefront's heaviest, and with fewer wavefronts outputs are further off (520 tokens, d = 128,
-  // G = 32, fp16 2.319e-4 of the 2-norm in three splits, 2.329e-4 in one, though 5.9 instead of 7.5 us; bf16 1.6614e-3
-  // and 1.6688e-3, d = 96 1.6583e-3 and 1.6748e-3).
-  if (rows != DIFFERENT_LENGTHS && best_splits > 1 && !force_wpb && !force_splits &&
-      (TQ == 0 ? TF <= 24 : TF + TQ <= 16 && s.ngc <= 2)) {
+  // Few items (units of fp rows, tiles): one split of 8.  The estimate above divides the work evenly, but an item is not
+  // shared, and what a split saves is less than the merge costs: nothing but fp rows, 2 to 128 kv heads, take 0.72 to 0.96
+  // of the time up to 20 units (three to a wavefront), 0.80 to 0.90 up to 24 for d = 64 or where the groups alone fill a
+  // quarter of the chip; elsewhere 24 units take 1.03.  8, not the 12 below, which would have a second set of empty
+  // wavefronts (20 units, d = 128: 1.07 of the time of the splits with 12, 0.95 with 8).  With tiles up to two items to a
+  // wavefront: 0.73 to 0.98 of the time, but with more than one unit to a wavefront and few groups the long ones, d = 96 and
+  // 128, only up to 14 items (0.96 to 0.99; 15 take 1.00 to 1.05), and d = 128 with one channel group not at all (1.03 to
+  // 1.10).  Not caches of three or four channel groups with tiles: their probabilities are rounded, all but a wavefront's
+  // heaviest, and with fewer wavefronts outputs are further off (520 tokens, d = 128, G = 32, fp16 2.319e-4 of the 2-norm
+  // in three splits, 2.329e-4 in one, though 5.9 instead of 7.5 us; bf16 1.6614e-3 and 1.6688e-3, d = 96 1.6583e-3 and
+  // 1.6748e-3).
+  const bool easy = s.d == 64 || 4 * groups >= cus;
+  const int most_items = TQ == 0 ? (easy ? 24 : 20) : s.ngc > 2 ? 0 : easy || TF <= 8 ? 16 : s.d == 128 && s.ngc == 1 ? 8 : 14;
+  if (rows != DIFFERENT_LENGTHS && best_splits > 1 && !force_wpb && !force_splits && TF + TQ <= most_items) {
     best_wpb = 8;
     best_splits = 1;
+    keep_8 = true;
   }
   // Twelve wavefronts per workgroup (three per SIMD) pay off for long contexts on few
   // groups: measured on 131072 tokens x 8 kv heads 25.7 against 27.3 us, but slower

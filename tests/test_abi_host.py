@@ -240,6 +240,24 @@ def test_few_items_of_three_or_four_channel_groups_stay_split():
             assert B.logquant_decode_plan(_cfg(d=d, dtype=dtype, group=64), 136, 384).splits == 1
 
 
+def test_few_items_get_one_split_of_8_wavefronts():
+    """Also where 12 wavefronts would otherwise take its place, and not where a split was faster."""
+    def plan(n_fp, n_q, **kw):
+        p = B.logquant_decode_plan(_cfg(**kw), n_fp, n_q)
+        return p.waves_per_block, p.splits
+    wide = dict(fp_budget=1024, group=128)
+    assert plan(20 * 32, 0, **wide) == (8, 1)
+    assert plan(21 * 32, 0, **wide)[1] > 1
+    assert plan(24 * 32, 0, d=64, **wide) == (8, 1)
+    assert plan(24 * 32, 0, B=8, **wide) == (8, 1)                        # 64 groups
+    assert plan(24 * 32 + 1, 0, B=8, **wide) != (8, 1)
+    for kw in (dict(group=64, fp_budget=256), dict(group=128, d=96, fp_budget=256)):
+        assert plan(10 * 32, 4 * 64, B=2, q_capacity=1280, **kw) == (8, 1)
+        assert plan(11 * 32, 4 * 64, B=2, q_capacity=1280, **kw)[1] > 1
+    assert plan(9 * 32, 128, group=128, fp_budget=256)[1] > 1
+    assert plan(8 * 32, 128, group=128, fp_budget=256) == (8, 1)
+
+
 def test_head_groups_of_rows_of_different_lengths_follow_the_bytes_read():
     """Eight query heads are one set from 24 MB: what the rows read, not the longest row times their number."""
     def heads_per_workgroup(lengths):
