@@ -86,6 +86,10 @@ void plan_decode(const Shape& s, int n_fp, int n_q, int64_t bytes_read, lq_plan*
     const bool unsplit_8 = best < 1e300 && best_splits == 1;   // (wpb == 4: what the candidates of 8 came to)
     for (int sp = 1; sp <= smax; ++sp) {
       if (force_splits && sp != force_splits && force_splits <= smax) continue;
+      // Two sets of query heads: workgroups of 4 only unsplit, where 8 take 1.13 to 1.32 times as long (8 shapes).  Of 37 shapes
+      // with rows of one length that the estimate would split among 4, 8 take 0.81 to 1.15 of the time, 0.94 on average (30 kv heads
+      // x 13125 tokens, d = 96, 4 bits, 8 heads each, 0.81).
+      if (hb > 4 && wpb == 4 && sp > 1 && rows == LOCK_STEP && !force_wpb) break;
       const int rounds = (sp * groups + slots - 1) / slots;
       // Rows of different lengths, more workgroups than fit at once: the last round is one of short rows and never full,
       // so that 8 wavefronts are done sooner than their count of rounds says.  Where they would not split, 4 do not

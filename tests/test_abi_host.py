@@ -258,6 +258,16 @@ def test_few_items_get_one_split_of_8_wavefronts():
     assert plan(8 * 32, 128, group=128, fp_budget=256) == (8, 1)
 
 
+def test_two_sets_of_query_heads_are_split_among_workgroups_of_8():
+    def plan(rows, Hkv, n_q, **kw):
+        p = B.logquant_decode_plan(_cfg(B=rows, Hq=8 * Hkv, Hkv=Hkv, q_capacity=131072, **kw), 140, n_q)
+        assert p.blocks == p.splits * rows * Hkv
+        return p.waves_per_block, p.splits
+    assert plan(15, 2, 13056, bits=4) == (8, 8)
+    assert plan(39, 1, 64000) == (8, 6)
+    assert plan(60, 8, 1024) == (4, 1)
+
+
 def test_head_groups_of_rows_of_different_lengths_follow_the_bytes_read():
     """Eight query heads are one set from 24 MB: what the rows read, not the longest row times their number."""
     def heads_per_workgroup(lengths):
