@@ -224,7 +224,7 @@ extern "C" lq_status logquant_plain_decode_attn(const lq_config* cfg, const lq_c
   if (st != LQ_OK) return st;
   if (cache->n_fp + cache->n_q < 1) return LQ_ERR_STATE;
   lq_plan plan;
-  plan_decode(s, cache->n_fp, cache->n_q, cache_bytes_read(s, cache->n_fp, cache->n_q), &plan);
+  plan_decode(s, cache->n_fp, cache->n_q, &plan);
   if (!(softmax_scale > 0.f)) softmax_scale = 1.0f / sqrtf((float)s.d);
   clear_stale_error();
   void* ws = split_workspace(s, workspace).partials;
