@@ -197,7 +197,7 @@ lq_status logquant_decode_plan(const lq_config* cfg, int32_t n_fp, int32_t n_q, 
   if (st != LQ_OK) return st;
   if (n_fp < 0 || n_fp > s.full || n_q < 0 || n_q > s.qcap || n_q % s.Wq || n_fp + n_q < 1)
     return LQ_ERR_STATE;
-  plan_decode(s, n_fp, n_q, cache_bytes_read(s, n_fp, n_q), out);
+  plan_decode(s, n_fp, n_q, out);
   return LQ_OK;
 }
 
@@ -211,7 +211,7 @@ lq_status logquant_decode_attn(const lq_config* cfg, const lq_cache* cache, cons
   if ((st = cache_state_ok(s, cache)) != LQ_OK) return st;
   if (cache->n_fp + cache->n_q < 1) return LQ_ERR_STATE;
   lq_plan plan;
-  plan_decode(s, cache->n_fp, cache->n_q, cache_bytes_read(s, cache->n_fp, cache->n_q), &plan);
+  plan_decode(s, cache->n_fp, cache->n_q, &plan);
   if (!(softmax_scale > 0.f)) softmax_scale = 1.0f / sqrtf((float)s.d);
   clear_stale_error();
   if (launch_decode_attn(s, *cache, q, softmax_scale, out, split_workspace(s, workspace), plan, (hipStream_t)stream) !=
@@ -248,7 +248,7 @@ lq_status logquant_decode_attn_static(const lq_config* cfg, const lq_cache* cach
   const size_t partial_bytes = logquant_workspace_bytes(cfg) - counter_bytes(s);
   if (counter_bytes(s) > STATIC_COUNTER_BYTES || partial_bytes > STATIC_PARTIAL_BYTES) return LQ_ERR_CAPACITY;
   lq_plan plan;
-  plan_decode(s, cache->n_fp, cache->n_q, cache_bytes_read(s, cache->n_fp, cache->n_q), &plan);
+  plan_decode(s, cache->n_fp, cache->n_q, &plan);
   if (!(softmax_scale > 0.f)) softmax_scale = 1.0f / sqrtf((float)s.d);
   clear_stale_error();
   int dev = -1;
@@ -288,7 +288,7 @@ lq_status logquant_decode_step(const lq_config* cfg, lq_cache* cache, const void
   lq_cache after = *cache;
   after.n_fp += 1;
   lq_plan plan;
-  plan_decode(s, after.n_fp, after.n_q, cache_bytes_read(s, after.n_fp, after.n_q), &plan);
+  plan_decode(s, after.n_fp, after.n_q, &plan);
   if (!(softmax_scale > 0.f)) softmax_scale = 1.0f / sqrtf((float)s.d);
   clear_stale_error();
   if (launch_decode_step(s, after, k_new, v_new, q, softmax_scale, out, split_workspace(s, workspace), plan,
@@ -343,21 +343,22 @@ static SeqState seq_entry(const Shape& s, int n_fp, int n_q, int cur) {
 static void plan_seq(const Shape& s, const int* n_fp, const int* n_q, lq_plan* plan, SeqState* st) {
   int mf = 0, mq = 0;
   bool same = true;
-  int64_t bytes = 0;
-  Shape one = s;
-  one.B = 1;
   for (int b = 0; b < s.B; ++b) {
     if (n_fp[b] > mf) mf = n_fp[b];
     if (n_q[b] > mq) mq = n_q[b];
     same = same && n_fp[b] == n_fp[0] && n_q[b] == n_q[0];
-    bytes += cache_bytes_read(one, n_fp[b], n_q[b]);
   }
-  plan_decode(s, mf, mq, bytes, plan, same ? SAME_LENGTH : DIFFERENT_LENGTHS);
+  plan_decode(s, mf, mq, plan, same ? SAME_LENGTH : DIFFERENT_LENGTHS);
   const int NW = plan->splits * plan->waves_per_block;
+  int64_t bytes = 0;
+  Shape one = s;
+  one.B = 1;
   for (int b = 0; b < s.B; ++b) {
+    bytes += cache_bytes_read(one, n_fp[b], n_q[b]);
     if (st) st[b].item = tiles_of(s, n_q[b]);
     if (st) st[b].nwf = plan->splits == 1 && mq > 0 ? 0 : fp_wave_share(s, NW, n_fp[b], n_q[b]);   // (0: no share is kept)
   }
+  plan->bytes_read = bytes;
   if (st) {   // rows by decreasing work (stable: equal rows keep their order)
     std::vector<int> idx(s.B);
     for (int b = 0; b < s.B; ++b) idx[b] = b;

@@ -56,11 +56,11 @@ int fp_wave_share(const Shape& s, int NW, int n_fp, int n_q) {
   return best;
 }
 
-// n_fp, n_q: of the longest row; bytes_read: of all rows.
-void plan_decode(const Shape& s, int n_fp, int n_q, int64_t bytes_read, lq_plan* plan, Rows rows) {
+void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
   const int TQ = tiles_of(s, n_q), TF = (n_fp + 31) / 32;
   const double r = fp_unit_weight(s);
   const double units = TQ + r * TF;
+  const int64_t bytes_read = cache_bytes_read(s, n_fp, n_q);
   const int hb = heads_per_group(s, bytes_read);
   const int groups = s.B * s.Hkv * (s.gh / hb);
   const int cus = compute_units();

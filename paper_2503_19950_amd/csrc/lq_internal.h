@@ -77,9 +77,6 @@ lq_status make_shape(const lq_config* cfg, Shape* s);
 // (0.88): 30 kv heads x 7872 slots, bf16, 27 MB, 19.8 -> 15.1 us; 184 x 3700, 4 bits, 116 MB, 42.9 -> 29.0; but
 // 4 x 46000, 19 MB, 14.5 -> 16.2.  Numbers that four does not come close to dividing (5, 7: one head at a time) always
 // are one set (7 heads, 16 kv heads of 4096 tokens, 17.2 -> 12.8 us; 6, 32 of 8192, 21.0 -> 12.4).
-// Rows of different lengths count with what each of them reads (one row of 8000 tokens and 15 of 300, 8 kv heads, 17 MB:
-// taken as 16 of 8000 they were one set, 30.5 instead of 26.6 us; of 28 shapes with eight heads the 15 below 24 MB take
-// 0.81 to 1.19 of the time with one set, 1.02 on average, the 13 others 0.66 to 1.17, 0.92).
 inline int most_heads(const Shape& s, int limit) {
   int hb = s.gh < limit ? s.gh : limit;
   while (s.gh % hb) --hb;
@@ -158,7 +155,7 @@ hipError_t launch_decode_step(const Shape& s, const lq_cache& c, const void* k_n
                               const void* q, float scale, void* out, const Workspace& ws, const lq_plan& plan,
                               hipStream_t st, const SeqArg* seq = nullptr);
 enum Rows { LOCK_STEP, SAME_LENGTH, DIFFERENT_LENGTHS };   // one set of counts, or counts per row
-void plan_decode(const Shape& s, int n_fp, int n_q, int64_t bytes_read, lq_plan* plan, Rows rows = LOCK_STEP);
+void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows = LOCK_STEP);
 int compute_units();   // of the device the launches are planned for
 // Rows of different lengths, workgroups of 4 wavefronts that are on the chip all at once, two to a compute unit: the
 // longest row shares a compute unit with the shortest, and the workgroups dispatched last, the short ones, get no

@@ -268,20 +268,6 @@ def test_two_sets_of_query_heads_are_split_among_workgroups_of_8():
     assert plan(60, 8, 1024) == (4, 1)
 
 
-def test_head_groups_of_rows_of_different_lengths_follow_the_bytes_read():
-    """Eight query heads are one set from 24 MB: what the rows read, not the longest row times their number."""
-    def heads_per_workgroup(lengths):
-        W = 64
-        cfg = _cfg(B=len(lengths), Hq=64, Hkv=8, q_capacity=16384)
-        events = [0 if x < 3 * W else (x - 3 * W) // W + 1 for x in lengths]
-        p = B.logquant_decode_plan_seq(cfg, [x - e * W for x, e in zip(lengths, events)], [W * e for e in events])
-        return p.bytes_read, 64 * len(lengths) // (p.blocks // p.splits)
-    few, many = heads_per_workgroup([8000] + [300] * 15), heads_per_workgroup([8000] * 2 + [1500] * 14)
-    assert few[0] < 24000000 <= many[0]
-    assert (few[1], many[1]) == (4, 8)
-    assert heads_per_workgroup([8000] * 16)[1] == 8
-
-
 def test_plan_counts_live_slots_only_and_state_checks_use_slots():
     # W = 42, G = 64: 64 slots per filtering event, 42 of them hold tokens; key scales and
     # zero-points exist once per 64 slots
