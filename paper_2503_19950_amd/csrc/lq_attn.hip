@@ -86,10 +86,11 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
     const bool unsplit_8 = best < 1e300 && best_splits == 1;   // (wpb == 4: what the candidates of 8 came to)
     for (int sp = 1; sp <= smax; ++sp) {
       if (force_splits && sp != force_splits && force_splits <= smax) continue;
-      // Two sets of query heads: workgroups of 4 only unsplit, where 8 take 1.13 to 1.32 times as long (8 shapes).  Of 37 shapes
-      // with rows of one length that the estimate would split among 4, 8 take 0.81 to 1.15 of the time, 0.94 on average (30 kv heads
-      // x 13125 tokens, d = 96, 4 bits, 8 heads each, 0.81).
-      if (hb > 4 && wpb == 4 && sp > 1 && rows == LOCK_STEP && !force_wpb) break;
+      // Two sets of query heads, rows of one length: not five or more splits among workgroups of 4.  Of 32 shapes that the
+      // estimate would split so, 8 wavefronts take 0.81 to 1.04 of the time, 0.93 on average (15 rows x 2 kv heads x 13125
+      // tokens, d = 96, 4 bits, 8 heads each, 19.6 -> 16.2 us).  Three splits of 4 are no worse on average (0.94 to 1.23 with
+      // 8: 39 x 8 x 5099 tokens 55 -> 68 us), and unsplit 4 are better (8 shapes 1.13 to 1.32).
+      if (hb > 4 && wpb == 4 && sp > 3 && rows == LOCK_STEP && !force_wpb) break;
       const int rounds = (sp * groups + slots - 1) / slots;
       // Rows of different lengths, more workgroups than fit at once: the last round is one of short rows and never full,
       // so that 8 wavefronts are done sooner than their count of rounds says.  Where they would not split, 4 do not

@@ -258,7 +258,7 @@ def test_few_items_get_one_split_of_8_wavefronts():
     assert plan(8 * 32, 128, group=128, fp_budget=256) == (8, 1)
 
 
-def test_two_sets_of_query_heads_are_split_among_workgroups_of_8():
+def test_many_splits_of_two_sets_of_query_heads_have_workgroups_of_8():
     def plan(rows, Hkv, n_q, **kw):
         p = B.logquant_decode_plan(_cfg(B=rows, Hq=8 * Hkv, Hkv=Hkv, q_capacity=131072, **kw), 140, n_q)
         assert p.blocks == p.splits * rows * Hkv
@@ -266,6 +266,7 @@ def test_two_sets_of_query_heads_are_split_among_workgroups_of_8():
     assert plan(15, 2, 13056, bits=4) == (8, 8)
     assert plan(39, 1, 64000) == (8, 6)
     assert plan(60, 8, 1024) == (4, 1)
+    assert plan(39, 8, 4992, group=64) == (4, 3)
 
 
 def test_plan_counts_live_slots_only_and_state_checks_use_slots():
