@@ -75,8 +75,16 @@ lq_status make_shape(const lq_config* cfg, Shape* s);
 // share it, and one of eight in large ones, which read every byte once.  Of 110 shapes with eight heads per kv head, the 66
 // that read less than 24 MB take 0.91 to 1.54 of the time with one set of eight (1.2 on average), the 44 others 0.68 to 1.10
 // (0.88): 30 kv heads x 7872 slots, bf16, 27 MB, 19.8 -> 15.1 us; 184 x 3700, 4 bits, 116 MB, 42.9 -> 29.0; but
-// 4 x 46000, 19 MB, 14.5 -> 16.2.  Numbers that four does not come close to dividing (5, 7: one head at a time) always
-// are one set (7 heads, 16 kv heads of 4096 tokens, 17.2 -> 12.8 us; 6, 32 of 8192, 21.0 -> 12.4).
+// 4 x 46000, 19 MB, 14.5 -> 16.2.  Six heads are the same: two workgroups of three below 24 MB (one set takes 0.98 to 1.43 of
+// their time, 1.27 on average, 15 shapes), one set above (0.82, 1.03 and 1.11).  Ten and fourteen are fives or sevens against
+// twos: the larger sets from where they save 24 MB of reading, 8 and 4.8 MB of the cache (0.89 to 1.45 of the time below it,
+// 1.21 on average, 16 shapes, 0.54 to 1.25, 0.85, above it, 45: 14 heads, 1 kv head x 18750 tokens, 8.2 -> 11.8 us; 24 x 5200,
+// d = 96, 41 -> 22).  Twelve and fifteen stay fours and threes: sixes and fives read too little less (above 24 MB 0.96 to
+// 1.09, 1.04 on average, 7 shapes).  Five and seven, else one head at a time, always are one set: 0.26 to 1.09 of the time
+// from 10 MB, 0.68 on average (16 kv heads of 4096 tokens, 7 heads, 17.2 -> 12.8 us), though 1.05 to 1.50 below 4 MB, 1.27 on
+// average (7 heads, 1 kv head x 6250, d = 64, 6.5 -> 8.5).
+// Rows of different lengths count as so many of the longest, like the rest of their plan (by what they read 16 rows of 300 to
+// 8000 tokens, 8 kv heads, would take 26.5 instead of 30.7 us, but 24 of 600 to 6000, 4 kv heads, 21.0 instead of 17.2).
 inline int most_heads(const Shape& s, int limit) {
   int hb = s.gh < limit ? s.gh : limit;
   while (s.gh % hb) --hb;
@@ -84,7 +92,10 @@ inline int most_heads(const Shape& s, int limit) {
 }
 inline int heads_per_group(const Shape& s, int64_t bytes_read) {
   const int many = most_heads(s, 8), few = most_heads(s, 4);
-  return 2 * few >= many && bytes_read < 24000000 ? few : many;
+  if (few == 1) return many;
+  if (3 * many <= 5 * few) return few;
+  const int64_t saved = bytes_read * (s.gh / few - s.gh / many);
+  return bytes_read < 24000000 && (many <= 2 * few || saved < 24000000) ? few : many;
 }
 
 // Whether the values' codes, scales and zero-points are read past the caches (non-temporal).  They are read once a launch, by

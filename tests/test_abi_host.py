@@ -258,6 +258,19 @@ def test_few_items_get_one_split_of_8_wavefronts():
     assert plan(8 * 32, 128, group=128, fp_budget=256) == (8, 1)
 
 
+def test_query_heads_of_a_workgroup():
+    """By the number of query heads of a kv head and by what the launch reads."""
+    def heads(gh, rows, n_q):
+        p = B.logquant_decode_plan(_cfg(B=rows, Hq=8 * gh, Hkv=8, q_capacity=131072), 140, n_q)
+        return p.bytes_read, gh * 8 * rows // (p.blocks // p.splits)
+    for gh, few, many, line in ((8, 4, 8, 24e6), (16, 4, 8, 24e6), (6, 3, 6, 24e6), (18, 3, 6, 24e6), (10, 2, 5, 8e6), (14, 2, 7, 4.8e6)):
+        for rows, n_q in ((1, 512), (1, 4992), (1, 5888), (1, 9600), (1, 10368), (2, 14848), (2, 15424), (8, 8192)):
+            b, h = heads(gh, rows, n_q)
+            assert h == (few if b < line else many), (gh, b)
+    for gh, only in ((4, 4), (3, 3), (9, 3), (12, 4), (15, 3), (20, 4), (5, 5), (7, 7), (11, 1), (13, 1)):
+        assert {heads(gh, 1, 512)[1], heads(gh, 8, 8192)[1]} == {only}
+
+
 def test_many_splits_of_two_sets_of_query_heads_have_workgroups_of_8():
     def plan(rows, Hkv, n_q, **kw):
         p = B.logquant_decode_plan(_cfg(B=rows, Hq=8 * Hkv, Hkv=Hkv, q_capacity=131072, **kw), 140, n_q)
