@@ -269,12 +269,8 @@ __device__ __forceinline__ float ld_dev(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// CACHE: how caches treat the line; NT: it is not needed again
-constexpr int NT = 2;
-template <int N> struct Cache { static constexpr int value = N; };
-template <int CACHE = 0>
 __device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
-  const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, CACHE);
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 __device__ __forceinline__ void buffer_store16(uint4 x, __amdgpu_buffer_rsrc_t rs, int voff, int soff) {
@@ -389,13 +385,12 @@ template <int KIND> struct SeqArgs { SeqState e[SEQ_CHUNK]; };
 template <> struct SeqArgs<EQUAL> {};
 
 // PROG: how fp rows and tiles are dealt to the wavefronts, see lq_schedule.h.
-// V_CACHE: how the values' loads ask to be cached (NT where streams_values).
 // NH: sets of four query heads that a workgroup works on side by side, P.hb heads in all.  Two sets share the loads of a
 // tile and the codes once they are unpacked; each has its own q*s, probabilities and sums (250 registers for d = 128, none
 // spilled but 4 to 5 with padding, 4 bits and G = 32).  Eight heads per kv head in two workgroups of four were bound by
 // unpacking and by reading every byte twice: 8 kv heads x 9 rows x 49079 tokens, d = 96, 104 -> 83 us a launch, 64 x 8192,
 // d = 128, 24.8 -> 20.5 (heads_per_group says when).
-template <bool BF16, int D, int G, int NWB, int BITS, int KIND, int PROG, int NH, int V_CACHE>
+template <bool BF16, int D, int G, int NWB, int BITS, int KIND, int PROG, int NH>
 __global__ void __launch_bounds__(64 * NWB, NWB == 12 ? 3 : 2)
 attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   constexpr bool ONE = PROG == ONE_SPLIT, DRAW = PROG == DRAWN;
@@ -713,19 +708,18 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
     const auto rs_kz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kzb), 0, kmeta_bytes, 0x00020000);
     const auto rs_vs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vsb), 0, vmeta_bytes, 0x00020000);
     const auto rs_vz = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vzb), 0, vmeta_bytes, 0x00020000);
-    auto load_words = [&](auto cache, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
-      constexpr int HOW = decltype(cache)::value;
+    auto load_words = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
       Words<WPL> r;
 #pragma unroll
       for (int i = 0; i + 4 <= WPL; i += 4) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff + 4 * i, (int)soff, HOW);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff + 4 * i, (int)soff, 0);
         r.w[i] = v[0]; r.w[i + 1] = v[1]; r.w[i + 2] = v[2]; r.w[i + 3] = v[3];
       }
       if constexpr (WPL % 4 == 3) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)voff + 4 * (WPL - 3), (int)soff, HOW);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs, (int)voff + 4 * (WPL - 3), (int)soff, 0);
         r.w[WPL - 3] = v[0]; r.w[WPL - 2] = v[1]; r.w[WPL - 1] = v[2];
       } else if constexpr (WPL % 4 == 2) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff + 4 * (WPL - 2), (int)soff, HOW);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff + 4 * (WPL - 2), (int)soff, 0);
         r.w[WPL - 2] = v[0]; r.w[WPL - 1] = v[1];
       }
       return r;
@@ -764,14 +758,14 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
       const int t = pl.t;
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2)
-        T.kc[b2] = load_words(Cache<0>(), rs_kc, b2 ? k_off2 | pl.dead : code_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
+        T.kc[b2] = load_words(rs_kc, b2 ? k_off2 | pl.dead : code_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
     };
     auto load_v = [&](Tile& T, const Place& pl, int b2) {
       const int t = pl.t;
       const uint32_t c_off = b2 ? v_off2 | pl.dead : code_off, m_off = b2 ? vm_off2 | pl.dead : vm_off;
-      T.vc[b2] = load_words(Cache<V_CACHE>(), rs_vc, c_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
-      T.vs[b2] = buffer_load16<V_CACHE>(rs_vs, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
-      T.vz[b2] = buffer_load16<V_CACHE>(rs_vz, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
+      T.vc[b2] = load_words(rs_vc, c_off, (uint32_t)t * (2 * 64 * WPL * 4) + b2 * (64 * WPL * 4));
+      T.vs[b2] = buffer_load16(rs_vs, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
+      T.vz[b2] = buffer_load16(rs_vz, (int)m_off, (int)((uint32_t)t * (2 * NGC * 32 * 2) + b2 * (NGC * 32 * 2)));
     };
     // Tiles that are drawn.  The first two of a wavefront without units are fixed, and the loads of the first go out
     // before anything else touches memory.  The later tiles are dealt out dynamically, so that wavefronts that start
@@ -1322,57 +1316,57 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   }
 }
 
-template <bool BF16, int D, int NWB, int BITS, int NH, int V_CACHE, int KIND, int PROG>
+template <bool BF16, int D, int NWB, int BITS, int NH, int KIND, int PROG>
 static hipError_t launch_mfma_g(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   SeqArgs<KIND> S;
   if constexpr (KIND != EQUAL)
     if (seq && seq->in_args())
       for (int i = 0; i < seq->n; ++i) S.e[i] = seq->host[i];
   switch (s.G) {
-    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, KIND, PROG, NH, V_CACHE>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, KIND, PROG, NH, V_CACHE>), grid, dim3(64 * NWB), 0, st, P, S); break;
-    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, KIND, PROG, NH, V_CACHE>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 32: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 32, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    case 64: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 64, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
+    default: hipLaunchKernelGGL((attn_mfma_kernel<BF16, D, 128, NWB, BITS, KIND, PROG, NH>), grid, dim3(64 * NWB), 0, st, P, S); break;
   }
   return launch_status(__func__);
 }
 
-template <bool BF16, int D, int NWB, int BITS, int NH, int V_CACHE, int PROG>
+template <bool BF16, int D, int NWB, int BITS, int NH, int PROG>
 static hipError_t launch_mfma_k(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   if constexpr (PROG != DRAWN || NWB != 4)
-    if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, NH, V_CACHE, PADDED, PROG>(s, P, seq, grid, st);
+    if (s.Wq != s.W) return launch_mfma_g<BF16, D, NWB, BITS, NH, PADDED, PROG>(s, P, seq, grid, st);
   if constexpr (PROG != DRAWN)   // (with counts per row each row decides for itself whether it draws)
-    if (seq) return launch_mfma_g<BF16, D, NWB, BITS, NH, V_CACHE, PER_ROW, PROG>(s, P, seq, grid, st);
-  return launch_mfma_g<BF16, D, NWB, BITS, NH, V_CACHE, EQUAL, PROG>(s, P, seq, grid, st);
+    if (seq) return launch_mfma_g<BF16, D, NWB, BITS, NH, PER_ROW, PROG>(s, P, seq, grid, st);
+  return launch_mfma_g<BF16, D, NWB, BITS, NH, EQUAL, PROG>(s, P, seq, grid, st);
 }
 
-template <bool BF16, int D, int NWB, int BITS, int NH, int V_CACHE>
+template <bool BF16, int D, int NWB, int BITS, int NH>
 static hipError_t launch_mfma_p(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   const int NW = P.splits * NWB, TF = (P.n_fp + 31) / 32, TQ = P.tiles;
-  if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, NH, V_CACHE, ONE_SPLIT>(s, P, seq, grid, st);
+  if (P.splits == 1 && P.n_q > 0) return launch_mfma_k<BF16, D, NWB, BITS, NH, ONE_SPLIT>(s, P, seq, grid, st);
   // (With counts per sequence each row decides for itself, in the kernel.  Padded rows of one length are not planned with
   // 4 wavefronts: forced to, they take their tiles in a fixed order.)
   if (P.splits > 1 && !seq && !(NWB == 4 && s.Wq != s.W) && draws_tiles(P.dynamic, NW, P.nwf, TF, TQ))
-    return launch_mfma_k<BF16, D, NWB, BITS, NH, V_CACHE, DRAWN>(s, P, seq, grid, st);
+    return launch_mfma_k<BF16, D, NWB, BITS, NH, DRAWN>(s, P, seq, grid, st);
   if constexpr (NWB == 8)
     if (!keeps_units_together(NW, P.nwf, TQ, (int64_t)grid.x * grid.y * grid.z >= compute_units()))
-      return launch_mfma_k<BF16, D, NWB, BITS, NH, V_CACHE, APART>(s, P, seq, grid, st);
-  return launch_mfma_k<BF16, D, NWB, BITS, NH, V_CACHE, BY_SPLIT>(s, P, seq, grid, st);
+      return launch_mfma_k<BF16, D, NWB, BITS, NH, APART>(s, P, seq, grid, st);
+  return launch_mfma_k<BF16, D, NWB, BITS, NH, BY_SPLIT>(s, P, seq, grid, st);
 }
 
-template <bool BF16, int NWB, int BITS, int NH, int V_CACHE>
+template <bool BF16, int NWB, int BITS, int NH>
 static hipError_t launch_mfma_d(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   switch (s.d) {
-    case 64: return launch_mfma_p<BF16, 64, NWB, BITS, NH, V_CACHE>(s, P, seq, grid, st);
-    case 96: return launch_mfma_p<BF16, 96, NWB, BITS, NH, V_CACHE>(s, P, seq, grid, st);
-    default: return launch_mfma_p<BF16, 128, NWB, BITS, NH, V_CACHE>(s, P, seq, grid, st);
+    case 64: return launch_mfma_p<BF16, 64, NWB, BITS, NH>(s, P, seq, grid, st);
+    case 96: return launch_mfma_p<BF16, 96, NWB, BITS, NH>(s, P, seq, grid, st);
+    default: return launch_mfma_p<BF16, 128, NWB, BITS, NH>(s, P, seq, grid, st);
   }
 }
 
 // One source file for each of these (lq_attn_mfma_w*.hip): several hundred kernels in all, which as one file took many minutes.
-template <int NWB, int BITS, int NH, int V_CACHE>
+template <int NWB, int BITS, int NH>
 hipError_t launch_mfma_t(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  return s.bf16 ? launch_mfma_d<true, NWB, BITS, NH, V_CACHE>(s, P, seq, grid, st)
-                : launch_mfma_d<false, NWB, BITS, NH, V_CACHE>(s, P, seq, grid, st);
+  return s.bf16 ? launch_mfma_d<true, NWB, BITS, NH>(s, P, seq, grid, st)
+                : launch_mfma_d<false, NWB, BITS, NH>(s, P, seq, grid, st);
 }
 
 }  // namespace lq

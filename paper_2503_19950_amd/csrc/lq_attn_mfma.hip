@@ -5,25 +5,23 @@
 
 namespace lq {
 
-extern template hipError_t launch_mfma_t<12, 2, 1, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 2, 1, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 4, 1, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 2, 1, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 4, 1, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<12, 2, 1, NT>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 2, 1, NT>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 2, 1, NT>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 2, 2, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<8, 4, 2, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 2, 2, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
-extern template hipError_t launch_mfma_t<4, 4, 2, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<12, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 4, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 2, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 4, 1>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<8, 4, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+extern template hipError_t launch_mfma_t<4, 4, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
 
-template <int BITS, int NH, int V_CACHE>
-static hipError_t launch_waves(const Shape& s, const AttnParams& P, int waves_per_block, const SeqArg* seq, dim3 grid, hipStream_t st) {
-  if constexpr (NH == 1 && BITS == 2)
-    if (waves_per_block == 12) return launch_mfma_t<12, BITS, NH, V_CACHE>(s, P, seq, grid, st);
-  if (waves_per_block == 4) return launch_mfma_t<4, BITS, NH, V_CACHE>(s, P, seq, grid, st);
-  return launch_mfma_t<8, BITS, NH, V_CACHE>(s, P, seq, grid, st);
+template <int NH>
+static hipError_t launch_heads(const Shape& s, const AttnParams& P, int waves_per_block, const SeqArg* seq, dim3 grid, hipStream_t st) {
+  if constexpr (NH == 1)
+    if (waves_per_block == 12) return launch_mfma_t<12, 2, 1>(s, P, seq, grid, st);
+  if (waves_per_block == 4)
+    return s.bits == 4 ? launch_mfma_t<4, 4, NH>(s, P, seq, grid, st) : launch_mfma_t<4, 2, NH>(s, P, seq, grid, st);
+  return s.bits == 4 ? launch_mfma_t<8, 4, NH>(s, P, seq, grid, st) : launch_mfma_t<8, 2, NH>(s, P, seq, grid, st);
 }
 
 // seq == nullptr: every sequence has the counts of `c` and the live buffer c.cur;
@@ -61,10 +59,7 @@ hipError_t launch_decode_attn_mfma(const Shape& s, const lq_cache& c, const void
   P.across = groups % 8 == 0 ? 8 : 1;
   P.div_subgroups.set(s.gh / P.hb); P.div_kv_heads.set(s.Hkv);
   const dim3 grid(P.across, plan.splits, groups / P.across);
-  const int wpb = plan.waves_per_block;
-  if (P.hb > 4) return s.bits == 4 ? launch_waves<4, 2, 0>(s, P, wpb, seq, grid, st) : launch_waves<2, 2, 0>(s, P, wpb, seq, grid, st);
-  if (s.bits == 4) return launch_waves<4, 1, 0>(s, P, wpb, seq, grid, st);
-  return streams_values(s, P.hb, plan.bytes_read) ? launch_waves<2, 1, NT>(s, P, wpb, seq, grid, st) : launch_waves<2, 1, 0>(s, P, wpb, seq, grid, st);
+  return P.hb > 4 ? launch_heads<2>(s, P, plan.waves_per_block, seq, grid, st) : launch_heads<1>(s, P, plan.waves_per_block, seq, grid, st);
 }
 
 }  // namespace lq

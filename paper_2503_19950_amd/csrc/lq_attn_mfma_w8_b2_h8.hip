@@ -2,5 +2,5 @@
 #include "lq_attn_mfma.h"
 
 namespace lq {
-template hipError_t launch_mfma_t<8, 2, 2, 0>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
+template hipError_t launch_mfma_t<8, 2, 2>(const Shape&, const AttnParams&, const SeqArg*, dim3, hipStream_t);
 }  // namespace lq

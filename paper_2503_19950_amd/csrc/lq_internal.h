@@ -98,19 +98,6 @@ inline int heads_per_group(const Shape& s, int64_t bytes_read) {
   return bytes_read < 24000000 && (many <= 2 * few || saved < 24000000) ? few : many;
 }
 
-// Whether the values' codes, scales and zero-points are read past the caches (non-temporal).  They are read once a launch, by
-// one load a line, and the layers of a model together are beyond the 256 MB of the last-level cache: lines that nobody
-// will find there again cost the others a place and the memory traffic a share.  Only the values, so that a program with
-// few layers still finds its keys there: with all of it, 64 rows of 4096 tokens, one layer, 248 MB, took 5900 -> 6297 us for
-// 128 steps, with the values alone 5757 -> 5784.  From 64 MB, where the caches of four layers no longer fit (four layers of
-// 131072 tokens, 86 MB each, 95.9 -> 91.3 us, with W = 42 121.1 -> 118.7; of 8 x 8192, 57 MB, one step on three sets in
-// turn 65.1 -> 62.5, but step after step on one set 64.4 -> 67.0), to 160 MB, above which it gains nothing (1.1 GB 194.0
-// against 194.5).  Not where several workgroups read the same rows (eight heads as two workgroups of four 55.5 -> 59.2)
-// and not with 4 bits, where two loads share a line (35.0 -> 36.7, keys and values).
-inline bool streams_values(const Shape& s, int hb, int64_t bytes_read) {
-  return s.bits == 2 && hb == s.gh && hb <= 4 && bytes_read >= 64000000 && bytes_read < 160000000;
-}
-
 // Upper bound on context splits per (b, kv head) that decode_attn may use.
 int max_splits(const Shape& s);
 
