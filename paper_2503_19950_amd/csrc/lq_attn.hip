@@ -134,14 +134,13 @@ void plan_decode(const Shape& s, int n_fp, int n_q, lq_plan* plan, Rows rows) {
     best_splits = 1;
     keep_8 = true;
   }
-  // Twelve wavefronts per workgroup (three per SIMD) pay off for long contexts on few
-  // groups: measured on 131072 tokens x 8 kv heads 25.7 against 27.3 us, but slower
-  // than 8 with fewer than ~6 tiles per wavefront and slower than 4 when every
-  // compute unit holds two workgroups anyway.  Only built for 2-bit codes (with 4-bit
-  // codes it was measured to make no difference: 37.3 against 37.2 us).
-  // (and only when the launch fits the chip in one round: with more workgroups than
-  // compute units, as in a batch of 64 rows with per-row counts, 8 is faster: 49 against 54 us)
-  // (and not for more than four query heads, whose registers would not fit)
+  // Twelve wavefronts per workgroup (three per SIMD) for long contexts on few groups: not with fewer than six tiles to a
+  // wavefront, and only when the launch fits the chip in one round (64 rows with per-row counts 54 us, with 8 49).  They
+  // cover latency with a third wavefront, but where the loads bound the launch that no longer pays: of 70 shapes inside the
+  // rule, 8 take 0.82 to 1.06 of their time with several splits (0.98 on average, 37 shapes; 98209 tokens x 8 kv
+  // heads, four layers, 19.6 us a launch with 12, 17.8 with 8), with padding 0.92 to 1.09 (1.00, 30 shapes), in one split 0.96 to 0.98 (3 shapes).
+  // Only built for 2-bit codes (with 4-bit codes it made no difference: 37.3 against 37.2 us), and not for more than four
+  // query heads, whose registers would not fit.
   if (s.bits == 2 && hb <= 4 && (force_wpb == 12 || (!force_wpb && best_wpb == 8 && !keep_8 && units / (best_splits * 8.0) >= 6.0 &&
                                           (int64_t)best_splits * groups <= cus)))
     best_wpb = 12;

@@ -1211,13 +1211,12 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   }
   __syncthreads();
   if (!is_last) return;
-  // Up to NI * RPI splits one wavefront merges a head (several in turn where there are fewer wavefronts).  With more of them all wavefronts merge, those with wave % hb == h
-  // sharing the rows (splits) of head h, and their sums meet in LDS: 0.8 us less from the ticket to the end at 32 splits,
+  // Up to NI * RPI splits one wavefront merges a head (several in turn where there are fewer wavefronts).  With more of them
+  // NWB / hb wavefronts share the rows (splits) of a head, the others idle, and their sums meet in LDS: 0.8 us less from the ticket to the end at 32 splits,
   // but 0.6 us more at few (3 splits of 512 tokens 9.7 instead of 9.0 us a launch, 8 splits of 2048 tokens at d = 64
   // 8.7 instead of 8.0).  The partials are read past the caches (device-coherent loads), 16 bytes per lane so that the
   // address unit sees few, wide instructions, and the loads of a batch are issued before anything is consumed: the merge
   // then costs about one memory round trip.
-  static_assert(NWB % 4 == 0, "every head gets the same number of wavefronts");
   constexpr int PR = D + 4;                    // floats per partial row
   constexpr int C4 = D / 4;                    // 16-byte chunks per row
   constexpr int RPI = 64 / C4;                 // rows covered by one wave-level load
@@ -1228,7 +1227,7 @@ attn_mfma_kernel(const AttnParams P, const SeqArgs<KIND> S) {
   const int parts = alone ? 1 : NWB / P.hb;
   const int64_t gstride = (int64_t)P.gh * PR;  // floats between consecutive splits
   float* sum = &o_lds[0][0][0];                // [part][head][D] (o_lds is free again)
-  static_assert(sizeof(o_lds) >= NWB * D * sizeof(float), "parts * hb = NWB rows of sums");
+  static_assert(sizeof(o_lds) >= NWB * D * sizeof(float), "parts * hb rows of sums, at most NWB");
   for (int hp = wave; hp < P.hb * parts; hp += NWB) {   // (head, part): several heads in turn where there are fewer wavefronts
     const int head = hp % P.hb, part = hp / P.hb;
     const float* gbase = P.ws + ((int64_t)bh * P.splits * P.gh + hsub * P.hb + head) * PR;
@@ -1362,7 +1361,7 @@ static hipError_t launch_mfma_d(const Shape& s, const AttnParams& P, const SeqAr
   }
 }
 
-// One source file for each of these (lq_attn_mfma_w*.hip): several hundred kernels in all, which as one file took many minutes.
+// One source file for each of these (lq_attn_mfma_w*.hip): 1440 kernels in all, which as one file took many minutes.
 template <int NWB, int BITS, int NH>
 hipError_t launch_mfma_t(const Shape& s, const AttnParams& P, const SeqArg* seq, dim3 grid, hipStream_t st) {
   return s.bf16 ? launch_mfma_d<true, NWB, BITS, NH>(s, P, seq, grid, st)
